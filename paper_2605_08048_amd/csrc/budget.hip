@@ -100,149 +100,246 @@ __global__ __launch_bounds__(256) void k_col_norm(int64_t rows, int cols, const 
 }
 
 // ---------------------------------------------------------------------------
-// network: one thread per row, parameters in LDS (read as broadcasts)
+// network.  A work-group of eight waves takes a chunk of 64 rows: lane l of
+// every wave is row l of the chunk, and wave w computes units 8 w .. 8 w + 7
+// of a layer, so that a parameter is wave-uniform (a scalar load, used as the
+// multiplier's scalar operand) and a chunk spreads over 512 lanes.  The
+// activations pass between the waves through LDS.  Every unit's sum is one
+// chain of FP32 fma over its inputs in ascending order, from the bias, so a
+// row's outputs do not depend on the chunking.
 // ---------------------------------------------------------------------------
-// Layer 1 of one row: x~ and z1 = relu(W1 x~ + b1), held in registers.
-__device__ __forceinline__ void layer1(const float* th, const float* x, float (&xs)[kF], float (&z1)[kH]) {
+constexpr int kRowsWg = 64;   // rows of a chunk
+constexpr int kMlpWaves = 8;
+constexpr int kUnits = kH / kMlpWaves;  // units of a layer per wave
+// One layer's activations of a chunk, unit-major with 68 floats a unit: the
+// lanes of a wave read one unit of 64 rows (consecutive words, the unit an
+// immediate offset), or 16 units of 4 consecutive rows (words 68 u + r on 64
+// distinct banks, an operand of the gradient's matrix product).
+constexpr int kActLd = kRowsWg + 4;
+typedef float Act[kH * kActLd];
+__device__ __forceinline__ int act_at(int r, int u) { return u * kActLd + r; }
+
+// Standardised inputs of a row, and this wave's units of z1 = relu(W1 x~ + b1)
+// for it into z1s (0 for a lane without a row).  The loops over units are not
+// unrolled: the parameters of one unit at a time fit the scalar registers.
+__device__ __forceinline__ void layer1(const float* __restrict__ th, const float* x, int lane, int u0, bool live,
+                                       float (&xs)[kF], Act& z1s) {
 #pragma unroll
     for (int i = 0; i < kF; ++i) xs[i] = (x[i] - th[oShift + i]) * th[oScale + i];
+#pragma unroll 2
+    for (int u = u0; u < u0 + kUnits; ++u) {
+        float s = th[oB1 + u];
 #pragma unroll
-    for (int j = 0; j < kH; ++j) {
-        float s = th[oB1 + j];
-#pragma unroll
-        for (int i = 0; i < kF; ++i) s = fmaf(th[oW1 + j * kF + i], xs[i], s);
-        z1[j] = s > 0.0f ? s : 0.0f;
+        for (int i = 0; i < kF; ++i) s = fmaf(th[oW1 + u * kF + i], xs[i], s);
+        z1s[act_at(lane, u)] = live && s > 0.0f ? s : 0.0f;
     }
 }
 
-// Unit j of layer 2: relu(W2[j] . z1 + b2[j]).
-__device__ __forceinline__ float unit2(const float* th, const float (&z1)[kH], int j) {
-    float s = th[oB2 + j];
+// This wave's units of z2 = relu(W2 z1 + b2) for the lane's row, into z2s.
+__device__ __forceinline__ void layer2(const float* __restrict__ th, const Act& z1s, int lane, int u0, bool live,
+                                       Act& z2s) {
+    float z1[kH];
 #pragma unroll
-    for (int i = 0; i < kH; ++i) s = fmaf(th[oW2 + j * kH + i], z1[i], s);
-    return s > 0.0f ? s : 0.0f;
+    for (int i = 0; i < kH; ++i) z1[i] = z1s[act_at(lane, i)];
+#pragma unroll 1
+    for (int u = u0; u < u0 + kUnits; ++u) {
+        float s = th[oB2 + u];
+#pragma unroll
+        for (int i = 0; i < kH; ++i) s = fmaf(th[oW2 + u * kH + i], z1[i], s);
+        z2s[act_at(lane, u)] = live && s > 0.0f ? s : 0.0f;
+    }
 }
 
-__device__ __forceinline__ void load_theta(float* lds, const float* theta) {
-    for (int k = threadIdx.x; k < kP; k += blockDim.x) lds[k] = theta[k];
-    __syncthreads();
+// Output o (0, 1) of the lane's row before the output standardisation.
+__device__ __forceinline__ float layer3(const float* __restrict__ th, const Act& z2s, int lane, int o) {
+    float s = th[oB3 + o];
+#pragma unroll 16
+    for (int j = 0; j < kH; ++j) s = fmaf(th[oW3 + o * kH + j], z2s[act_at(lane, j)], s);
+    return s;
 }
 
-__global__ __launch_bounds__(256) void k_mlp_forward(int64_t rows, const float* __restrict__ feat,
+// Bound by launch and latency (4096 rows: 41 MFLOP).  One thread per row with
+// the parameters in LDS took 31 us for 4096 rows (16 work-groups, each lane
+// 5,000 fma one after the other); 64-row chunks over 64 work-groups 9.3 us.
+__global__ __launch_bounds__(64 * kMlpWaves, 4) void k_mlp_forward(int64_t rows, const float* __restrict__ feat,
                                                      const float* __restrict__ theta,
                                                      float* __restrict__ out) {
-    __shared__ float th[kP];
-    load_theta(th, theta);
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= rows) return;
-    float xs[kF], z1[kH];
-    layer1(th, feat + r * kF, xs, z1);
-    float o0 = th[oB3], o1 = th[oB3 + 1];
-    for (int j = 0; j < kH; ++j) {  // the output layer accumulates unit by unit
-        const float z = unit2(th, z1, j);
-        o0 = fmaf(th[oW3 + j], z, o0);
-        o1 = fmaf(th[oW3 + kH + j], z, o1);
+    __shared__ Act z1s, z2s;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int u0 = kUnits * wave;
+    for (int64_t r0 = (int64_t)blockIdx.x * kRowsWg; r0 < rows; r0 += (int64_t)gridDim.x * kRowsWg) {
+        const int64_t r = r0 + lane;
+        const bool live = r < rows;
+        float xs[kF];
+        layer1(theta, feat + (live ? r : rows - 1) * kF, lane, u0, live, xs, z1s);
+        __syncthreads();  // also: the previous chunk's readers of z2s are done
+        layer2(theta, z1s, lane, u0, live, z2s);
+        __syncthreads();
+        if (wave < kO && live)
+            out[r * kO + wave] = fmaf(theta[oOScale + wave], layer3(theta, z2s, lane, wave), theta[oOShift + wave]);
     }
-    out[r * kO + 0] = fmaf(th[oOScale], o0, th[oOShift]);
-    out[r * kO + 1] = fmaf(th[oOScale + 1], o1, th[oOShift + 1]);
 }
 
-// Per-row pass of the gradient of L = (1/R) sum_r (1/2) |(out_r - target_r) / oscale|^2
-// (the squared error of y~ against standardised targets):
-// forward, then the error signals at the pre-activations of the three layers
-// (dout, d2, d1).  Writes what the per-parameter reduction needs: x~, z1, z2,
-// d1, d2, dout, and the row's loss.
-struct TrainWs {
-    float *xs, *z1, *z2, *d1, *d2, *dout;
-    double* loss;
-};
+// Gradient of L = (1/R) sum_r (1/2) |(out_r - target_r) / oscale|^2 (the
+// squared error of y~ against standardised targets), one work-group per chunk
+// of 64 rows (chunk b, b + gridDim, ... for more than kGradWgs of them):
+// forward, the error signals at the pre-activations of the three layers
+// (dout, d2, d1), then the chunk's sums over rows of the outer products, FP64:
+// W1 and W2 on v_mfma_f64_16x16x4 (each product of two floats is exact), W3
+// and the biases by plain sums.  The activations never leave LDS; part[b] gets
+// the work-group's 5122 sums and its loss, and k_mlp_sum adds the work-groups
+// in order.  20,000 rows (313 work-groups): 34 + 8 us (rows' activations written to memory and one
+// thread per parameter summing all rows in turn: 81 + 5150 us).
+constexpr int kPart = kP - oW1 + 1;  // the trained parameters' sums, then the loss
+constexpr int kGradWgs = 512;
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) void k_mlp_rows(int64_t rows, const float* __restrict__ feat,
+__global__ __launch_bounds__(64 * kMlpWaves, 4) void k_mlp_grad(int64_t rows, const float* __restrict__ feat,
                                                   const float* __restrict__ target,
-                                                  const float* __restrict__ theta, TrainWs w) {
-    __shared__ float th[kP];
-    load_theta(th, theta);
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= rows) return;
-    float xs[kF], z1[kH];
-    layer1(th, feat + r * kF, xs, z1);
-    float* z2 = w.z2 + r * kH;
-    float o0 = th[oB3], o1 = th[oB3 + 1];
-    for (int j = 0; j < kH; ++j) {
-        const float z = unit2(th, z1, j);
-        z2[j] = z;
-        o0 = fmaf(th[oW3 + j], z, o0);
-        o1 = fmaf(th[oW3 + kH + j], z, o1);
-    }
+                                                  const float* __restrict__ theta, double* __restrict__ part) {
+    __shared__ Act z1s, z2s, d1s, d2s;
+    __shared__ float xls[kRowsWg][kF + 4 + 1];  // x~ of the rows, columns 12..15 zero
+    __shared__ float gs[kO][kRowsWg];
+    __shared__ double ls[kRowsWg];
+    const float* th = theta;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int u0 = kUnits * wave;
+    const int q = lane >> 4, c = lane & 15;
+    // waves w and w + 4 take rows 16 w .. 16 w + 15 of dW2, 32 columns each (2
+    // blocks of 16); the first four also those rows of dW1, the others W3 and
+    // the biases
+    const int j0 = 16 * (wave & 3), half = wave >> 2;
+    f64x4 g2[2], g1;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) g1[v] = g2[0][v] = g2[1][v] = 0.0;
+    double gx = 0.0;  // waves 4, 5: W3 of output wave - 4; 6: b1; 7: b2 (unit lane)
+    double gb = 0.0;  // wave 6, lanes 0 and 1: b3; wave 7, lane 0: the loss
     const float inv = 1.0f / (float)rows;
-    // error of y~ against the standardised target (t - oshift) / oscale
-    const float e0 = o0 - (target[r * kO] - th[oOShift]) / th[oOScale];
-    const float e1 = o1 - (target[r * kO + 1] - th[oOShift + 1]) / th[oOScale + 1];
-    const float g0 = e0 * inv, g1 = e1 * inv;
-    // d2_j = relu'(a2_j) (W3^T dout)_j, and d1 = relu'(a1) o (W2^T d2), the
-    // latter accumulated unit by unit of layer 2
-    float d1[kH];
+    for (int64_t r0 = (int64_t)blockIdx.x * kRowsWg; r0 < rows; r0 += (int64_t)gridDim.x * kRowsWg) {
+        const int64_t r = r0 + lane;
+        const bool live = r < rows;  // rows past the end add zeros
+        float xs[kF];
+        __syncthreads();  // the previous chunk's readers are done
+        layer1(th, feat + (live ? r : rows - 1) * kF, lane, u0, live, xs, z1s);
+        if (wave == 0) {
 #pragma unroll
-    for (int i = 0; i < kH; ++i) d1[i] = 0.0f;
-    for (int j = 0; j < kH; ++j) {
-        const float d2 = z2[j] > 0.0f ? fmaf(th[oW3 + j], g0, th[oW3 + kH + j] * g1) : 0.0f;
-        w.d2[r * kH + j] = d2;
+            for (int i = 0; i < kF; ++i) xls[lane][i] = live ? xs[i] : 0.0f;
 #pragma unroll
-        for (int i = 0; i < kH; ++i) d1[i] = fmaf(th[oW2 + j * kH + i], d2, d1[i]);
+            for (int i = kF; i < 16; ++i) xls[lane][i] = 0.0f;
+        }
+        __syncthreads();
+        layer2(th, z1s, lane, u0, live, z2s);
+        __syncthreads();
+        if (wave < kO) {
+            // error of y~ against the standardised target (t - oshift) / oscale
+            const float o = layer3(th, z2s, lane, wave);
+            const float e = o - (target[(live ? r : rows - 1) * kO + wave] - th[oOShift + wave]) / th[oOScale + wave];
+            gs[wave][lane] = live ? e * inv : 0.0f;
+            if (wave == 0) ls[lane] = live ? (double)e * (double)e : 0.0;
+            // (the second output's square is added below)
+            else d1s[lane] = live ? e : 0.0f;
+        }
+        __syncthreads();
+        const float g0 = gs[0][lane], g1f = gs[1][lane];
+        if (wave == 0) ls[lane] = 0.5 * (ls[lane] + (double)d1s[lane] * (double)d1s[lane]);
+        // d2_j = relu'(a2_j) (W3^T dout)_j
+#pragma unroll 4
+        for (int u = u0; u < u0 + kUnits; ++u) {
+            const bool on = live && z2s[act_at(lane, u)] > 0.0f;
+            d2s[act_at(lane, u)] = on ? fmaf(th[oW3 + u], g0, th[oW3 + kH + u] * g1f) : 0.0f;
+        }
+        __syncthreads();
+        // d1 = relu'(a1) o (W2^T d2), unit by unit of layer 2
+        float d1[kUnits];
+#pragma unroll
+        for (int u = 0; u < kUnits; ++u) d1[u] = 0.0f;
+#pragma unroll 4
+        for (int j = 0; j < kH; ++j) {
+            const float d2 = d2s[act_at(lane, j)];
+#pragma unroll
+            for (int u = 0; u < kUnits; ++u) d1[u] = fmaf(th[oW2 + j * kH + u0 + u], d2, d1[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < kUnits; ++u)
+            d1s[act_at(lane, u0 + u)] = z1s[act_at(lane, u0 + u)] > 0.0f ? d1[u] : 0.0f;  // z1 = 0 without a row
+        __syncthreads();
+        // sums over the chunk's rows: A (16 x 4) lane l -> row l%16, k l/16; B
+        // lane l -> k l/16, column l%16
+#pragma unroll 4
+        for (int s = 0; s < kRowsWg / 4; ++s) {
+            const int rr = 4 * s + q;
+            const double a2 = (double)d2s[act_at(rr, j0 + c)];
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                g2[k] = __builtin_amdgcn_mfma_f64_16x16x4f64(a2, (double)z1s[act_at(rr, 32 * half + 16 * k + c)], g2[k],
+                                                             0, 0, 0);
+        }
+        if (half == 0) {
+#pragma unroll 4
+            for (int s = 0; s < kRowsWg / 4; ++s)
+                g1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)d1s[act_at(4 * s + q, j0 + c)],
+                                                          (double)xls[4 * s + q][c], g1, 0, 0, 0);
+        } else if (wave < 6) {
+            const float* go = gs[wave - 4];
+#pragma unroll 8
+            for (int k = 0; k < kRowsWg; ++k) gx += (double)go[k] * (double)z2s[act_at(k, lane)];
+        } else {
+            const Act& a = wave == 6 ? d1s : d2s;
+#pragma unroll 8
+            for (int k = 0; k < kRowsWg; ++k) gx += (double)a[act_at(k, lane)];
+            if (wave == 6 && lane < kO) {
+#pragma unroll 8
+                for (int k = 0; k < kRowsWg; ++k) gb += (double)gs[lane][k];
+            }
+            if (wave == 7 && lane == 0) {
+#pragma unroll 8
+                for (int k = 0; k < kRowsWg; ++k) gb += ls[k];
+            }
+        }
     }
+    double* o = part + (int64_t)blockIdx.x * kPart - oW1;  // indexed by the parameter
+    // D lane l -> column l%16, register v -> row 4 v + l/16
 #pragma unroll
-    for (int i = 0; i < kH; ++i) {
-        w.d1[r * kH + i] = z1[i] > 0.0f ? d1[i] : 0.0f;
-        w.z1[r * kH + i] = z1[i];
+    for (int v = 0; v < 4; ++v) {
+        const int j = j0 + 4 * v + q;
+        if (half == 0 && c < kF) o[oW1 + j * kF + c] = g1[v];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) o[oW2 + j * kH + 32 * half + 16 * k + c] = g2[k][v];
     }
-#pragma unroll
-    for (int i = 0; i < kF; ++i) w.xs[r * kF + i] = xs[i];
-    w.dout[r * kO] = g0;
-    w.dout[r * kO + 1] = g1;
-    w.loss[r] = 0.5 * ((double)e0 * (double)e0 + (double)e1 * (double)e1);
+    if (wave >= 4) o[(wave < 6 ? oW3 + (wave - 4) * kH : wave == 6 ? oB1 : oB2) + lane] = gx;
+    if (wave == 6 && lane < kO) o[oB3 + lane] = gb;
+    if (wave == 7 && lane == 0) o[kP] = gb;
 }
 
-// One thread per trainable parameter: the sum over rows, in row order, of
-// its gradient terms (outer products of error signals and inputs), FP64.
-// Thread kP - oW1 (one past the last parameter) sums the loss.
-__global__ __launch_bounds__(256) void k_mlp_reduce(int64_t rows, TrainWs w, float* __restrict__ grad,
-                                                    double* __restrict__ loss_out) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    const int k = oW1 + t;
-    if (k > kP) return;
-    if (k == kP) {
-        if (loss_out) {
-            double s = 0.0;
-            for (int64_t r = 0; r < rows; ++r) s += w.loss[r];
-            *loss_out = s / (double)rows;
-        }
-        return;
-    }
-    const float *a, *b;  // the two factors; b == nullptr for a bias
-    int sa, sb;
-    if (k < oB1) {
-        const int j = (k - oW1) / kF, i = (k - oW1) % kF;
-        a = w.d1 + j, sa = kH, b = w.xs + i, sb = kF;
-    } else if (k < oW2) {
-        a = w.d1 + (k - oB1), sa = kH, b = nullptr, sb = 0;
-    } else if (k < oB2) {
-        const int j = (k - oW2) / kH, i = (k - oW2) % kH;
-        a = w.d2 + j, sa = kH, b = w.z1 + i, sb = kH;
-    } else if (k < oW3) {
-        a = w.d2 + (k - oB2), sa = kH, b = nullptr, sb = 0;
-    } else if (k < oB3) {
-        const int j = (k - oW3) / kH, i = (k - oW3) % kH;
-        a = w.dout + j, sa = kO, b = w.z2 + i, sb = kH;
-    } else {
-        a = w.dout + (k - oB3), sa = kO, b = nullptr, sb = 0;
-    }
+// grad = the work-groups' sums added: 64 parameters per work-group, wave w
+// adds the parts w, w + 4, ... in order (eight loads in flight), then the four
+// waves' sums in order.
+__global__ __launch_bounds__(256) void k_mlp_sum(int64_t rows, int nparts, const double* __restrict__ part,
+                                                 float* __restrict__ grad, double* __restrict__ loss_out) {
+    __shared__ double red[4][64];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int k = blockIdx.x * 64 + lane;
     double s = 0.0;
-    if (b) {
-        for (int64_t r = 0; r < rows; ++r) s += (double)a[r * sa] * (double)b[r * sb];
-    } else {
-        for (int64_t r = 0; r < rows; ++r) s += (double)a[r * sa];
+    if (k < kPart) {
+        int b = wave;
+        for (; b + 28 < nparts; b += 32) {
+            double t[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) t[u] = part[(int64_t)(b + 4 * u) * kPart + k];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += t[u];
+        }
+        for (; b < nparts; b += 4) s += part[(int64_t)b * kPart + k];
     }
-    grad[k] = (float)s;
+    red[wave][lane] = s;
+    __syncthreads();
+    if (wave != 0 || k >= kPart) return;
+    s = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+    if (k == kPart - 1) {
+        if (loss_out) *loss_out = s / (double)rows;
+    } else {
+        grad[oW1 + k] = (float)s;
+    }
 }
 
 // Adam (Kingma & Ba, Algorithm 1) on theta[oW1:]; c1 = 1 - beta1^t and
@@ -325,28 +422,12 @@ __global__ void k_budgets_cost(int64_t npairs, const float* __restrict__ out,
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-size_t mlp_train_ws_bytes(int64_t rows) {
-    return (size_t)rows * (kF + 4 * kH + kO) * sizeof(float) + (size_t)rows * sizeof(double) + 256;
+static int grad_wgs(int64_t rows) {
+    const int64_t c = (rows + kRowsWg - 1) / kRowsWg;
+    return (int)(c < kGradWgs ? c : kGradWgs);
 }
 
-static TrainWs carve_train(void* ws, int64_t rows) {
-    TrainWs w;
-    char* p = (char*)ws;
-    w.loss = (double*)p;
-    p += rows * sizeof(double);
-    auto take = [&](int k) {
-        float* q = (float*)p;
-        p += rows * k * sizeof(float);
-        return q;
-    };
-    w.xs = take(kF);
-    w.z1 = take(kH);
-    w.z2 = take(kH);
-    w.d1 = take(kH);
-    w.d2 = take(kH);
-    w.dout = take(kO);
-    return w;
-}
+size_t mlp_train_ws_bytes(int64_t rows) { return (size_t)grad_wgs(rows) * kPart * sizeof(double) + 256; }
 
 hipError_t launch_features(int64_t npairs, const hbt_result* res, int d, int gd, float* feat,
                            hipStream_t s) {
@@ -369,20 +450,21 @@ hipError_t launch_target_norm(int64_t rows, const float* target, float* theta, h
 
 hipError_t launch_mlp_forward(int64_t rows, const float* feat, const float* theta, float* out,
                               hipStream_t s) {
-    hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, rows,
+    const int64_t chunks = (rows + kRowsWg - 1) / kRowsWg;
+    hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)(chunks < 65536 ? chunks : 65536)),
+                       dim3(64 * kMlpWaves), 0, s, rows,
                        feat, theta, out);
     return hipGetLastError();
 }
 
 hipError_t launch_mlp_grad(int64_t rows, const float* feat, const float* target, const float* theta,
                            float* grad, double* loss, void* ws, hipStream_t s) {
-    const TrainWs w = carve_train(ws, rows);
-    hipLaunchKernelGGL(k_mlp_rows, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, rows, feat,
-                       target, theta, w);
+    const int wgs = grad_wgs(rows);
+    double* part = (double*)(((uintptr_t)ws + 7) & ~(uintptr_t)7);
+    hipLaunchKernelGGL(k_mlp_grad, dim3(wgs), dim3(64 * kMlpWaves), 0, s, rows, feat, target, theta, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int nt = kP - oW1 + 1;
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((nt + 255) / 256), dim3(256), 0, s, rows, w, grad, loss);
+    hipLaunchKernelGGL(k_mlp_sum, dim3((kPart + 63) / 64), dim3(256), 0, s, rows, wgs, part, grad, loss);
     return hipGetLastError();
 }
 
