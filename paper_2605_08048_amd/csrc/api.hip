@@ -206,7 +206,7 @@ struct Plan {
     int d = 0, d_pad = 0, nslot = 0;
     int precision = HBT_F32;
     int input_dtype = HBT_IN_F32;
-    int max_np = 0;
+    int min_np = 0, max_np = 0;  // smallest and largest padded pooled size
     std::vector<PairDesc> pairs;
     std::vector<BlockPair> bp;
     std::vector<SumChunk> chunks;
@@ -376,6 +376,7 @@ void add_pair(Plan& P, const void* X, const void* Y, int64_t n, int64_t m, uint3
     P.xoct += x_octets(n);
     P.zrows += pd.Np;
     P.ncoef += n;
+    P.min_np = P.npairs ? std::min(P.min_np, (int)pd.Np) : (int)pd.Np;
     P.max_np = std::max(P.max_np, (int)pd.Np);
     P.pairs.push_back(pd);
     P.npairs = (int)P.pairs.size();
@@ -794,8 +795,8 @@ hbt_status batched_pipelined(const Plan& P, const Workspace& w, const hbt_perm_p
         hipEvent_t es, ea;
         {
             StageTimer t_(HBT_STAGE_SPLIT, qs);
-            HIP_TRY(launch_split_masks(w.bp, np, r1, P.max_np, common->seed, w.mask, w.sstat,
-                                       P.tune.split_cap, qs, r0));
+            HIP_TRY(launch_split_masks(w.bp, np, r1, P.min_np, P.max_np, common->seed, w.mask, w.sstat,
+                                       P.tune.split_cap, qs, r0, P.block_rows));
         }
         HIP_TRY(ev.record(qs, &es));
         {
@@ -993,7 +994,7 @@ hbt_status hbt_perm_test(const void* X, const void* Y, const hbt_perm_params* pr
     };
     auto block_splits = [&](int64_t b0, int64_t nb, hipStream_t q) -> hipError_t {
         if (prm->masks) return launch_copy_masks(prm->masks, b0, nb, N, (int)prm->n, pd.Wp, w.mask, w.sstat, q);
-        return launch_split_masks(w.bp, 1, nb, P.max_np, prm->seed, w.mask, w.sstat,
+        return launch_split_masks(w.bp, 1, nb, P.min_np, P.max_np, prm->seed, w.mask, w.sstat,
                                   P.tune.split_cap, q);
     };
     {
@@ -1162,7 +1163,8 @@ static bool plan_clouds(Plan& P, int64_t nclouds, const void* Z_all, const int64
         pd.cy0 = cy.cx1;
         pd.cy1 = cy.cy1;
         P.ncoef += pd.n;
-        P.max_np = std::max(P.max_np, (int)pd.Np);
+        P.min_np = P.npairs ? std::min(P.min_np, (int)pd.Np) : (int)pd.Np;
+    P.max_np = std::max(P.max_np, (int)pd.Np);
         P.fold_segs = std::max(P.fold_segs, fold_segments(pd.n));
         P.pairs.push_back(pd);
         const auto key = std::make_tuple((int64_t)pd.n, (int64_t)pd.m, B[p], pd.pair_index);
@@ -1340,7 +1342,7 @@ hbt_status hbt_perm_test_batched(int64_t npairs, const void* Z_all, const int64_
         StageTimer t_(HBT_STAGE_SPLIT, qs);
         HIP_TRY(upload(w.bp, P.bp.data(), P.bp.size() * sizeof(BlockPair), qs));
         HIP_TRY(zero(w.sstat, (size_t)(np + 1) / 2 * 8, qs));
-        HIP_TRY(launch_split_masks(w.bp, np, P.block_rows, P.max_np, common->seed, w.mask, w.sstat,
+        HIP_TRY(launch_split_masks(w.bp, np, P.block_rows, P.min_np, P.max_np, common->seed, w.mask, w.sstat,
                                    P.tune.split_cap, qs));
     }
     {
@@ -1585,7 +1587,7 @@ hbt_status hbt_perm_test_clouds(int64_t nclouds, const void* Z_all, const int64_
         StageTimer t_(HBT_STAGE_SPLIT, qs);
         HIP_TRY(upload(w.bp, P.bp.data(), P.bp.size() * sizeof(BlockPair), qs));
         HIP_TRY(zero(w.sstat, (size_t)(np + 1) / 2 * 8, qs));
-        HIP_TRY(launch_split_masks(w.bp, np, P.block_rows, P.max_np, common->seed, w.mask, w.sstat,
+        HIP_TRY(launch_split_masks(w.bp, np, P.block_rows, P.min_np, P.max_np, common->seed, w.mask, w.sstat,
                                    P.tune.split_cap, qs));
     }
     {

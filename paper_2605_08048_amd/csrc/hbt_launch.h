@@ -79,9 +79,10 @@ size_t split_lds_limit();
 // there, and rows of pairs that share another pair's splits are skipped.
 constexpr int kSplitWgPerCuBesideAlign = 6;
 hipError_t launch_split_masks(const BlockPair* bp, int npairs,
-                              int64_t rows, int max_np, uint64_t seed, uint32_t* mask,
+                              int64_t rows, int min_np, int max_np, uint64_t seed, uint32_t* mask,
                               int32_t* sstat, int wg_per_cu, hipStream_t s,
-                              int64_t row0 = 0  /* split rows [row0, rows) */);
+                              int64_t row0 = 0,  // split rows [row0, rows) ...
+                              int64_t total_rows = 0);  // ... of this many in the table (0: rows)
 // Explicit masks: copy rows of ceil(N/32) words into the workspace layout and
 // check that each holds exactly n items.
 hipError_t launch_copy_masks(const uint32_t* user, int64_t user_row0, int64_t rows, int N, int n,

@@ -10,7 +10,9 @@
 // P == theta are ranked by (S_i, i) and the first n - #{P < theta} join.
 // Only those bucket items ever need a secondary key.
 //
-// One wavefront per split row; waves of a work-group are independent and
+// Two kernels: pairs of up to kQuadItems pooled items are drawn four split rows
+// a wavefront, larger pairs one; a launch of both kinds of pairs runs both, each
+// skipping the other's rows.  Waves of a work-group are independent and
 // synchronise only within themselves.
 #include <atomic>
 
@@ -37,7 +39,7 @@ struct SplitLds {
     }
 };
 constexpr int kSplitWaves = 4;          // waves (split rows) per work-group
-constexpr int kSplitStaticLds = kSplitWaves * 1024;
+constexpr int kSplitStaticLds = kSplitWaves * (1024 + 4);
 
 // hist[W][key] += 1 for the 16 keys of a block.  The wave's histogram offset
 // W * 1024 goes into the LDS instruction's immediate offset, so that a key
@@ -52,6 +54,17 @@ template <int OFF>
 __device__ __forceinline__ void lds_inc(uint32_t addr, uint32_t one) {
     asm volatile("ds_add_u32 %0, %1 offset:%2" : : "v"(addr), "v"(one), "i"(OFF) : "memory");
 }
+// The LDS word's value before adding one to it (a place in a list), waited for
+// here: with atomicAdd the compiler elects one lane and counts the others, more
+// vector instructions than the one or two lanes that usually want a place.
+__device__ __forceinline__ uint32_t lds_take(uint32_t* word) {
+    uint32_t pos;
+    asm volatile("ds_add_rtn_u32 %0, %1, %2\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(pos)
+                 : "v"((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)word), "v"(1u)
+                 : "memory");
+    return pos;
+}
 #pragma clang diagnostic pop
 template <int W>
 __device__ __forceinline__ void count_block(uint32_t (*hist)[256], uint4 w) {
@@ -62,82 +75,120 @@ __device__ __forceinline__ void count_block(uint32_t (*hist)[256], uint4 w) {
         lds_inc<W * 1024>(base + (((word_of(w, j >> 2) >> (8 * (j & 3))) & 0xffu) << 2), one);
 }
 
-// Bit j of the result = [byte j % 4 of word j / 4 < theta] for the 16 keys of
-// a block (item j's primary key, below the bucket byte theta), with four
-// bytes compared at once: for each byte x and t = theta,
+// The bits 7 of the four bytes of each of a block's words (f(word) in w.x .. w.w
+// order), gathered to 16 bits: bit 4 q + b from byte b of word q, item 4 q + b of
+// the block.  Per word, one product moves its four bits to the top nibble (the
+// partial products fall on distinct bits, so nothing carries into it) and one
+// funnel shift appends the nibble.
+template <typename F>
+__device__ __forceinline__ uint32_t gather_bits7(uint4 w, F f) {
+    uint32_t acc = 0u;
+#pragma unroll
+    for (int q = 3; q >= 0; --q)
+        acc = __builtin_amdgcn_alignbit(acc, (f(word_of(w, q)) & 0x80808080u) * 0x00204081u, 28);
+    return acc;
+}
+
+// Bit j of the result = [key j of the block < theta] (theta4: theta in every
+// byte), four bytes at a time: for each byte x and t = theta,
 //   x < t  <=>  (x7 = 0 and t7 = 1) or (x7 = t7 and (x & 127) < (t & 127)),
 // where (x & 127) + (128 - (t & 127)) has bit 7 set exactly when
 // (x & 127) >= (t & 127) (no carry leaves the byte); one three-input logic
-// operation combines the three conditions in bit 7.  The 16 flags are then
-// gathered: bit 8 b + q <- byte b of word q, packed to bit 4 b + q, and the
-// 4 x 4 bit matrix transposed (two delta swaps) to bit 4 q + b.
+// operation combines the three conditions in bit 7.
 __device__ __forceinline__ uint32_t below_theta(uint4 w, uint32_t theta4) {
     const uint32_t k = 0x80808080u - (theta4 & 0x7f7f7f7fu);  // per byte 128 - (t & 127)
     // truth table of (~x & t) | (~(x ^ t) & ~s) over the operands (x, t, s)
     constexpr unsigned kTT = ((~0xF0u & 0xCCu) | (~(0xF0u ^ 0xCCu) & ~0xAAu)) & 0xffu;
-    auto lt7 = [&](uint32_t x) {
+    return gather_bits7(w, [&](uint32_t x) {
         return __builtin_amdgcn_bitop3_b32(x, theta4, (x & 0x7f7f7f7fu) + k, (unsigned char)kTT);
-    };
-    uint32_t u = (lt7(w.x) >> 7) & 0x01010101u;
-    u |= (lt7(w.y) >> 6) & 0x02020202u;
-    u |= (lt7(w.z) >> 5) & 0x04040404u;
-    u |= (lt7(w.w) >> 4) & 0x08080808u;
-    uint32_t v = (u | (u >> 4)) & 0x00ff00ffu;
-    v = (v | (v >> 8)) & 0xffffu;
-    uint32_t t = (v ^ (v >> 3)) & 0x0A0Au;
-    v ^= t ^ (t << 3);
-    t = (v ^ (v >> 6)) & 0x00CCu;
-    v ^= t ^ (t << 6);
-    return v;
+    });
+}
+
+// Bit j of the result = [key j of the block == theta].
+__device__ __forceinline__ uint32_t equal_theta(uint4 w, uint32_t theta4) {
+    return gather_bits7(w, [&](uint32_t x) {
+        const uint32_t y = x ^ theta4;
+        return ~(((y & 0x7f7f7f7fu) + 0x7f7f7f7fu) | y);
+    });
+}
+
+// Pair of a split row.  Pairs of one batch mostly have equally many rows, so
+// the pair at the row's place in proportion (pairs_per_row = npairs / rows) is
+// looked at first: one load instead of a search of log2(npairs) loads, each
+// waiting for the one before (half the time of a wave that drew one split).
+__device__ __forceinline__ int pair_of_row(const BlockPair* bp, int npairs, int64_t row, double pairs_per_row) {
+    int p = (int)(((double)row + 0.5) * pairs_per_row);
+    p = __builtin_amdgcn_readfirstlane(p < npairs ? p : npairs - 1);
+    const int64_t r0 = bp[p].mrow0;
+    if (r0 <= row && row < r0 + bp[p].nb) return p;
+    return upper_index(npairs, row, [&](int k) { return bp[k].mrow0; });
+}
+
+// A finished mask row from LDS to memory.
+__device__ __forceinline__ void write_mask_row(uint32_t* out, const uint32_t* mlds, const BlockPair& pd) {
+    const int lane = threadIdx.x & 63;
+    if (pd.ygap == 0) {
+        for (int w = lane; w < pd.Wp; w += 64) out[w] = mlds[w];
+        return;
+    }
+    // two-run storage: X's items keep their positions, Y's move ygap
+    // positions on (X's padding in between); n + ygap is a multiple of 128
+    const int ys = pd.n + pd.ygap;
+    for (int w = lane; w < pd.Wp; w += 64) {
+        uint32_t x;
+        if (32 * w < ys) {
+            x = mlds[w] & range_bits(w, 0, pd.n);
+        } else {
+            const int p0 = 32 * w - pd.ygap, q = p0 >> 5, sh = p0 & 31;
+            const uint32_t a = mlds[q], b = q + 1 < pd.Wp ? mlds[q + 1] : 0u;
+            x = sh ? (a >> sh) | (b << (32 - sh)) : a;
+            x &= range_bits(w, ys, ys + pd.m);
+        }
+        out[w] = x;
+    }
 }
 
 // Philox block c of split b: the primary keys of items 16c .. 16c+15 as 16
-// little-endian bytes.  Items at or past N get the key 0xFF; they are removed
-// from the histogram's top bin afterwards and never enter group 1.
-__device__ __forceinline__ uint4 primary_block(int c, int N, uint32_t b, uint32_t pair,
-                                               uint32_t k0, uint32_t k1) {
-    uint4 w = philox4x32_10(make_uint4((uint32_t)c, b, pair, 0u), k0, k1);
-    const int lim = N - 16 * c;
-    if (lim < 16) {
-        auto fill = [&](uint32_t x, int base) {
-            const int v = lim - base;
-            return v >= 4 ? x : v <= 0 ? 0xffffffffu : x | (0xffffffffu << (8 * v));
-        };
-        w = make_uint4(fill(w.x, 0), fill(w.y, 4), fill(w.z, 8), fill(w.w, 12));
-    }
-    return w;
+// little-endian bytes.
+__device__ __forceinline__ uint4 primary_block(int c, uint32_t b, uint32_t pair, uint32_t k0, uint32_t k1) {
+    return philox4x32_10(make_uint4((uint32_t)c, b, pair, 0u), k0, k1);
+}
+// The pair's last block holds lim (1 .. 16) items; the keys past them become
+// 0xFF: they are taken out of the histogram's top bin afterwards and never enter
+// group 1.
+__device__ __forceinline__ uint4 pad_block(uint4 w, int lim) {
+    auto fill = [&](int base) {  // wave-uniform
+        const int v = lim - base;
+        return v >= 4 ? 0u : v <= 0 ? 0xffffffffu : 0xffffffffu << (8 * v);
+    };
+    return make_uint4(w.x | fill(0), w.y | fill(4), w.z | fill(8), w.w | fill(12));
 }
 
-// One wave per split row.  R > 0: each lane keeps its (at most R) Philox
-// blocks in registers between the histogram and the classification pass
-// (pairs with N <= 1024 R); R == 0: the blocks are generated again.
+// One split row.  R > 0: each lane keeps its (at most R) Philox blocks in
+// registers between the histogram and the classification pass (pairs with N
+// <= 1024 R); R == 0: the blocks are generated again.
 template <int R>
-__global__ __launch_bounds__(256) void k_split_masks(const BlockPair* __restrict__ bp, int npairs,
-                                                     int64_t rows, int max_np, uint32_t key0,
-                                                     uint32_t key1, uint32_t* __restrict__ mask,
-                                                     int32_t* sstat, int64_t row0) {
-    __shared__ uint32_t hist_all[kSplitWaves][256];
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+__device__ __forceinline__ void split_row(const BlockPair& pd, int p, int64_t row, int max_np, uint32_t key0,
+                                          uint32_t key1, uint32_t* __restrict__ mask, int32_t* sstat,
+                                          uint32_t (*hist_all)[256], uint32_t* nlist, unsigned char* smem) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int lane = threadIdx.x & 63, N = pd.n + pd.m;
+    // nothing of a row stays in registers across the caller's loop
+    asm volatile("" : "+v"(lane), "+s"(N));
     const SplitLds L(max_np);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * kSplitWaves + wave + row0;
-    if (row >= rows) return;
     unsigned char* base = smem + wave * L.total;
     uint32_t* hist = hist_all[wave];
     uint32_t* cidx = (uint32_t*)(base + L.cidx);
     uint32_t* ckey = (uint32_t*)(base + L.ckey);
     uint32_t* mlds = (uint32_t*)(base + L.mlds);
-
-    const int p = upper_index(npairs, row, [&](int k) { return bp[k].mrow0; });
-    const BlockPair pd = bp[p];   // the pair's sizes, mask row width and index (not a PairDesc)
-    if (pd.owner != p) return;    // another pair's rows draw these masks (wave-uniform)
-    const uint32_t b = bp[p].perm_base + (uint32_t)(row - bp[p].mrow0);
-    const int N = pd.n + pd.m, n = pd.n;
+    const uint32_t b = pd.perm_base + (uint32_t)(row - pd.mrow0);
+    const int n = pd.n;
     const int nc = (N + 15) >> 4;       // Philox blocks holding items
     const int nw = pd.Wp * 2;           // blocks covering the padded mask row (Np / 16)
     const int niter = (nw + 63) >> 6;   // wave-uniform
 
     ((uint4*)hist)[lane] = make_uint4(0u, 0u, 0u, 0u);
+    if (lane == 0) *nlist = 0u;
     wave_sync();
     // 1. primary keys and their histogram
     constexpr int RK = R > 0 ? R : 1;
@@ -146,7 +197,8 @@ __global__ __launch_bounds__(256) void k_split_masks(const BlockPair* __restrict
         const int c = 64 * k + lane;
         uint4 w = make_uint4(0u, 0u, 0u, 0u);
         if (c < nc) {
-            w = primary_block(c, N, b, pd.pair_index, key0, key1);
+            w = primary_block(c, b, pd.pair_index, key0, key1);
+            if (c == nc - 1) w = pad_block(w, N - 16 * (nc - 1));
             switch (wave) {  // wave-uniform
                 case 0: count_block<0>(hist_all, w); break;
                 case 1: count_block<1>(hist_all, w); break;
@@ -196,7 +248,7 @@ __global__ __launch_bounds__(256) void k_split_masks(const BlockPair* __restrict
     const uint32_t need = (uint32_t)n - below;
     if (bucket > (uint32_t)kCandCap) {  // not seen in practice (expected size N / 256)
         if (lane == 0) atomicExch(&sstat[p], (int)HBT_ERR_INTERNAL);
-        uint32_t* out = const_cast<uint32_t*>(mask_row(mask, bp[p], row, pd.Wp));
+        uint32_t* out = const_cast<uint32_t*>(mask_row(mask, pd, row, pd.Wp));
         for (int w = lane; w < pd.Wp; w += 64) out[w] = 0u;  // an empty group: nothing to gather
         return;
     }
@@ -204,46 +256,45 @@ __global__ __launch_bounds__(256) void k_split_masks(const BlockPair* __restrict
     //    block, two neighbouring lanes form one 32-bit mask word; blocks that
     //    hold a byte equal to theta (a few per split) list those items
     const uint32_t theta4 = theta * 0x01010101u;
-    uint32_t cbase = 0;  // bucket items listed so far (wave-uniform)
+    // (the items of two rounds' blocks at a time, in any order: a rank does not
+    // depend on the list's)
     auto classify = [&](int k, uint4 w) {
         const int c = 64 * k + lane;
-        uint32_t lt = below_theta(w, theta4);
-        // bit 7 of each byte equal to theta (exact), gathered into one word:
-        // bit 8 b + q marks item 4 q + b of the block
-        uint32_t eq = 0u;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const uint32_t x = word_of(w, q) ^ theta4;
-            const uint32_t z = ~(((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) & 0x80808080u;
-            eq |= z >> (7 - q);
-        }
-        if (c >= nc) {
-            lt = 0u;
-            eq = 0u;
-        } else if (16 * c + 16 > N) {  // tail block: drop the padding items (keys 0xFF)
-            for (int j = N - 16 * c; j < 16; ++j) eq &= ~(1u << (8 * (j & 3) + (j >> 2)));
-        }
-        const uint32_t ne = (uint32_t)__popc(eq);
-        const uint32_t incl = wave_incl_scan(ne);
-        uint32_t pos = cbase + incl - ne;
-        cbase += __builtin_amdgcn_readlane(incl, 63);
-        while (eq) {
-            const int t = __ffs(eq) - 1;
-            cidx[pos++] = (uint32_t)(16 * c + 4 * (t & 7) + (t >> 3));
-            eq &= eq - 1u;
+        uint32_t lt = below_theta(w, theta4), eq = equal_theta(w, theta4);
+        if (64 * k + 64 >= nc) {  // the round with the last block: its padding keys and the lanes past it
+            if (c == nc - 1) eq &= (2u << (N - 16 * (nc - 1) - 1)) - 1u;
+            if (c >= nc) {
+                lt = 0u;
+                eq = 0u;
+            }
         }
         // lane ^ 1's bits (quad_perm [1,0,3,2])
         const uint32_t nb = (uint32_t)__builtin_amdgcn_mov_dpp((int)lt, 0xB1, 0xF, 0xF, false);
         if (!(lane & 1) && c < nw) mlds[c >> 1] = lt | (nb << 16);
+        return eq;
+    };
+    auto list_items = [&](int k, uint32_t eq) {  // bits 0-15 of round k, 16-31 of round k + 1
+        while (eq) {
+            const uint32_t t = (uint32_t)__ffs(eq) - 1u;
+            cidx[lds_take(nlist)] = (uint32_t)(16 * (64 * k + lane)) + (t >> 4) * 1024u + (t & 15u);
+            eq &= eq - 1u;
+        }
     };
     if constexpr (R > 0) {
 #pragma unroll
-        for (int k = 0; k < R; ++k)
-            if (k < niter) classify(k, key[k]);  // wave-uniform
+        for (int k = 0; k < R; k += 2)
+            if (k < niter) {  // wave-uniform
+                uint32_t eq = classify(k, key[k]);
+                if (k + 1 < R && k + 1 < niter) eq |= classify(k + 1, key[k + 1 < R ? k + 1 : k]) << 16;
+                list_items(k, eq);
+            }
     } else {
         for (int k = 0; k < niter; ++k) {
             const int c = 64 * k + lane;
-            classify(k, c < nc ? primary_block(c, N, b, pd.pair_index, key0, key1) : make_uint4(0u, 0u, 0u, 0u));
+            uint4 w = make_uint4(0u, 0u, 0u, 0u);
+            if (c < nc) w = primary_block(c, b, pd.pair_index, key0, key1);
+            if (c == nc - 1) w = pad_block(w, N - 16 * (nc - 1));
+            list_items(k, classify(k, w));
         }
     }
     wave_sync();
@@ -286,25 +337,255 @@ __global__ __launch_bounds__(256) void k_split_masks(const BlockPair* __restrict
         }
     }
     wave_sync();
-    uint32_t* out = const_cast<uint32_t*>(mask_row(mask, bp[p], row, pd.Wp));
-    if (pd.ygap == 0) {
-        for (int w = lane; w < pd.Wp; w += 64) out[w] = mlds[w];
-    } else {
-        // two-run storage: X's items keep their positions, Y's move ygap
-        // positions on (X's padding in between); n + ygap is a multiple of 128
-        const int ys = n + pd.ygap;
-        for (int w = lane; w < pd.Wp; w += 64) {
-            uint32_t x;
-            if (32 * w < ys) {
-                x = mlds[w] & range_bits(w, 0, n);
-            } else {
-                const int p0 = 32 * w - pd.ygap, q = p0 >> 5, sh = p0 & 31;
-                const uint32_t a = mlds[q], b = q + 1 < pd.Wp ? mlds[q + 1] : 0u;
-                x = sh ? (a >> sh) | (b << (32 - sh)) : a;
-                x &= range_bits(w, ys, ys + pd.m);
+    write_mask_row(const_cast<uint32_t*>(mask_row(mask, pd, row, pd.Wp)), mlds, pd);
+}
+
+// Wave g takes the rows rows_wave g .. of the pairs of more than skip_wp mask
+// words a row (the others are k_split_quads'); rows_wave > 1 where the rows are
+// many: a quarter of the waves to start and to find their pair.
+template <int R>
+__global__ __launch_bounds__(64 * kSplitWaves) void k_split_masks(const BlockPair* __restrict__ bp, int npairs,
+                                                                  int64_t rows, int max_np, uint32_t key0,
+                                                                  uint32_t key1, uint32_t* __restrict__ mask,
+                                                                  int32_t* sstat, int64_t row0, int skip_wp,
+                                                                  double pairs_per_row, int rows_wave) {
+    __shared__ uint32_t hist_all[kSplitWaves][256];
+    __shared__ uint32_t nlist_all[kSplitWaves];
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int64_t row = ((int64_t)blockIdx.x * kSplitWaves + wave) * rows_wave + row0;
+    const int64_t end = row + rows_wave < rows ? row + rows_wave : rows;
+    while (row < end) {
+        const int p = pair_of_row(bp, npairs, row, pairs_per_row);
+        const BlockPair pd = bp[p];  // the pair's sizes, mask row width and index (not a PairDesc)
+        const int64_t pend = pd.mrow0 + pd.nb < end ? pd.mrow0 + pd.nb : end;
+        // else another pair's rows, or the other kernel, draw these masks (wave-uniform)
+        if (pd.owner == p && pd.Wp > skip_wp)
+            for (; row < pend; ++row) {
+                split_row<R>(pd, p, row, max_np, key0, key1, mask, sstat, hist_all, &nlist_all[wave], smem);
+                wave_sync();
             }
-            out[w] = x;
+        row = pend;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Four split rows per wave, for pairs of up to kQuadItems pooled items: 16
+// lanes a row (lane 16 r + t draws blocks t, t + 16, ... of row r), so a pair of
+// 128 items takes one round of 32 lanes instead of four of 8; the four histograms
+// are scanned at once; and the rows' bucket items share one list and one
+// secondary draw, ranked by (row, S, i).  Bound by VALU issue (920 vector
+// instructions a wave at 760 items, one per SIMD every 4.3 cycles).  2.5 million
+// rows of 200 to 2000 items: 1.06 ms, and 0.11 ms for the other kernel's skipping
+// of them, against 2.5 ms with one wave a row (620 instructions each, and as long
+// again waiting for the search of its pair).
+// ---------------------------------------------------------------------------
+constexpr int kQuad = 4;
+constexpr int kListCap = 320;  // bucket items of a wave's rows (about 4 N / 256 <= 32 of them)
+static_assert(12 * kListCap <= kQuad * 1024, "the list and its keys take the histograms' words");
+
+// hist[key] += 1 for the 16 keys of a block, the histogram at LDS address hb (a
+// multiple of 1024).
+__device__ __forceinline__ void count_block_at(uint32_t hb, uint4 w) {
+    const uint32_t one = 1u;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint32_t x = word_of(w, q);
+        lds_inc<0>(((x << 2) & 0x3fcu) | hb, one);
+        lds_inc<0>(((x >> 6) & 0x3fcu) | hb, one);
+        lds_inc<0>(((x >> 14) & 0x3fcu) | hb, one);
+        lds_inc<0>(((x >> 22) & 0x3fcu) | hb, one);
+    }
+}
+
+// Split rows row .. row + nr - 1 (nr <= 4) of pair p, of at most 16 K blocks.
+template <int K>
+__device__ __forceinline__ void split_rows(const BlockPair& pd, int p, int64_t row, int nr, uint32_t key0,
+                                           uint32_t key1, uint32_t* __restrict__ mask, int32_t* sstat,
+                                           uint32_t (*hist)[256], uint4* meta, uint32_t* mlds) {
+    int lane = threadIdx.x & 63, N = pd.n + pd.m;
+    // nothing of these rows stays in registers across the caller's loop
+    asm volatile("" : "+v"(lane), "+s"(N), "+s"(key0), "+s"(key1));
+    const int r4 = lane >> 4, t = lane & 15;
+    const uint32_t b0 = pd.perm_base + (uint32_t)(row - pd.mrow0);
+    const int Wp = pd.Wp;
+    const uint32_t n = (uint32_t)pd.n;
+    const int nc = (N + 15) >> 4, nw = Wp * 2;  // blocks with items, and of a mask row
+    const int lim = N - 16 * (nc - 1);          // items of the last block
+    const bool live = r4 < nr;
+    const uint32_t hb = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)hist + 1024u * (uint32_t)r4;
+#pragma unroll
+    for (int i = 0; i < kQuad; ++i) ((uint4*)hist)[64 * i + lane] = make_uint4(0u, 0u, 0u, 0u);
+    wave_sync();
+    // 1. primary keys and their histograms
+    uint4 key[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        key[k] = make_uint4(0u, 0u, 0u, 0u);
+        if (16 * k < nc) {  // wave-uniform
+            const int c = 16 * k + t;
+            if (live && c < nc) {
+                key[k] = primary_block(c, b0 + (uint32_t)r4, pd.pair_index, key0, key1);
+                if (c == nc - 1) key[k] = pad_block(key[k], lim);
+                count_block_at(hb, key[k]);
+            }
         }
+    }
+    wave_sync();
+    // 2. theta, the items below it and its bucket, per row: lane t of row r's 16
+    //    lanes holds bins 16 t .. 16 t + 15 (the padding keys taken out of bin 255)
+    {
+        uint32_t h[16];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint4 v = ((const uint4*)hist[r4])[4 * t + i];
+            h[4 * i] = v.x;
+            h[4 * i + 1] = v.y;
+            h[4 * i + 2] = v.z;
+            h[4 * i + 3] = v.w;
+        }
+        const uint32_t pad = (uint32_t)(16 * nc - N);
+        if (t == 15) h[15] -= pad;
+        uint32_t sum = 0;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sum += h[i];
+        int v = (int)sum;  // inclusive scan over the 16 lanes
+        v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+        const uint32_t incl = (uint32_t)v, excl = incl - sum;
+        if (live && excl < n && n <= incl) {  // one lane per row
+            uint32_t acc = excl, below = excl, cnt = 0;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                acc += h[i];
+                const bool lt = acc < n;
+                cnt += lt;
+                below = lt ? acc : below;
+            }
+            const uint32_t theta = 16u * (uint32_t)t + cnt;
+            const uint32_t bucket = hist[r4][theta] - (theta == 255u ? pad : 0u);
+            meta[r4] = make_uint4(theta * 0x01010101u, n - below, bucket, 0u);
+        } else if (!live && t == 0) {
+            meta[r4] = make_uint4(0u, 0u, 0u, 0u);
+        }
+    }
+    wave_sync();
+    const uint32_t c0 = __builtin_amdgcn_readfirstlane(meta[0].z), c1 = __builtin_amdgcn_readfirstlane(meta[1].z),
+                   c2 = __builtin_amdgcn_readfirstlane(meta[2].z), c3 = __builtin_amdgcn_readfirstlane(meta[3].z);
+    uint32_t* out = const_cast<uint32_t*>(mask_row(mask, pd, row, Wp));
+    if (c0 + c1 + c2 + c3 > (uint32_t)kListCap) {  // not seen in practice, as in k_split_masks
+        if (lane == 0) atomicExch(&sstat[p], (int)HBT_ERR_INTERNAL);
+        for (int w = lane; w < nr * Wp; w += 64) out[w] = 0u;  // empty groups: nothing to gather
+        return;
+    }
+    // 3. classification: each lane builds the 16 bits "P < theta" of its block,
+    //    two neighbouring lanes one mask word; the bucket items go to the list
+    //    (row << 16 | item) in any order
+    uint32_t* list = hist[0];
+    const uint32_t listed = c0 + c1 + c2 + c3;
+    uint32_t* nlist = &meta[0].w;
+    const uint32_t theta4 = meta[r4].x;
+    uint32_t* mrow = mlds + r4 * Wp + (t >> 1);
+    uint32_t eq2 = 0u;  // two rounds' items equal to theta
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        if (16 * k < nw) {  // wave-uniform
+            const int c = 16 * k + t;
+            uint32_t lt = below_theta(key[k], theta4), eq = equal_theta(key[k], theta4);
+            if (!live) eq = 0u;
+            if (16 * k + 16 >= nc) {  // the round with the last block: its padding keys and the lanes past it
+                if (c == nc - 1) eq &= (2u << (lim - 1)) - 1u;
+                if (c >= nc) {
+                    lt = 0u;
+                    eq = 0u;
+                }
+            }
+            // lane ^ 1's bits (quad_perm [1,0,3,2])
+            const uint32_t nb = (uint32_t)__builtin_amdgcn_mov_dpp((int)lt, 0xB1, 0xF, 0xF, false);
+            if (!(lane & 1) && live && c < nw) mrow[8 * k] = lt | (nb << 16);
+            eq2 |= eq << (16 * (k & 1));
+        }
+        if (k & 1) {  // the items of two rounds
+            while (eq2) {
+                const uint32_t j = (uint32_t)__ffs(eq2) - 1u;
+                list[lds_take(nlist)] =
+                    ((uint32_t)r4 << 16) | (uint32_t)(256 * (k - 1) + 16 * t) + (j >> 4) * 256u + (j & 15u);
+                eq2 &= eq2 - 1u;
+            }
+        }
+    }
+    wave_sync();
+    // 4., 5. secondary keys; an item's rank among all listed ones in (row, S, i)
+    //    order, less the bucket items of the rows before, is its rank in its row,
+    //    and the first `need` of a row join group 1
+    auto key_of = [&](uint32_t e) {
+        const uint32_t i = e & 0xffffu, s = e >> 16;
+        const uint4 w = philox4x32_10(make_uint4(i >> 2, b0 + s, pd.pair_index, 1u), key0, key1);
+        return ((uint64_t)s << 48) | ((uint64_t)word_of(w, i & 3) << 16) | i;
+    };
+    auto join = [&](uint32_t e, uint32_t rank) {
+        const uint32_t i = e & 0xffffu, s = e >> 16;
+        const uint32_t before = (s > 0 ? c0 : 0u) + (s > 1 ? c1 : 0u) + (s > 2 ? c2 : 0u);
+        if (rank - before < meta[s].y) atomicOr(&mlds[(int)s * Wp + (int)(i >> 5)], 1u << (i & 31));
+    };
+    if (listed <= 64u) {  // the usual case: ranks through lane broadcasts
+        uint32_t e = 0;
+        uint64_t ky = ~0ull;
+        if ((uint32_t)lane < listed) {
+            e = list[lane];
+            ky = key_of(e);
+        }
+        uint32_t rank = 0;
+        for (uint32_t q = 0; q < listed; ++q) {
+            const uint64_t k2 = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(ky >> 32), q) << 32) |
+                                (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)ky, q);
+            rank += k2 < ky;
+        }
+        if ((uint32_t)lane < listed) join(e, rank);
+    } else {  // through LDS
+        uint64_t* lkey = (uint64_t*)(list + kListCap);
+        for (uint32_t q = lane; q < listed; q += 64) lkey[q] = key_of(list[q]);
+        wave_sync();
+        for (uint32_t k = lane; k < listed; k += 64) {
+            const uint64_t ky = lkey[k];
+            uint32_t rank = 0;
+            for (uint32_t q = 0; q < listed; ++q) rank += lkey[q] < ky;
+            join(list[k], rank);
+        }
+    }
+    wave_sync();
+    if (pd.ygap == 0) {  // the rows are one run
+        for (int w = lane; w < nr * Wp; w += 64) out[w] = mlds[w];
+    } else {
+        for (int i = 0; i < nr; ++i) write_mask_row(out + i * Wp, mlds + i * Wp, pd);
+    }
+}
+
+// Wave g takes the split rows 4 g .. 4 g + 3, those of one pair together; rows
+// of pairs of more than 16 K blocks are left to k_split_masks.
+template <int K>
+__global__ __launch_bounds__(64 * kSplitWaves) void k_split_quads(const BlockPair* __restrict__ bp, int npairs,
+                                                                  int64_t rows, uint32_t key0, uint32_t key1,
+                                                                  uint32_t* __restrict__ mask, int32_t* sstat,
+                                                                  int64_t row0, double pairs_per_row) {
+    __shared__ __attribute__((aligned(1024))) uint32_t hist_all[kSplitWaves][kQuad][256];
+    __shared__ uint4 meta_all[kSplitWaves][kQuad];
+    __shared__ uint32_t mlds_all[kSplitWaves][kQuad * 8 * K];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int64_t row = ((int64_t)blockIdx.x * kSplitWaves + wave) * kQuad + row0;
+    const int64_t end = row + kQuad < rows ? row + kQuad : rows;
+    while (row < end) {
+        const int p = pair_of_row(bp, npairs, row, pairs_per_row);
+        const BlockPair pd = bp[p];  // the pair's sizes, mask row width and index (not a PairDesc)
+        const int64_t pend = pd.mrow0 + pd.nb;
+        const int nr = (int)((pend < end ? pend : end) - row);
+        if (pd.owner == p && pd.Wp <= 8 * K) {  // else another pair's rows, or the other kernel, draw these masks
+            split_rows<K>(pd, p, row, nr, key0, key1, mask, sstat, hist_all[wave], meta_all[wave], mlds_all[wave]);
+            wave_sync();
+        }
+        row += nr;
     }
 }
 
@@ -335,28 +616,48 @@ size_t split_lds_limit() {
     return lim;
 }
 
+// Rounds of the four-row kernel and the pooled items it takes.
+constexpr int kQuadRounds = 8, kQuadRoundsSmall = 4;
+constexpr int kQuadItems = 256 * kQuadRounds;
+
 size_t split_lds_per_block(int max_np) { return (size_t)kSplitWaves * SplitLds(max_np).total + kSplitStaticLds; }
 
 hipError_t launch_split_masks(const BlockPair* bp, int npairs,
-                              int64_t rows, int max_np, uint64_t seed, uint32_t* mask,
-                              int32_t* sstat, int wg_per_cu, hipStream_t s, int64_t row0) {
+                              int64_t rows, int min_np, int max_np, uint64_t seed, uint32_t* mask,
+                              int32_t* sstat, int wg_per_cu, hipStream_t s, int64_t row0, int64_t total_rows) {
     if (rows <= row0) return hipSuccess;
+    if (total_rows < rows) total_rows = rows;
+    const size_t share = wg_per_cu > 0 ? lds_per_cu() / (size_t)wg_per_cu : 0;
+    const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+    const dim3 block(64 * kSplitWaves);
+    const double ppr = (double)npairs / (double)total_rows;
+    if (min_np <= kQuadItems) {
+        const int64_t per_wg = (int64_t)kSplitWaves * kQuad;
+        const dim3 grid((unsigned)((rows - row0 + per_wg - 1) / per_wg));
+        auto go = [&](auto kern, int K) {
+            const size_t own = (size_t)kSplitWaves * kQuad * (1024 + 16 + 32 * K);
+            hipLaunchKernelGGL(kern, grid, block, share > own ? share - own : 0, s, bp, npairs, rows, k0, k1, mask,
+                               sstat, row0, ppr);
+        };
+        if (max_np <= 256 * kQuadRoundsSmall) go(k_split_quads<kQuadRoundsSmall>, kQuadRoundsSmall);
+        else go(k_split_quads<kQuadRounds>, kQuadRounds);
+        if (max_np <= kQuadItems) return hipGetLastError();
+    }
     const SplitLds L(max_np);
     // four split rows per work-group; at most 64 KB of LDS per work-group
     size_t lds = (size_t)kSplitWaves * L.total;
-    if (wg_per_cu > 0) {
-        const size_t share = lds_per_cu() / (size_t)wg_per_cu;
-        if (share > lds + kSplitStaticLds) lds = share - kSplitStaticLds;
-    }
+    if (share > lds + kSplitStaticLds) lds = share - kSplitStaticLds;
     if (lds + kSplitStaticLds > 65536 || lds + kSplitStaticLds > split_lds_limit()) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)((rows - row0 + kSplitWaves - 1) / kSplitWaves)), block(64 * kSplitWaves);
-    const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+    const int rows_wave = rows - row0 >= 32768 ? 4 : 1;
+    const int64_t per_wg = (int64_t)kSplitWaves * rows_wave;
+    const dim3 grid((unsigned)((rows - row0 + per_wg - 1) / per_wg));
+    const int skip_wp = min_np <= kQuadItems ? kQuadItems / 32 : 0;
     // registers for the keys of the largest pair: R blocks of 16 per lane
     const int r = (max_np + 1023) / 1024;
-#define HBT_SPLIT(RR) hipLaunchKernelGGL(k_split_masks<RR>, grid, block, lds, s, bp, npairs, rows, max_np, k0, k1, mask, sstat, row0)
-    if (r <= 1) HBT_SPLIT(1);
-    else if (r <= 2) HBT_SPLIT(2);
-    else if (r <= 4) HBT_SPLIT(4);
+#define HBT_SPLIT(RR)                                                                                             \
+    hipLaunchKernelGGL(k_split_masks<RR>, grid, block, lds, s, bp, npairs, rows, max_np, k0, k1, mask, sstat, row0, \
+                       skip_wp, ppr, rows_wave)
+    if (r <= 4) HBT_SPLIT(4);
     else if (r <= 8) HBT_SPLIT(8);
     else if (r <= 12) HBT_SPLIT(12);
     else if (r <= 16) HBT_SPLIT(16);
