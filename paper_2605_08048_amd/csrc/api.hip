@@ -10,7 +10,7 @@
 #include <map>
 #include <mutex>
 #include <string>
-#include <tuple>
+#include <unordered_map>
 #include <vector>
 
 #include "hbt_launch.h"
@@ -209,7 +209,7 @@ struct Plan {
     int min_np = 0, max_np = 0;  // smallest and largest padded pooled size
     std::vector<PairDesc> pairs;
     std::vector<BlockPair> bp;
-    std::vector<SumChunk> chunks;
+    int64_t nchunks = 0;          // column-sum chunks (chunk_of derives them on the device)
     std::vector<GemmTile> tiles;
     std::vector<GemmGroup> groups; // split BF16: the kTileWide groups, then the 256-wide ones
     int64_t ntile_total = 0;      // tiles of the split-BF16 kernel over all groups
@@ -268,8 +268,8 @@ Workspace carve(const Plan& P, void* ws) {
     w.tiles = c.take<GemmTile>(std::max<size_t>(P.tiles.size(), 1));
     w.groups = c.take<GemmGroup>(std::max<size_t>(P.groups.size(), 1));
     w.Btot = c.take<int64_t>(np);
-    w.partial_sum = c.take<double>(std::max<size_t>(P.chunks.size(), 1) * P.d);
-    w.chunk_bad = c.take<int32_t>(std::max<size_t>(P.chunks.size(), 1));
+    w.partial_sum = c.take<double>(std::max<int64_t>(P.nchunks, 1) * P.d);
+    w.chunk_bad = c.take<int32_t>(std::max<int64_t>(P.nchunks, 1));
     w.sxy = c.take<double>((size_t)np * 2 * P.d_pad);
     w.st = c.take<PairState>(np);
     w.v = c.take<double>((size_t)np * P.d_pad);
@@ -359,15 +359,12 @@ void add_pair(Plan& P, const void* X, const void* Y, int64_t n, int64_t m, uint3
     pd.coef0 = P.ncoef;
     pd.pair_index = pair_index;
     pd.flip = m < n ? 1 : 0;
-    const int p = (int)P.pairs.size();
-    pd.cx0 = (int32_t)P.chunks.size();
-    for (int64_t r = 0; r < n; r += kSumChunk)
-        P.chunks.push_back(SumChunk{p, 0, (int32_t)r, (int32_t)std::min<int64_t>(n, r + kSumChunk)});
-    pd.cx1 = (int32_t)P.chunks.size();
-    for (int64_t j = n / kSumChunkY; kSumChunkY * j < pd.Np; ++j)  // groups from row n to Np
-        P.chunks.push_back(SumChunk{p, 1, (int32_t)(std::max<int64_t>(n, kSumChunkY * j) - n),
-                                    (int32_t)(std::min<int64_t>(n + m, kSumChunkY * (j + 1)) - n)});
-    pd.cy1 = (int32_t)P.chunks.size();
+    // the X chunks, then the 32-row groups from the one holding row n to Np
+    pd.cx0 = (int32_t)P.nchunks;
+    P.nchunks += (n + kSumChunk - 1) / kSumChunk;
+    pd.cx1 = (int32_t)P.nchunks;
+    P.nchunks += pd.Np / kSumChunkY - n / kSumChunkY;
+    pd.cy1 = (int32_t)P.nchunks;
     pd.cy0 = pd.cx1;
     pd.zrow_y = P.zrows;
     pd.nxc = pd.Np / kRowPad;
@@ -531,6 +528,7 @@ void add_groups(Plan& P, const std::vector<int>& order, const int64_t* B, int pa
     const TileCost& tc = P.tune;
     Plan::Chunk c{pa, pb, (int)P.groups.size(), 0, 0, 0, 0};
     std::vector<GemmGroup> g2;
+    P.groups.reserve(P.groups.size() + order.size());
     for (int p : order) {
         const int w = P.precision == HBT_I8X3 ? kTileI8 : choose_width(B[p], tc);
         const int nbt = (int)((B[p] + w - 1) / w);
@@ -576,6 +574,53 @@ BlockPair block_pair(int64_t mrow0, int64_t mword0, uint64_t perm_base, int64_t 
 void add_ctiles(Plan& P, int p, int64_t nb) {
     for (int64_t b = 0; b < nb; b += kTileB)
         for (int i0 = 0; i0 < P.pairs[p].Np; i0 += kCTileRows) P.ctiles.push_back(CTile{p, (int32_t)b, i0, 0});
+}
+
+// The first pair with the same n, m, B and Philox word (identical splits: the
+// counters and the key are the same), whose masks the others read.  Only a
+// caller's own indices can repeat: the default ones count up.
+class SplitOwners {
+  public:
+    SplitOwners(bool may_repeat, size_t npairs) : may_repeat_(may_repeat) {
+        if (may_repeat) first_.reserve(npairs);
+    }
+    // the owner of pair p's splits: itself or an earlier pair
+    int of(int p, int64_t n, int64_t m, int64_t B, uint32_t idx) {
+        if (!may_repeat_) return p;
+        return first_.emplace(Key{(uint64_t)n << 32 | (uint64_t)m, B, idx}, p).first->second;
+    }
+
+  private:
+    struct Key {
+        uint64_t nm;
+        int64_t B;
+        uint32_t idx;
+        bool operator==(const Key& o) const { return nm == o.nm && B == o.B && idx == o.idx; }
+    };
+    struct Hash {
+        size_t operator()(const Key& k) const {
+            uint64_t h = (k.nm ^ ((uint64_t)k.B << 20) ^ ((uint64_t)k.idx << 41) ^ k.idx) * 0x9E3779B97F4A7C15ull;
+            return (size_t)(h ^ (h >> 29));
+        }
+    };
+    bool may_repeat_;
+    std::unordered_map<Key, int, Hash> first_;
+};
+
+// Pairs [pa, pb) by padded pooled size, largest first, equal sizes in order
+// (longest-processing-time order of the product's tiles).
+std::vector<int> largest_first(const Plan& P, int pa, int pb) {
+    std::vector<int> start((size_t)P.max_np / kRowPad + 2, 0);  // per size: pairs larger than it
+    for (int p = pa; p < pb; ++p) ++start[(size_t)(P.pairs[p].Np / kRowPad)];
+    int before = 0;
+    for (size_t k = start.size(); k-- > 0;) {
+        const int here = start[k];
+        start[k] = before;
+        before += here;
+    }
+    std::vector<int> order((size_t)(pb - pa));
+    for (int p = pa; p < pb; ++p) order[(size_t)start[(size_t)(P.pairs[p].Np / kRowPad)]++] = p;
+    return order;
 }
 
 // Single-pair plan with blocks of B0 splits.
@@ -625,14 +670,14 @@ hbt_status enqueue_prologue(const Plan& P, const Workspace& w, int align, int gd
     }
     StageTimer t(HBT_STAGE_ALIGN, s);
     if (vector_rows(P) && P.need_store)
-        HIP_TRY(launch_colsum_store_vec(P.precision, w.pairs, P.npairs, (int)P.chunks.size(), P.d,
+        HIP_TRY(launch_colsum_store_vec(P.precision, w.pairs, P.npairs, (int)P.nchunks, P.d,
                                         P.d_pad, w.partial_sum, w.zstore, P.zrows * P.d_pad, w.z32,
                                         w.chunk_bad, s));
     else if (vector_rows(P))
-        HIP_TRY(launch_colsum_vec(w.pairs, P.npairs, (int)P.chunks.size(), P.d, P.d_pad, w.partial_sum,
+        HIP_TRY(launch_colsum_vec(w.pairs, P.npairs, (int)P.nchunks, P.d, P.d_pad, w.partial_sum,
                                   w.chunk_bad, s));
     else
-        HIP_TRY(launch_colsum(P.input_dtype, w.pairs, P.npairs, (int)P.chunks.size(), P.d,
+        HIP_TRY(launch_colsum(P.input_dtype, w.pairs, P.npairs, (int)P.nchunks, P.d,
                               w.partial_sum, w.chunk_bad, s));
     HIP_TRY(launch_finalize(w.pairs, P.npairs, w.partial_sum, w.chunk_bad, P.d, P.d_pad, align, gd, w.sxy, w.st,
                             w.v, w.t64, w.t32, w.cnt, res, s));
@@ -1130,16 +1175,17 @@ static bool plan_clouds(Plan& P, int64_t nclouds, const void* Z_all, const int64
         cd.zrow0 = P.zrows;
         cd.zrow_y = P.zrows;
         cd.nxc = cd.Np / kRowPad;
-        cd.cx0 = cd.cx1 = cd.cy0 = (int32_t)P.chunks.size();
-        for (int64_t j = 0; kSumChunkY * j < cd.Np; ++j)
-            P.chunks.push_back(SumChunk{(int32_t)c, 1, (int32_t)(kSumChunkY * j),
-                                        (int32_t)std::min<int64_t>(cd.m, kSumChunkY * (j + 1))});
-        cd.cy1 = (int32_t)P.chunks.size();
+        cd.cx0 = cd.cx1 = cd.cy0 = (int32_t)P.nchunks;
+        P.nchunks += cd.Np / kSumChunkY;
+        cd.cy1 = (int32_t)P.nchunks;
         P.zrows += cd.Np;
         P.cdesc.push_back(cd);
     }
     int64_t rows = 0, words = 0;
-    std::map<std::tuple<int64_t, int64_t, int64_t, uint32_t>, int> first;
+    SplitOwners owners(pair_index != nullptr, (size_t)npairs);
+    P.pairs.reserve((size_t)npairs);
+    P.bp.reserve((size_t)npairs);
+    P.Btot.assign(B, B + npairs);
     for (int64_t p = 0; p < npairs; ++p) {
         const PairDesc& cx = P.cdesc[(size_t)pair_x[p]];
         const PairDesc& cy = P.cdesc[(size_t)pair_y[p]];
@@ -1167,25 +1213,15 @@ static bool plan_clouds(Plan& P, int64_t nclouds, const void* Z_all, const int64
     P.max_np = std::max(P.max_np, (int)pd.Np);
         P.fold_segs = std::max(P.fold_segs, fold_segments(pd.n));
         P.pairs.push_back(pd);
-        const auto key = std::make_tuple((int64_t)pd.n, (int64_t)pd.m, B[p], pd.pair_index);
-        const auto hit = first.find(key);
-        if (hit == first.end()) {
-            first.emplace(key, (int)p);
-            P.bp.push_back(block_pair(rows, words, common->perm_offset, B[p], (int)p, pd));
-            words += B[p] * pd.Wp;
-        } else {
-            const BlockPair& o = P.bp[(size_t)hit->second];
-            P.bp.push_back(block_pair(rows, o.mword0, common->perm_offset, B[p], hit->second, pd));
-        }
-        P.Btot.push_back(B[p]);
+        const int own = owners.of((int)p, pd.n, pd.m, B[p], pd.pair_index);
+        P.bp.push_back(block_pair(rows, own == (int)p ? words : P.bp[(size_t)own].mword0, common->perm_offset, B[p], own,
+                                  pd));
+        if (own == (int)p) words += B[p] * pd.Wp;
         rows += B[p];
     }
     P.npairs = (int)npairs;
     finish_plan(P, d, common->precision, common->input_dtype);
-    std::vector<int> order((size_t)npairs);
-    for (int64_t p = 0; p < npairs; ++p) order[(size_t)p] = (int)p;
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return P.pairs[a].Np > P.pairs[b].Np; });
-    add_groups(P, order, B, 0, (int)npairs);
+    add_groups(P, largest_first(P, 0, (int)npairs), B, 0, (int)npairs);
     P.block_rows = rows;
     P.block_mask_words = words;
     return true;
@@ -1206,38 +1242,24 @@ static bool plan_batched(Plan& P, int64_t npairs, const void* Z_all, const int64
                          const uint32_t* pair_index, int64_t d, const hbt_perm_params* common) {
     const size_t es = common->input_dtype == HBT_IN_F64 ? 8 : 4;
     int64_t rows = 0, words = 0;
-    // Pairs with equal n, m, B and pair index get identical splits (the
-    // counters and the key are the same): the first of them draws the masks
-    // and the others read its mask words.
-    std::map<std::tuple<int64_t, int64_t, int64_t, uint32_t>, int> first;
+    SplitOwners owners(pair_index != nullptr, (size_t)npairs);
+    P.pairs.reserve((size_t)npairs);
+    P.bp.reserve((size_t)npairs);
+    P.Btot.assign(B, B + npairs);
     for (int64_t p = 0; p < npairs; ++p) {
         const char* X = Z_all ? (const char*)Z_all + (size_t)row_offset[p] * d * es : nullptr;
         const char* Y = X ? X + (size_t)n[p] * d * es : nullptr;
         const uint32_t idx = pair_index ? pair_index[p] : common->pair_index + (uint32_t)p;
         add_pair(P, X, Y, n[p], m[p], idx);
-        const auto key = std::make_tuple(n[p], m[p], B[p], idx);
-        const auto hit = first.find(key);
-        if (hit == first.end()) {
-            first.emplace(key, (int)p);
-            P.bp.push_back(block_pair(rows, words, common->perm_offset, B[p], (int)p, P.pairs.back()));
-            words += B[p] * P.pairs.back().Wp;
-        } else {
-            const BlockPair& o = P.bp[(size_t)hit->second];
-            P.bp.push_back(block_pair(rows, o.mword0, common->perm_offset, B[p], hit->second, P.pairs.back()));
-        }
-        P.Btot.push_back(B[p]);
+        const PairDesc& pd = P.pairs.back();
+        const int own = owners.of((int)p, n[p], m[p], B[p], idx);
+        P.bp.push_back(block_pair(rows, own == (int)p ? words : P.bp[(size_t)own].mword0, common->perm_offset, B[p], own,
+                                  pd));
+        if (own == (int)p) words += B[p] * pd.Wp;
         rows += B[p];
     }
     finish_plan(P, d, common->precision, common->input_dtype);
-    // tiles, largest pooled size first (longest-processing-time order)
-    auto by_size = [&](int pa, int pb) {
-        std::vector<int> order;
-        for (int p = pa; p < pb; ++p) order.push_back(p);
-        std::stable_sort(order.begin(), order.end(),
-                         [&](int a, int b) { return P.pairs[a].Np > P.pairs[b].Np; });
-        return order;
-    };
-    const std::vector<int> order = by_size(0, (int)npairs);
+    const std::vector<int> order = largest_first(P, 0, (int)npairs);
     // the tile list of the FP32 / FP64 products (the others use the groups)
     const int tb = groupsum_tile_splits(P.precision);
     if (P.precision == HBT_F32 || P.precision == HBT_F64)
@@ -1259,7 +1281,7 @@ static bool plan_batched(Plan& P, int64_t npairs, const void* Z_all, const int64
             acc += (double)B[p] * P.pairs[p].Np;
             const int k = (int)P.cplan.size();
             if (p + 1 == npairs || (acc >= total * (k + 1) / nchunk && k + 1 < nchunk)) {
-                add_groups(P, by_size(pa, (int)p + 1), B, pa, (int)p + 1);
+                add_groups(P, largest_first(P, pa, (int)p + 1), B, pa, (int)p + 1);
                 pa = (int)p + 1;
             }
         }
@@ -1605,7 +1627,7 @@ hbt_status hbt_perm_test_clouds(int64_t nclouds, const void* Z_all, const int64_
         // every cloud summed and stored once; per pair the directions, v, T_obs
         // and the reflected total; then the pairs' coefficients 2 (v . x_i) / (v . v)
         StageTimer t_(HBT_STAGE_ALIGN, s);
-        HIP_TRY(launch_colsum_store_vec(P.precision, w.cdesc, (int)P.cdesc.size(), (int)P.chunks.size(), P.d,
+        HIP_TRY(launch_colsum_store_vec(P.precision, w.cdesc, (int)P.cdesc.size(), (int)P.nchunks, P.d,
                                         P.d_pad, w.partial_sum, w.zstore, P.zrows * P.d_pad, nullptr,
                                         w.chunk_bad, s));
         HIP_TRY(launch_finalize(w.pairs, np, w.partial_sum, w.chunk_bad, P.d, P.d_pad, common->align, common->gd,

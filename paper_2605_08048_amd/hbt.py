@@ -207,12 +207,13 @@ def _input_dtype(X):
 
 
 def results_to_numpy(res_tensor):
-    raw = res_tensor.cpu().numpy().tobytes()
-    return np.frombuffer(raw, dtype=RESULT_DTYPE).copy()
+    host = res_tensor.cpu()
+    r = host.reshape(-1).numpy().view(RESULT_DTYPE)
+    return r.copy() if host is res_tensor else r
 
 
 def _result_dict(row):
-    return {k: (row[k].item()) for k in RESULT_DTYPE.names}
+    return dict(zip(RESULT_DTYPE.names, row.item()))
 
 
 def make_params(n, m, d, B, *, seed=0, perm_offset=0, pair_index=0, precision="f32", input_dtype=0,
@@ -240,7 +241,7 @@ def align(X, Y, *, align=True, gd="banerjee", out=None, stream=None):
             raise HbtError(ERR_ARG, f"out must be a contiguous {X.dtype} tensor of shape {tuple(X.shape)}")
     Xo = out if out is not None else torch.empty_like(X)
     v = torch.empty(d, dtype=torch.float64, device=dev)
-    res = torch.zeros(RESULT_BYTES, dtype=torch.uint8, device=dev)
+    res = torch.empty(RESULT_BYTES, dtype=torch.uint8, device=dev)  # every field is written
     L = lib()
     need = L.hbt_align_workspace_size(n, m, d)
     ws = workspace(need, dev)
@@ -286,7 +287,7 @@ def perm_test(X, Y, B, *, seed=0, perm_offset=0, pair_index=0, precision="f32", 
     if want_T == "norms":
         prm.flags |= FLAG_T_OUT_NORMS
     L = lib()
-    res = torch.zeros(RESULT_BYTES, dtype=torch.uint8, device=dev)
+    res = torch.empty(RESULT_BYTES, dtype=torch.uint8, device=dev)  # every field is written
     T = torch.empty((B, 3) if want_T == "norms" else B, dtype=torch.float64 if t64 else torch.float32,
                     device=dev) if want_T else None
     mo = torch.empty((B, W), dtype=torch.int32, device=dev) if want_masks else None
@@ -406,7 +407,7 @@ def perm_test_batched(Z_all, row_offset, n, m, B, *, seed=0, perm_offset=0, pair
         ws = workspace
         if ws.numel() < need:
             raise ValueError(f"workspace of {ws.numel()} bytes, the call needs {need}")
-    res = results if results is not None else torch.zeros(RESULT_BYTES * P, dtype=torch.uint8, device=dev)
+    res = results if results is not None else torch.empty(RESULT_BYTES * P, dtype=torch.uint8, device=dev)
     _check(L.hbt_perm_test_batched(P, C.c_void_p(Z_all.data_ptr()), ptr(off), ptr(nn), ptr(mm), ptr(BB),
                                    None if ids is None else ptr(ids), d, C.byref(prm),
                                    C.c_void_p(res.data_ptr()), C.c_void_p(ws.data_ptr()), ws.numel(),
@@ -458,7 +459,7 @@ def perm_test_clouds(Z_all, cloud_offset, cloud_rows, pair_x, pair_y, B, *, seed
         _on_device("results", results, dev)
         if results.dtype != torch.uint8 or results.numel() < RESULT_BYTES * P or not results.is_contiguous():
             raise HbtError(ERR_SIZE, f"results must be a contiguous uint8 tensor of {RESULT_BYTES * P} bytes")
-    res = results if results is not None else torch.zeros(RESULT_BYTES * P, dtype=torch.uint8, device=dev)
+    res = results if results is not None else torch.empty(RESULT_BYTES * P, dtype=torch.uint8, device=dev)
     _check(L.hbt_perm_test_clouds(rows.size, C.c_void_p(Z_all.data_ptr()), ptr(off), ptr(rows), P, ptr(px),
                                   ptr(py), ptr(BB), None if ids is None else ptr(ids), d, C.byref(prm),
                                   C.c_void_p(res.data_ptr()), C.c_void_p(ws.data_ptr()), ws.numel(),
