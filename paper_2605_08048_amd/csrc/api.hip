@@ -186,6 +186,7 @@ struct Workspace {
     uint32_t* rcnt;     // per pair: their number
     GemmGroup* rgroups; // tile table of the refinement product (one group per product group)
     int64_t* rtiles;    // its tile count
+    unsigned char* blob; // description the device builds a batched call's tables from
     size_t bytes;
 };
 
@@ -237,6 +238,7 @@ struct Plan {
     bool fold = false;             // pairs of shared clouds, stored unreflected
     int fold_segs = 0;             // the largest pair's fold_segments(n)
     std::vector<PairDesc> cdesc;   // their clouds
+    bool batched = false;          // a batched or shared-clouds call: its tables are built on the device
 };
 
 // The product kernels number their tiles with 32-bit integers.  A plan whose
@@ -341,6 +343,9 @@ Workspace carve(const Plan& P, void* ws) {
         w.rgroups = nullptr;
         w.rtiles = nullptr;
     }
+    // per pair at most 32 bytes (sizes or clouds, offset, splits, Philox word,
+    // owner, order), per cloud 12, and the arrays' alignment
+    w.blob = P.batched ? c.take<unsigned char>((size_t)np * 32 + P.cdesc.size() * 12 + 128) : nullptr;
     w.bytes = c.off + 256;
     return w;
 }
@@ -757,6 +762,108 @@ int64_t recheck_slot_budget(int npairs, int d_pad) {
     return v < held ? (int64_t)v : held;
 }
 
+// The tables of a batched call (one pipeline chunk) from its compact
+// description: upload and one kernel, which also clears the counters.
+// row_offset: of the pairs, or of the clouds.
+hipError_t build_tables(const Plan& P, const Workspace& w, const char* base, const int64_t* row_offset,
+                        const int64_t* B, const uint32_t* pair_index, const int64_t* pair_x, const int64_t* pair_y,
+                        const hbt_perm_params* common, hipStream_t s) {
+    const size_t np = P.pairs.size(), nc = P.cdesc.size();
+    std::vector<unsigned char> blob;
+    blob.reserve(np * 8 + nc * 4 + 64);
+    auto array = [&](size_t count, size_t size) {  // room for an aligned array; its offset
+        const size_t at = (blob.size() + size - 1) / size * size;
+        blob.resize(at + count * size);
+        return (int32_t)at;
+    };
+    TableArgs A;
+    memset(&A, 0, sizeof A);
+    A.blob = w.blob;
+    A.base = base;
+    A.row_bytes = (int64_t)P.d * (P.input_dtype == HBT_IN_F64 ? 8 : 4);
+    A.npairs = (int32_t)np;
+    A.nclouds = (int32_t)nc;
+    A.o_sizes = A.o_cloud_rows = A.o_pair_x = A.o_pair_y = A.o_offset = A.o_splits = A.o_index = A.o_owner = -1;
+    // first rows that are not the running sum of the sizes
+    const std::vector<PairDesc>& runs = nc ? P.cdesc : P.pairs;
+    int64_t next = A.offset0 = row_offset[0];
+    bool running = true;
+    for (size_t k = 0; k < runs.size() && running; ++k) {
+        running = row_offset[k] == next;
+        next += runs[k].n + runs[k].m;
+    }
+    if (!running) {
+        A.o_offset = array(runs.size(), 8);
+        memcpy(&blob[(size_t)A.o_offset], row_offset, runs.size() * 8);
+    }
+    A.splits0 = (uint32_t)B[0];
+    bool same = true, own = true;
+    for (size_t p = 0; p < np; ++p) {
+        same &= B[p] == B[0];
+        own &= P.bp[p].owner == (int32_t)p;
+    }
+    auto fill32 = [&](int32_t at, auto value) {
+        for (size_t p = 0; p < np; ++p) {
+            const uint32_t v = value(p);
+            memcpy(&blob[(size_t)at + 4 * p], &v, 4);
+        }
+    };
+    if (nc) {
+        A.o_cloud_rows = array(nc, 4);
+        for (size_t c = 0; c < nc; ++c) {
+            const uint32_t v = (uint32_t)P.cdesc[c].m;
+            memcpy(&blob[(size_t)A.o_cloud_rows + 4 * c], &v, 4);
+        }
+    } else {
+        A.o_sizes = array(np, 4);
+        fill32(A.o_sizes, [&](size_t p) { return (uint32_t)P.pairs[p].n | (uint32_t)P.pairs[p].m << 16; });
+    }
+    if (!same) {
+        A.o_splits = array(np, 4);
+        fill32(A.o_splits, [&](size_t p) { return (uint32_t)B[p]; });
+    }
+    A.index0 = common->pair_index;
+    if (pair_index) {
+        A.o_index = array(np, 4);
+        fill32(A.o_index, [&](size_t p) { return pair_index[p]; });
+    }
+    if (!own) {
+        A.o_owner = array(np, 4);
+        fill32(A.o_owner, [&](size_t p) { return (uint32_t)P.bp[p].owner; });
+    }
+    auto indices = [&](size_t count, bool narrow, auto value) {
+        const int32_t at = array(count, narrow ? 2 : 4);
+        for (size_t k = 0; k < count; ++k) {
+            const uint32_t v = (uint32_t)value(k);  // little-endian: the low two bytes first
+            memcpy(&blob[(size_t)at + k * (narrow ? 2 : 4)], &v, narrow ? 2 : 4);
+        }
+        return at;
+    };
+    if (nc) {
+        A.narrow_clouds = nc <= 65536;
+        A.o_pair_x = indices(np, A.narrow_clouds, [&](size_t p) { return pair_x[p]; });
+        A.o_pair_y = indices(np, A.narrow_clouds, [&](size_t p) { return pair_y[p]; });
+    }
+    A.ngroups = (int32_t)P.groups.size();
+    A.ngw = P.ngw;
+    A.narrow_order = np <= 65536;
+    A.o_order = indices(P.groups.size(), A.narrow_order, [&](size_t g) { return P.groups[g].pair; });
+    A.width_wide = kTileWide;
+    A.width_narrow = P.precision == HBT_I8X3 ? kTileI8 : kTileNarrow;
+    A.nslot = P.nslot;
+    A.perm_base = (uint32_t)common->perm_offset;
+    A.pairs = w.pairs;
+    A.cdesc = w.cdesc;
+    A.bp = w.bp;
+    A.groups = w.groups;
+    A.Btot = w.Btot;
+    A.nflag = w.nflag;
+    A.rcnt = w.rcnt;
+    A.sstat = w.sstat;
+    hipError_t e = upload(w.blob, blob.data(), blob.size(), s);
+    return e != hipSuccess ? e : launch_build_tables(A, s);
+}
+
 // The stages after the group sums: statistic and counts, recheck, null
 // moments, p-values.
 hbt_status batched_epilogue(const Plan& P, const Workspace& w, const hbt_perm_params* common,
@@ -1161,6 +1268,7 @@ static bool plan_clouds(Plan& P, int64_t nclouds, const void* Z_all, const int64
                         const int64_t* pair_y, const int64_t* B, const uint32_t* pair_index, int64_t d,
                         const hbt_perm_params* common) {
     P.fold = true;
+    P.batched = true;
     for (int64_t c = 0; c < nclouds; ++c) {
         const char* base = Z_all ? (const char*)Z_all + (size_t)cloud_offset[c] * d * 4 : nullptr;
         P.aligned16 = P.aligned16 && ((uintptr_t)base % 16 == 0);
@@ -1242,6 +1350,7 @@ static bool plan_batched(Plan& P, int64_t npairs, const void* Z_all, const int64
                          const uint32_t* pair_index, int64_t d, const hbt_perm_params* common) {
     const size_t es = common->input_dtype == HBT_IN_F64 ? 8 : 4;
     int64_t rows = 0, words = 0;
+    P.batched = true;
     SplitOwners owners(pair_index != nullptr, (size_t)npairs);
     P.pairs.reserve((size_t)npairs);
     P.bp.reserve((size_t)npairs);
@@ -1341,46 +1450,31 @@ hbt_status hbt_perm_test_batched(int64_t npairs, const void* Z_all, const int64_
     Workspace w = carve(P, ws);
     const int np = P.npairs;
     if (P.cplan.size() > 1) return batched_pipelined(P, w, common, results, s);
-    // Three streams until the group sums: the caller's uploads the pair table
-    // and aligns; a second one uploads the block table (all the split stage
-    // reads) and draws the splits, which depend only on the seeds and the
-    // group sizes (integer VALU work beside HBM-bound work); a third uploads
-    // the tables only the later stages read.  The table uploads are chains of
-    // small kernels (a few microseconds each), so no chain waits for another.
+    // The tables first; then the caller's stream aligns while a second one
+    // draws the splits, which depend only on the seeds and the group sizes
+    // (integer VALU work beside HBM-bound work).
     // At most 6 split work-groups per CU (the default split_cap) leave
     // wave slots to the alignment kernels (measured on 512 pairs, d = 768,
     // split BF16: 8.03 ms per call at 8 or uncapped, where the alignment
     // then waits for wave slots; 7.25 ms at 6, the two stages 2.1 ms each;
     // 7.56 ms at 5, 7.63 ms at 4).
-    hipStream_t qs, qt;
+    hipStream_t qs;
     HIP_TRY(side_stream(&qs, 0));
-    HIP_TRY(side_stream(&qt, 1));
     Events ev;
     hipEvent_t e0;
-    HIP_TRY(ev.record(s, &e0));
-    HIP_TRY(hipStreamWaitEvent(qs, e0, 0));
-    HIP_TRY(hipStreamWaitEvent(qt, e0, 0));
-    {
-        StageTimer t_(HBT_STAGE_SPLIT, qs);
-        HIP_TRY(upload(w.bp, P.bp.data(), P.bp.size() * sizeof(BlockPair), qs));
-        HIP_TRY(zero(w.sstat, (size_t)(np + 1) / 2 * 8, qs));
-        HIP_TRY(launch_split_masks(w.bp, np, P.block_rows, P.min_np, P.max_np, common->seed, w.mask, w.sstat,
-                                   P.tune.split_cap, qs));
-    }
-    {
-        StageTimer t_(HBT_STAGE_OTHER, qt);
-        if (P.precision == HBT_BF16X2 || P.precision == HBT_I8X3 || P.precision == HBT_BF16_E4M3)
-            HIP_TRY(upload(w.groups, P.groups.data(), P.groups.size() * sizeof(GemmGroup), qt));
-        else
-            HIP_TRY(upload(w.tiles, P.tiles.data(), P.tiles.size() * sizeof(GemmTile), qt));
-        HIP_TRY(upload(w.Btot, P.Btot.data(), P.Btot.size() * sizeof(int64_t), qt));
-        HIP_TRY(zero(w.nflag, (size_t)(np + 1) / 2 * 8, qt));
-        if (P.lazy) HIP_TRY(zero(w.rcnt, (size_t)(np + 1) / 2 * 8, qt));
-        if (P.route2) HIP_TRY(upload(w.ctiles, P.ctiles.data(), P.ctiles.size() * sizeof(CTile), qt));
-    }
     {
         StageTimer t_(HBT_STAGE_OTHER, s);
-        HIP_TRY(upload(w.pairs, P.pairs.data(), P.pairs.size() * sizeof(PairDesc), s));
+        HIP_TRY(build_tables(P, w, (const char*)Z_all, row_offset, B, pair_index, nullptr, nullptr, common, s));
+        if (!P.tiles.empty())
+            HIP_TRY(upload(w.tiles, P.tiles.data(), P.tiles.size() * sizeof(GemmTile), s));
+        if (P.route2) HIP_TRY(upload(w.ctiles, P.ctiles.data(), P.ctiles.size() * sizeof(CTile), s));
+    }
+    HIP_TRY(ev.record(s, &e0));
+    HIP_TRY(hipStreamWaitEvent(qs, e0, 0));
+    {
+        StageTimer t_(HBT_STAGE_SPLIT, qs);
+        HIP_TRY(launch_split_masks(w.bp, np, P.block_rows, P.min_np, P.max_np, common->seed, w.mask, w.sstat,
+                                   P.tune.split_cap, qs));
     }
     st = enqueue_prologue(P, w, common->align, common->gd, results, s, false);
     if (st) return st;
@@ -1389,8 +1483,6 @@ hbt_status hbt_perm_test_batched(int64_t npairs, const void* Z_all, const int64_
         HIP_TRY(reflect(P, w, P.route2 ? w.z32 : nullptr, s));
     }
     HIP_TRY(ev.record(qs, &e0));
-    HIP_TRY(hipStreamWaitEvent(s, e0, 0));
-    HIP_TRY(ev.record(qt, &e0));
     HIP_TRY(hipStreamWaitEvent(s, e0, 0));
     {
         StageTimer t_(HBT_STAGE_GROUPSUM, s);
@@ -1597,31 +1689,20 @@ hbt_status hbt_perm_test_clouds(int64_t nclouds, const void* Z_all, const int64_
     hipStream_t s = (hipStream_t)stream;
     Workspace w = carve(P, ws);
     const int np = P.npairs;
-    hipStream_t qs, qt;
+    hipStream_t qs;
     HIP_TRY(side_stream(&qs, 0));
-    HIP_TRY(side_stream(&qt, 1));
     Events ev;
     hipEvent_t e0;
-    HIP_TRY(ev.record(s, &e0));
-    HIP_TRY(hipStreamWaitEvent(qs, e0, 0));
-    HIP_TRY(hipStreamWaitEvent(qt, e0, 0));
-    {
-        StageTimer t_(HBT_STAGE_SPLIT, qs);
-        HIP_TRY(upload(w.bp, P.bp.data(), P.bp.size() * sizeof(BlockPair), qs));
-        HIP_TRY(zero(w.sstat, (size_t)(np + 1) / 2 * 8, qs));
-        HIP_TRY(launch_split_masks(w.bp, np, P.block_rows, P.min_np, P.max_np, common->seed, w.mask, w.sstat,
-                                   P.tune.split_cap, qs));
-    }
-    {
-        StageTimer t_(HBT_STAGE_OTHER, qt);
-        HIP_TRY(upload(w.groups, P.groups.data(), P.groups.size() * sizeof(GemmGroup), qt));
-        HIP_TRY(upload(w.Btot, P.Btot.data(), P.Btot.size() * sizeof(int64_t), qt));
-        HIP_TRY(zero(w.nflag, (size_t)(np + 1) / 2 * 8, qt));
-    }
     {
         StageTimer t_(HBT_STAGE_OTHER, s);
-        HIP_TRY(upload(w.cdesc, P.cdesc.data(), P.cdesc.size() * sizeof(PairDesc), s));
-        HIP_TRY(upload(w.pairs, P.pairs.data(), P.pairs.size() * sizeof(PairDesc), s));
+        HIP_TRY(build_tables(P, w, (const char*)Z_all, cloud_offset, B, pair_index, pair_x, pair_y, common, s));
+    }
+    HIP_TRY(ev.record(s, &e0));
+    HIP_TRY(hipStreamWaitEvent(qs, e0, 0));
+    {
+        StageTimer t_(HBT_STAGE_SPLIT, qs);
+        HIP_TRY(launch_split_masks(w.bp, np, P.block_rows, P.min_np, P.max_np, common->seed, w.mask, w.sstat,
+                                   P.tune.split_cap, qs));
     }
     {
         // every cloud summed and stored once; per pair the directions, v, T_obs
@@ -1635,8 +1716,6 @@ hbt_status hbt_perm_test_clouds(int64_t nclouds, const void* Z_all, const int64_
         HIP_TRY(launch_fold_coef(w.pairs, np, w.st, w.v, P.d, P.d_pad, P.ncoef, w.coef, s));
     }
     HIP_TRY(ev.record(qs, &e0));
-    HIP_TRY(hipStreamWaitEvent(s, e0, 0));
-    HIP_TRY(ev.record(qt, &e0));
     HIP_TRY(hipStreamWaitEvent(s, e0, 0));
     {
         StageTimer t_(HBT_STAGE_GROUPSUM, s);

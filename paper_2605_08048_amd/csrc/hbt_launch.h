@@ -18,6 +18,38 @@ hipError_t upload(void* dst, const void* src, size_t bytes, hipStream_t s);
 // Zero `bytes` (a multiple of 8) of device memory with a fill kernel.
 hipError_t zero(void* dst, size_t bytes, hipStream_t s);
 
+// --- tables of a batched call ---------------------------------------------
+// What the device builds a batched call's tables from: `blob` holds the arrays
+// below at their byte offsets (a negative offset: the rule beside it).
+struct TableArgs {
+    const unsigned char* blob;
+    const char* base;         // Z_all
+    int64_t row_bytes;
+    int32_t npairs, nclouds;  // nclouds = 0: rows X_p, Y_p of each pair
+    int32_t o_sizes;          // uint32 n | m << 16 per pair (nclouds = 0)
+    int32_t o_cloud_rows;     // uint32 per cloud
+    int32_t o_pair_x, o_pair_y;  // cloud of X, of Y per pair
+    int32_t narrow_clouds;       // these two are uint16, else uint32
+    int32_t o_offset;         // int64 first row per pair (cloud); else offset0 + the rows before
+    int32_t o_splits;         // uint32 B per pair; else splits0
+    int32_t o_index;          // uint32 Philox word per pair; else index0 + p
+    int32_t o_owner;          // uint32 owner of the pair's splits; else itself
+    int32_t o_order;          // pair of each product group
+    int32_t narrow_order;     // uint16, else uint32
+    int32_t ngroups, ngw;     // groups, of which the first ngw of width_wide
+    int32_t width_wide, width_narrow, nslot;
+    uint32_t splits0, index0, perm_base;
+    int64_t offset0;
+    PairDesc *pairs, *cdesc;
+    BlockPair* bp;
+    GemmGroup* groups;
+    int64_t* Btot;
+    uint32_t* nflag;  // cleared, as are rcnt (nullable) and sstat
+    uint32_t* rcnt;
+    int32_t* sstat;
+};
+hipError_t launch_build_tables(const TableArgs& A, hipStream_t s);
+
 // --- alignment (Algorithm 1, Steps 1-4) ---------------------------------
 // FP64 column sums of every chunk: partial[chunk][d].
 // chunk_bad[chunk] = 1 when a row of the chunk is not a unit vector
