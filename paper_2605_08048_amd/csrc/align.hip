@@ -15,20 +15,23 @@ struct UploadChunk {
     unsigned char b[3072];
 };
 
-__global__ void k_upload(unsigned char* dst, UploadChunk c, int bytes) {
+__global__ void k_upload(unsigned char* dst, UploadChunk c, int bytes, uint64_t* clear, int clear_words) {
     for (int i = threadIdx.x; i < bytes; i += blockDim.x) dst[i] = c.b[i];
+    for (int i = threadIdx.x; i < clear_words; i += blockDim.x) clear[i] = 0;
 }
 
-hipError_t upload(void* dst, const void* src, size_t bytes, hipStream_t s) {
+hipError_t upload(void* dst, const void* src, size_t bytes, hipStream_t s, void* clear, size_t clear_bytes) {
     const unsigned char* p = (const unsigned char*)src;
     unsigned char* q = (unsigned char*)dst;
+    int words = (int)(clear_bytes / 8);
     while (bytes) {
         const size_t k = bytes < sizeof(UploadChunk) ? bytes : sizeof(UploadChunk);
         UploadChunk c;
         memcpy(c.b, p, k);
-        hipLaunchKernelGGL(k_upload, dim3(1), dim3(256), 0, s, q, c, (int)k);
+        hipLaunchKernelGGL(k_upload, dim3(1), dim3(256), 0, s, q, c, (int)k, (uint64_t*)clear, words);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
+        words = 0;
         p += k;
         q += k;
         bytes -= k;
@@ -288,95 +291,181 @@ hipError_t launch_fold_coef(const PairDesc* pairs, int npairs, const PairState* 
 // ---------------------------------------------------------------------------
 // finalize: one work-group per pair
 // ---------------------------------------------------------------------------
-// Deterministic block sum of per-thread values (256 threads).
-__device__ double block_sum(double x, double* red) {
-    const int t = threadIdx.x;
-    red[t] = x;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (t < o) red[t] += red[t + o];
-        __syncthreads();
-    }
-    const double r = red[0];
-    __syncthreads();
-    return r;
-}
+// Bound by the memory rate of the CUs that read the chunk partials (103 chunks at
+// d = 1024 are 844 KB).  kFinPair, for batches, where the pairs fill the chip: one
+// work-group per pair, a column of a thread after the other, few registers (the
+// split kernel's waves share the CUs).  kFinSplit, for few pairs: work-group
+// (x, p) adds 64 columns of pair p, wave w the w-th quarter of X's chunks and of
+// Y's, and the last of the pair's work-groups to end does the rest (they count
+// themselves on the pair's ticket, each after its sums are visible to the whole
+// device; nobody waits for anybody).  One pair of 103 chunks: 16 us, against 32
+// with one work-group.  512 pairs, d = 768: 75 us with kFinPair, 1180 with
+// kFinSplit, whose fences write back caches full of other pairs' rows, 177 as two
+// launches.
+// Both sum in one order, so a pair's results do not depend on the call it is in:
+// a column's partials as four quarters, each in chunk order; a sum over columns
+// as if by fin_threads(d_pad) threads, thread t taking columns t, t + threads, ...,
+// then a butterfly in each wave, then the waves in order.
+enum FinalizeMode { kFinPair, kFinSplit };
+constexpr int kFinCols = 64;
+__host__ __device__ constexpr int fin_threads(int d_pad) { return d_pad >= 1024 ? 1024 : (d_pad + 255) / 256 * 256; }
 
-__global__ __launch_bounds__(256) void k_finalize(const PairDesc* __restrict__ pairs,
-                                                  const double* __restrict__ partial,
-                                                  const int32_t* __restrict__ chunk_bad, int d,
-                                                  int d_pad, int align, int gd, double* sxy,
-                                                  PairState* st, double* v, double* t64,
-                                                  float* t32, PairCount* cnt, hbt_result* res,
-                                                  int p0, float* __restrict__ v32) {
-    __shared__ double red[256];
-    const int p = blockIdx.x + p0;
+template <int MODE>
+__global__ __launch_bounds__(256) void k_finalize(
+    const PairDesc* __restrict__ pairs, const double* __restrict__ partial, const int32_t* __restrict__ chunk_bad,
+    int d, int d_pad, int align, int gd, double* sxy, PairState* st, double* v, double* t64, float* t32,
+    PairCount* cnt, hbt_result* res, int p0, float* __restrict__ v32, uint32_t* ticket) {
+    __shared__ double red[16];
+    __shared__ double part[2][4][kFinCols];
+    __shared__ uint32_t before;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int p = (MODE == kFinPair ? blockIdx.x : blockIdx.y) + p0;
     const PairDesc pd = pairs[p];
     double* sx = sxy + (int64_t)p * 2 * d_pad;
     double* sy = sx + d_pad;
     double* vp = v + (int64_t)p * d_pad;
     double* tp = t64 + (int64_t)p * d_pad;
     float* tq = t32 + (int64_t)p * d_pad;
-    // Step 1: sums of X and Y, chunk partials added in chunk order (eight
-    // loads in flight at a time; the additions keep that order)
-    auto chunk_sum = [&](int k0, int k1, int c) {
+    // Step 1: sums of X and Y
+    auto quarter = [&](int k0, int k1, int q, int c) {
+        const int per = (k1 - k0 + 3) / 4, a = k0 + q * per, b = a + per < k1 ? a + per : k1;
         double acc = 0.0;
-        int k = k0;
-        for (; k + 8 <= k1; k += 8) {
-            double t[8];
+        for (int k = a; k < b; k += 16) {
+            double t[16];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) t[u] = partial[(int64_t)(k + u) * d + c];
+            for (int u = 0; u < 16; ++u) t[u] = partial[(int64_t)(k + u < b ? k + u : b - 1) * d + c];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) acc += t[u];
+            for (int u = 0; u < 16; ++u)
+                if (k + u < b) acc += t[u];  // uniform
         }
-        for (; k < k1; ++k) acc += partial[(int64_t)k * d + c];
         return acc;
     };
+    if constexpr (MODE == kFinSplit) {
+        const int c = kFinCols * blockIdx.x + lane;
+        part[0][wave][lane] = c < d ? quarter(pd.cx0, pd.cx1, wave, c) : 0.0;
+        part[1][wave][lane] = c < d ? quarter(pd.cy0, pd.cy1, wave, c) : 0.0;
+        __syncthreads();
+        if (wave < 2)
+            (wave ? sy : sx)[c] = (part[wave][0][lane] + part[wave][1][lane]) + (part[wave][2][lane] + part[wave][3][lane]);
+        // the work-group's sums (the barrier), then device-wide (thread 0's
+        // release); the other work-groups' sums likewise through its acquire
+        __syncthreads();
+        if (threadIdx.x == 0)
+            before = __hip_atomic_fetch_add(&ticket[p], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (before != gridDim.x - 1) return;
+    }
+    // this thread stands for the threads threadIdx.x + 256 j < nt, j < kSlots;
+    // the sums and v of their first columns stay in registers, those of others
+    // (d_pad > 1024) pass through memory
+    constexpr int kSlots = 4;
+    const int nt = fin_threads(d_pad);
     int bad = 0;
     for (int k = pd.cx0 + threadIdx.x; k < pd.cx1; k += 256) bad |= chunk_bad[k];
     for (int k = pd.cy0 + threadIdx.x; k < pd.cy1; k += 256) bad |= chunk_bad[k];
-    bad = __syncthreads_or(bad);
-    double ssx = 0.0, ssy = 0.0;
-    for (int c = threadIdx.x; c < d_pad; c += 256) {
-        double a = 0.0, b = 0.0;
-        if (c < d) {
-            a = chunk_sum(pd.cx0, pd.cx1, c);
-            b = chunk_sum(pd.cy0, pd.cy1, c);
+    double x4[kSlots], y4[kSlots], v4[kSlots];
+    if constexpr (MODE == kFinPair) {
+        auto column = [&](int k0, int k1, int c) {  // four chunks of each quarter in flight
+            const int per = (k1 - k0 + 3) / 4;
+            double q[4] = {0.0, 0.0, 0.0, 0.0};
+            for (int i = 0; i < per; i += 4) {
+                double t[4][4];
+#pragma unroll
+                for (int h = 0; h < 4; ++h)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int k = k0 + h * per + (i + u < per ? i + u : per - 1);
+                        t[h][u] = partial[(int64_t)(k < k1 ? k : k1 - 1) * d + c];
+                    }
+#pragma unroll
+                for (int h = 0; h < 4; ++h)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (i + u < per && k0 + h * per + i + u < k1) q[h] += t[h][u];  // uniform
+            }
+            return (q[0] + q[1]) + (q[2] + q[3]);
+        };
+#pragma unroll
+        for (int j = 0; j < kSlots; ++j) {
+            const int c = threadIdx.x + 256 * j;
+            x4[j] = c < d ? column(pd.cx0, pd.cx1, c) : 0.0;
+            y4[j] = c < d ? column(pd.cy0, pd.cy1, c) : 0.0;
         }
-        sx[c] = a;
-        sy[c] = b;
-        ssx += a * a;
-        ssy += b * b;
+        for (int c = threadIdx.x + 1024; c < d_pad; c += 256) {
+            sx[c] = c < d ? column(pd.cx0, pd.cx1, c) : 0.0;
+            sy[c] = c < d ? column(pd.cy0, pd.cy1, c) : 0.0;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < kSlots; ++j) {
+            const int c = threadIdx.x + 256 * j;
+            x4[j] = c < d_pad ? sx[c] : 0.0;
+            y4[j] = c < d_pad ? sy[c] : 0.0;
+        }
     }
-    ssx = block_sum(ssx, red);
-    ssy = block_sum(ssy, red);
+    auto columns = [&](auto f) {  // f(slot, c, x, y, v) of each column; f may set v
+#pragma unroll
+        for (int j = 0; j < kSlots; ++j) {
+            const int c0 = threadIdx.x + 256 * j;
+            if (256 * j >= nt) continue;
+            if (c0 < d_pad) f(j, c0, x4[j], y4[j], v4[j]);
+            for (int c = c0 + nt; c < d_pad; c += nt) f(j, c, sx[c], sy[c], vp[c]);
+        }
+    };
+    auto total = [&](const double (&x)[kSlots]) {  // over the slots of all threads; every thread gets it
+        __syncthreads();  // the previous total's readers are done with red
+#pragma unroll
+        for (int j = 0; j < kSlots; ++j) {
+            if (256 * j >= nt) continue;  // uniform: nt is a multiple of 256
+            double u = x[j];
+            for (int o = 32; o > 0; o >>= 1) u += __shfl_xor(u, o, 64);
+            if (lane == 0) red[wave + 4 * j] = u;
+        }
+        __syncthreads();
+        double u = 0.0;
+        for (int q = 0; q < nt / 64; ++q) u += red[q];
+        return u;
+    };
+    double a1[kSlots], a2[kSlots];
+    auto clear = [&](double (&x)[kSlots]) {
+#pragma unroll
+        for (int j = 0; j < kSlots; ++j) x[j] = 0.0;
+    };
+    clear(a1);
+    clear(a2);
+    columns([&](int j, int, double x, double y, double&) {
+        a1[j] += x * x;
+        a2[j] += y * y;
+    });
+    bad = __syncthreads_or(bad);
+    const double ssx = total(a1), ssy = total(a2);
     const double nx = sqrt(ssx), ny = sqrt(ssy);
     const double r_x = nx / (double)pd.n, r_y = ny / (double)pd.m;
     // mean directions and v = mu_x - mu_y (Eq. for u, before normalisation)
-    double vv = 0.0;
-    for (int c = threadIdx.x; c < d_pad; c += 256) {
-        const double mx = nx > 0.0 ? sx[c] / nx : 0.0;
-        const double my = ny > 0.0 ? sy[c] / ny : 0.0;
-        const double vc = mx - my;
-        vp[c] = vc;
-        vv += vc * vc;
-    }
-    vv = block_sum(vv, red);
+    clear(a1);
+    columns([&](int j, int, double x, double y, double& vc) {
+        const double mx = nx > 0.0 ? x / nx : 0.0;
+        const double my = ny > 0.0 ? y / ny : 0.0;
+        vc = mx - my;
+        a1[j] += vc * vc;
+    });
+    const double vv = total(a1);
     const int identity = (!align) || !(sqrt(vv) > 1e-12) || !(r_x > 0.0) || !(r_y > 0.0);
     // t = H s_x + s_y: the pooled total of Z = [X'; Y]
-    double w = 0.0;
-    for (int c = threadIdx.x; c < d_pad; c += 256) w += vp[c] * sx[c];
-    w = block_sum(w, red);
+    clear(a1);
+    columns([&](int j, int, double x, double, double& vc) { a1[j] += vc * x; });
+    const double w = total(a1);
     const double coef = identity ? 0.0 : 2.0 * w / vv;
-    double vt = 0.0;
-    for (int c = threadIdx.x; c < d_pad; c += 256) {
-        const double tc = (sx[c] - coef * vp[c]) + sy[c];
+    clear(a1);
+    columns([&](int j, int c, double x, double y, double& vc) {
+        const double tc = (x - coef * vc) + y;
+        if (c < nt) vp[c] = vc;
         tp[c] = tc;
         tq[c] = (float)tc;
-        vt += vp[c] * tc;
-        if (v32) v32[(int64_t)p * d_pad + c] = (float)vp[c];
-    }
-    vt = block_sum(vt, red);
+        a1[j] += vc * tc;
+        if (v32) v32[(int64_t)p * d_pad + c] = (float)vc;
+    });
+    const double vt = total(a1);
     if (threadIdx.x == 0) {
         const double dd = (double)d;
         const double fx = log_g(r_x, dd, gd), fy = log_g(r_y, dd, gd);
@@ -423,11 +512,17 @@ __global__ __launch_bounds__(256) void k_finalize(const PairDesc* __restrict__ p
 hipError_t launch_finalize(const PairDesc* pairs, int npairs, const double* partial,
                            const int32_t* chunk_bad, int d,
                            int d_pad, int align, int gd, double* sxy, PairState* st, double* v,
-                           double* t64, float* t32, PairCount* cnt, hbt_result* res,
+                           double* t64, float* t32, PairCount* cnt, hbt_result* res, uint32_t* ticket,
                            hipStream_t s, int p0, float* v32) {
     if (npairs <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_finalize, dim3(npairs), dim3(256), 0, s, pairs, partial, chunk_bad, d, d_pad, align,
-                       gd, sxy, st, v, t64, t32, cnt, res, p0, v32);
+    auto go = [&](auto kern, dim3 grid) {
+        hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, pairs, partial, chunk_bad, d, d_pad, align, gd, sxy, st, v, t64,
+                           t32, cnt, res, p0, v32, ticket);
+    };
+    if (npairs <= 8)
+        go(k_finalize<kFinSplit>, dim3((d_pad + kFinCols - 1) / kFinCols, npairs));
+    else
+        go(k_finalize<kFinPair>, dim3(npairs));
     return hipGetLastError();
 }
 
@@ -925,9 +1020,11 @@ template <typename Tin>
 __global__ __launch_bounds__(256) void k_reflect_out(const PairDesc* __restrict__ pair,
                                                      const PairState* __restrict__ st,
                                                      const double* __restrict__ v, int n, int d,
-                                                     Tin* X_out) {
+                                                     Tin* X_out, double* v_out) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int i = blockIdx.x * 4 + wave;
+    if (v_out && blockIdx.x == 0)
+        for (int c = threadIdx.x; c < d; c += 256) v_out[c] = v[c];
     if (i >= n) return;
     const Tin* x = (const Tin*)pair->X + (int64_t)i * d;
     Tin* y = X_out + (int64_t)i * d;
@@ -943,21 +1040,14 @@ __global__ __launch_bounds__(256) void k_reflect_out(const PairDesc* __restrict_
     for (int c = lane; c < d; c += 64) y[c] = (Tin)((double)x[c] - k * v[c]);
 }
 
-__global__ void k_copy_v(const double* v, int d, double* out) {
-    for (int c = threadIdx.x; c < d; c += blockDim.x) out[c] = v[c];
-}
-
 hipError_t launch_reflect_out(int input_dtype, const PairDesc* pair, const PairState* st,
                               const double* v, int n, int d, void* X_out, double* v_out,
                               hipStream_t s) {
     dim3 g((n + 3) / 4), b(256);
     if (input_dtype == HBT_IN_F64)
-        hipLaunchKernelGGL(k_reflect_out<double>, g, b, 0, s, pair, st, v, n, d, (double*)X_out);
+        hipLaunchKernelGGL(k_reflect_out<double>, g, b, 0, s, pair, st, v, n, d, (double*)X_out, v_out);
     else
-        hipLaunchKernelGGL(k_reflect_out<float>, g, b, 0, s, pair, st, v, n, d, (float*)X_out);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !v_out) return e;
-    hipLaunchKernelGGL(k_copy_v, dim3(1), dim3(256), 0, s, v, d, v_out);
+        hipLaunchKernelGGL(k_reflect_out<float>, g, b, 0, s, pair, st, v, n, d, (float*)X_out, v_out);
     return hipGetLastError();
 }
 

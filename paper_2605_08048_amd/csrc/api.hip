@@ -78,6 +78,12 @@ struct StageTimer {
     }
 };
 
+// Split keys (splits times padded pooled size) of a single pair's block above
+// which they are drawn on a second stream beside the alignment: the fork and
+// join (two events, two queues) cost about 30 us, the keys 0.5 us a million (50 x
+// 60, B = 999: 117 us a call with the fork, 86 without; 777 x 1333, B = 5003: 221
+// and 187; 3000 x 2000, B = 20,000: 47 us of splits, hidden).
+constexpr int64_t kForkKeys = (int64_t)1 << 26;
 constexpr int64_t kAutoBlock = 32768;  // splits per block when block_perms == 0
 
 int64_t round_up(int64_t x, int64_t k) { return (x + k - 1) / k * k; }
@@ -170,6 +176,7 @@ struct Workspace {
     int64_t* rplan;     // recheck work plan
     uint32_t* nflag;    // per pair: its recheck flags
     int32_t* sstat;     // per pair: problems of the split stage (merged into the result status)
+    uint32_t* ticket;   // per pair: the alignment's work-groups that have ended
     // point-to-centroid route
     float* sig;         // group sums of the smaller group, block rows x d_pad
     float* z32;         // row-major FP32 Z when the main storage is not FP32
@@ -187,6 +194,8 @@ struct Workspace {
     GemmGroup* rgroups; // tile table of the refinement product (one group per product group)
     int64_t* rtiles;    // its tile count
     unsigned char* blob; // description the device builds a batched call's tables from
+    int32_t* big_pair;   // the pairs of more than kQuadItems padded pooled items ...
+    int64_t* big_row0;   // ... and their split rows before each
     size_t bytes;
 };
 
@@ -291,6 +300,7 @@ Workspace carve(const Plan& P, void* ws) {
         w.rplan = c.take<int64_t>(recheck_plan_words(np));
         w.nflag = c.take<uint32_t>((size_t)(np + 1) / 2 * 2);
         w.sstat = c.take<int32_t>((size_t)(np + 1) / 2 * 2);
+        w.ticket = c.take<uint32_t>((size_t)(np + 1) / 2 * 2);
         if (P.route2) {
             w.sig = c.take<float>((size_t)std::max<int64_t>(P.block_rows, 1) * P.d_pad);
             w.z32 = P.precision == HBT_F32 ? nullptr : c.take<float>((size_t)P.zrows * P.d_pad);
@@ -346,6 +356,9 @@ Workspace carve(const Plan& P, void* ws) {
     // per pair at most 32 bytes (sizes or clouds, offset, splits, Philox word,
     // owner, order), per cloud 12, and the arrays' alignment
     w.blob = P.batched ? c.take<unsigned char>((size_t)np * 32 + P.cdesc.size() * 12 + 128) : nullptr;
+    w.big_pair = P.batched ? c.take<int32_t>(np) : nullptr;
+    w.big_row0 = P.batched ? c.take<int64_t>(np) : nullptr;
+    if (!P.need_store) w.ticket = c.take<uint32_t>(2);
     w.bytes = c.off + 256;
     return w;
 }
@@ -671,7 +684,8 @@ hbt_status enqueue_prologue(const Plan& P, const Workspace& w, int align, int gd
                             hipStream_t s, bool upload_pairs = true) {
     if (upload_pairs) {
         StageTimer t(HBT_STAGE_OTHER, s);
-        HIP_TRY(upload(w.pairs, P.pairs.data(), P.pairs.size() * sizeof(PairDesc), s));
+        HIP_TRY(upload(w.pairs, P.pairs.data(), P.pairs.size() * sizeof(PairDesc), s, w.ticket,
+                       (P.pairs.size() + 1) / 2 * 8));
     }
     StageTimer t(HBT_STAGE_ALIGN, s);
     if (vector_rows(P) && P.need_store)
@@ -685,7 +699,7 @@ hbt_status enqueue_prologue(const Plan& P, const Workspace& w, int align, int gd
         HIP_TRY(launch_colsum(P.input_dtype, w.pairs, P.npairs, (int)P.nchunks, P.d,
                               w.partial_sum, w.chunk_bad, s));
     HIP_TRY(launch_finalize(w.pairs, P.npairs, w.partial_sum, w.chunk_bad, P.d, P.d_pad, align, gd, w.sxy, w.st,
-                            w.v, w.t64, w.t32, w.cnt, res, s));
+                            w.v, w.t64, w.t32, w.cnt, res, w.ticket, s));
     return HBT_OK;
 }
 
@@ -760,6 +774,17 @@ int64_t recheck_slot_budget(int npairs, int d_pad) {
     const long long v = strtoll(e, &end, 10);
     if (end == e || v < 0) return held;
     return v < held ? (int64_t)v : held;
+}
+
+// The list of a batched call's larger pairs for the split stage.
+SplitBig split_big(const Plan& P, const Workspace& w) {
+    SplitBig b{w.big_pair, w.big_row0, 0, 0};
+    for (size_t p = 0; p < P.pairs.size(); ++p)
+        if (P.pairs[p].Np > kQuadItems) {
+            ++b.count;
+            b.rows += P.bp[p].nb;
+        }
+    return b;
 }
 
 // The tables of a batched call (one pipeline chunk) from its compact
@@ -860,6 +885,9 @@ hipError_t build_tables(const Plan& P, const Workspace& w, const char* base, con
     A.nflag = w.nflag;
     A.rcnt = w.rcnt;
     A.sstat = w.sstat;
+    A.ticket = w.ticket;
+    A.big_pair = w.big_pair;
+    A.big_row0 = w.big_row0;
     hipError_t e = upload(w.blob, blob.data(), blob.size(), s);
     return e != hipSuccess ? e : launch_build_tables(A, s);
 }
@@ -870,6 +898,8 @@ hbt_status batched_epilogue(const Plan& P, const Workspace& w, const hbt_perm_pa
                             hbt_result* results, hipStream_t s) {
     const int np = P.npairs;
     const int no_recheck = common->flags & HBT_FLAG_NO_RECHECK;
+    const PairEnd end{w.bp, w.st, w.sstat, w.tw, w.Btot, w.cnt, results};
+    bool ended = false;
     if (P.lazy) {
         // first pass: decide from the hi-plane sums what they can decide,
         // list the rest; second pass: split-BF16 sums of the listed splits
@@ -895,11 +925,13 @@ hbt_status batched_epilogue(const Plan& P, const Workspace& w, const hbt_perm_pa
         StageTimer t_(HBT_STAGE_RECHECK, s);
         HIP_TRY(launch_recheck(P.input_dtype, w.pairs, w.bp, np, w.st, w.v, w.t64, w.coef, w.mask, w.flags,
                                w.nflag, w.rplan, P.block_rows, P.max_np, w.rseg, recheck_slot_budget(np, P.d_pad),
-                               P.d, common->gd, common->alternative,
-                               w.cnt, w.tw, s));
+                               P.d, common->gd, common->alternative, w.cnt, w.tw, s, &end,
+                               np == 1 ? w.nflag + 1 : nullptr, &ended));
     }
-    { StageTimer t_(HBT_STAGE_OTHER, s); HIP_TRY(launch_moments(np, w.bp, w.st, w.tw, w.cnt, s)); }
-    { StageTimer t_(HBT_STAGE_OTHER, s); HIP_TRY(launch_final(np, w.bp, w.st, w.sstat, w.cnt, w.Btot, results, s)); }
+    if (!ended) {
+        StageTimer t_(HBT_STAGE_OTHER, s);
+        HIP_TRY(launch_pair_end(np, end, s));
+    }
     return HBT_OK;
 }
 
@@ -935,6 +967,7 @@ hbt_status batched_pipelined(const Plan& P, const Workspace& w, const hbt_perm_p
         HIP_TRY(upload(w.groups, P.groups.data(), P.groups.size() * sizeof(GemmGroup), s));
         HIP_TRY(upload(w.Btot, P.Btot.data(), P.Btot.size() * sizeof(int64_t), s));
         HIP_TRY(zero(w.nflag, (size_t)(np + 1) / 2 * 8, s));
+        HIP_TRY(zero(w.ticket, (size_t)(np + 1) / 2 * 8, s));
         if (P.lazy) HIP_TRY(zero(w.rcnt, (size_t)(np + 1) / 2 * 8, s));
     }
     HIP_TRY(ev.record(s, &e0));
@@ -948,7 +981,7 @@ hbt_status batched_pipelined(const Plan& P, const Workspace& w, const hbt_perm_p
         {
             StageTimer t_(HBT_STAGE_SPLIT, qs);
             HIP_TRY(launch_split_masks(w.bp, np, r1, P.min_np, P.max_np, common->seed, w.mask, w.sstat,
-                                       P.tune.split_cap, qs, r0, P.block_rows));
+                                       P.tune.split_cap, qs, SplitBig{}, r0, P.block_rows));
         }
         HIP_TRY(ev.record(qs, &es));
         {
@@ -957,7 +990,7 @@ hbt_status batched_pipelined(const Plan& P, const Workspace& w, const hbt_perm_p
                                             w.zstore, P.zrows * P.d_pad, w.z32, w.chunk_bad, s, c0));
             HIP_TRY(launch_finalize(w.pairs, c.pb - c.pa, w.partial_sum, w.chunk_bad, P.d, P.d_pad,
                                     common->align, common->gd, w.sxy, w.st, w.v, w.t64, w.t32, w.cnt,
-                                    results, s, c.pa));
+                                    results, w.ticket, s, c.pa));
             HIP_TRY(launch_reflect_vec(P.precision, w.pairs, np, o1, w.st, w.v, P.d, P.d_pad, w.coef,
                                        w.zstore, P.zrows * P.d_pad, nullptr, s, o0));
         }
@@ -1141,8 +1174,7 @@ hbt_status hbt_perm_test(const void* X, const void* Y, const hbt_perm_params* pr
         const GemmGroup grp{0, (int32_t)((nb + wdt - 1) / wdt), 0};
         hipError_t e;
         if ((e = upload(w.bp, &bq, sizeof bq, s)) != hipSuccess) return e;
-        if ((e = upload(w.groups, &grp, sizeof grp, s)) != hipSuccess) return e;
-        return zero(w.nflag, 8, s);
+        return upload(w.groups, &grp, sizeof grp, s, w.nflag, 8);  // the flag count and the ticket
     };
     auto block_splits = [&](int64_t b0, int64_t nb, hipStream_t q) -> hipError_t {
         if (prm->masks) return launch_copy_masks(prm->masks, b0, nb, N, (int)prm->n, pd.Wp, w.mask, w.sstat, q);
@@ -1152,8 +1184,9 @@ hbt_status hbt_perm_test(const void* X, const void* Y, const hbt_perm_params* pr
     {
         // The plan tables and block 0's tables sit next to each other at the
         // start of the workspace (pairs, bp, tiles, groups, Btot): one image,
-        // one upload.  The recheck counter and the split status are adjacent
-        // too: one fill.
+        // one upload.  The recheck counter (with a ticket behind it), the split
+        // status and the alignment's ticket are adjacent too: cleared by the
+        // same launch.
         StageTimer t_(HBT_STAGE_OTHER, s);
         const int64_t nb0 = std::min<int64_t>(B0, prm->B);
         const BlockPair bq = block_pair(0, 0, prm->perm_offset, nb0, 0, pd);
@@ -1168,17 +1201,21 @@ hbt_status hbt_perm_test(const void* X, const void* Y, const hbt_perm_params* pr
         put(w.tiles, P.tiles.data(), P.tiles.size() * sizeof(GemmTile));
         put(w.groups, &grp, sizeof grp);
         put(w.Btot, P.Btot.data(), sizeof(int64_t));
-        HIP_TRY(upload(w.pairs, img.data(), img.size(), s));
-        HIP_TRY(zero(w.nflag, (size_t)((const char*)(w.sstat + 2) - (const char*)w.nflag), s));
+        HIP_TRY(upload(w.pairs, img.data(), img.size(), s, w.nflag,
+                       (size_t)((const char*)(w.ticket + 2) - (const char*)w.nflag)));
     }
     // The first block's splits depend only on the seed and the sizes: they are
     // drawn on a second stream beside the alignment and joined before the
-    // group sums (as in the batched call); later blocks follow in order.
+    // group sums (as in the batched call); later blocks follow in order.  Few
+    // splits of a small pair go ahead of the alignment on the caller's stream:
+    // they take less time than the fork and join.
+    const int64_t nb0 = std::min<int64_t>(B0, prm->B);
+    const bool beside = nb0 * pd.Np > kForkKeys;
     Fork fork(s);
-    HIP_TRY(fork.begin());
+    if (beside) HIP_TRY(fork.begin());
     {
-        StageTimer t_(HBT_STAGE_SPLIT, fork.side);
-        HIP_TRY(block_splits(0, std::min<int64_t>(B0, prm->B), fork.side));
+        StageTimer t_(HBT_STAGE_SPLIT, beside ? fork.side : s);
+        HIP_TRY(block_splits(0, nb0, beside ? fork.side : s));
     }
     st = enqueue_prologue(P, w, prm->align, prm->gd, result, s, false);
     if (st) return st;
@@ -1191,7 +1228,7 @@ hbt_status hbt_perm_test(const void* X, const void* Y, const hbt_perm_params* pr
             HIP_TRY(launch_row_dot_t(w.pairs, 1, z32, w.t64, P.d_pad, P.zrows, w.zt, s));
         }
     }
-    HIP_TRY(fork.join());
+    if (beside) HIP_TRY(fork.join());
     for (int64_t b0 = 0; b0 < prm->B; b0 += B0) {
         const int64_t nb = std::min<int64_t>(B0, prm->B - b0);
         const int wdt = block_width(nb);
@@ -1223,6 +1260,8 @@ hbt_status hbt_perm_test(const void* X, const void* Y, const hbt_perm_params* pr
                                     z32, w.sig,
                                     w.mask, w.zt, w.partial2, P.block_rows, s));
         }
+        const PairEnd end{w.bp, w.st, w.sstat, w.tw, w.Btot, w.cnt, b0 + nb >= prm->B ? result : nullptr};
+        bool ended = false;
         void* T_blk = T_out ? (char*)T_out + b0 * t_size : nullptr;
         if (P.lazy) {
             // decide what the hi plane can, refine the rest with both planes
@@ -1248,13 +1287,15 @@ hbt_status hbt_perm_test(const void* X, const void* Y, const hbt_perm_params* pr
             StageTimer t_(HBT_STAGE_RECHECK, s);
             HIP_TRY(launch_recheck(P.input_dtype, w.pairs, w.bp, 1, w.st, w.v, w.t64, w.coef, w.mask,
                                    w.flags, w.nflag, w.rplan, nb, P.max_np, w.rseg, recheck_slot_budget(1, P.d_pad),
-                                   P.d, prm->gd, prm->alternative, w.cnt, w.tw, s));
+                                   P.d, prm->gd, prm->alternative, w.cnt, w.tw, s, &end, w.nflag + 1, &ended));
         }
-        { StageTimer t_(HBT_STAGE_OTHER, s); HIP_TRY(launch_moments(1, w.bp, w.st, w.tw, w.cnt, s)); }
+        if (!ended) {
+            StageTimer t_(HBT_STAGE_OTHER, s);
+            HIP_TRY(launch_pair_end(1, end, s));
+        }
         if (mask_out)
             HIP_TRY(launch_export_masks(w.mask, nb, pd.Wp, W, mask_out + b0 * W, s));
     }
-    { StageTimer t_(HBT_STAGE_OTHER, s); HIP_TRY(launch_final(1, w.bp, w.st, w.sstat, w.cnt, w.Btot, result, s)); }
     return HBT_OK;
 }
 
@@ -1474,7 +1515,7 @@ hbt_status hbt_perm_test_batched(int64_t npairs, const void* Z_all, const int64_
     {
         StageTimer t_(HBT_STAGE_SPLIT, qs);
         HIP_TRY(launch_split_masks(w.bp, np, P.block_rows, P.min_np, P.max_np, common->seed, w.mask, w.sstat,
-                                   P.tune.split_cap, qs));
+                                   P.tune.split_cap, qs, split_big(P, w)));
     }
     st = enqueue_prologue(P, w, common->align, common->gd, results, s, false);
     if (st) return st;
@@ -1702,7 +1743,7 @@ hbt_status hbt_perm_test_clouds(int64_t nclouds, const void* Z_all, const int64_
     {
         StageTimer t_(HBT_STAGE_SPLIT, qs);
         HIP_TRY(launch_split_masks(w.bp, np, P.block_rows, P.min_np, P.max_np, common->seed, w.mask, w.sstat,
-                                   P.tune.split_cap, qs));
+                                   P.tune.split_cap, qs, split_big(P, w)));
     }
     {
         // every cloud summed and stored once; per pair the directions, v, T_obs
@@ -1712,7 +1753,7 @@ hbt_status hbt_perm_test_clouds(int64_t nclouds, const void* Z_all, const int64_
                                         P.d_pad, w.partial_sum, w.zstore, P.zrows * P.d_pad, nullptr,
                                         w.chunk_bad, s));
         HIP_TRY(launch_finalize(w.pairs, np, w.partial_sum, w.chunk_bad, P.d, P.d_pad, common->align, common->gd,
-                                w.sxy, w.st, w.v, w.t64, w.t32, w.cnt, results, s, 0, w.v32));
+                                w.sxy, w.st, w.v, w.t64, w.t32, w.cnt, results, w.ticket, s, 0, w.v32));
         HIP_TRY(launch_fold_coef(w.pairs, np, w.st, w.v, P.d, P.d_pad, P.ncoef, w.coef, s));
     }
     HIP_TRY(ev.record(qs, &e0));

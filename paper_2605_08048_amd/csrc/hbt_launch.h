@@ -12,8 +12,10 @@ namespace hbt {
 
 // Copy `bytes` (<= 3072 per launch, split internally) of host data into
 // device memory through kernel arguments: stream-ordered, no host buffer
-// outlives the call, capturable in a graph.
-hipError_t upload(void* dst, const void* src, size_t bytes, hipStream_t s);
+// outlives the call, capturable in a graph.  clear_bytes (a multiple of 8) at
+// `clear` are zeroed by the first launch.
+hipError_t upload(void* dst, const void* src, size_t bytes, hipStream_t s, void* clear = nullptr,
+                  size_t clear_bytes = 0);
 
 // Zero `bytes` (a multiple of 8) of device memory with a fill kernel.
 hipError_t zero(void* dst, size_t bytes, hipStream_t s);
@@ -47,6 +49,9 @@ struct TableArgs {
     uint32_t* nflag;  // cleared, as are rcnt (nullable) and sstat
     uint32_t* rcnt;
     int32_t* sstat;
+    uint32_t* ticket; // cleared too
+    int32_t* big_pair;  // the pairs of more than kQuadItems padded pooled items, in order
+    int64_t* big_row0;  // ... and their split rows before each
 };
 hipError_t launch_build_tables(const TableArgs& A, hipStream_t s);
 
@@ -62,6 +67,7 @@ hipError_t launch_finalize(const PairDesc* pairs, int npairs, const double* part
                            const int32_t* chunk_bad, int d,
                            int d_pad, int align, int gd, double* sxy, PairState* st, double* v,
                            double* t64, float* t32, PairCount* cnt, hbt_result* res,
+                           uint32_t* ticket,  // a zeroed word per pair (used for up to 8 pairs)
                            hipStream_t s, int p0 = 0,  // pairs [p0, p0 + npairs)
                            float* v32 = nullptr);      // FP32 copy of v (d_pad per pair), nullable
 // coef[coef0 + i] = 2 (v . x_i) / (v . v) (0 when H = I) for the X rows of
@@ -110,9 +116,18 @@ size_t split_lds_limit();
 // only the block table (bp): sizes, mask row width and pair index are copied
 // there, and rows of pairs that share another pair's splits are skipped.
 constexpr int kSplitWgPerCuBesideAlign = 6;
+// Pairs of up to kQuadItems padded pooled items are drawn four rows a wave.  A
+// call with both kinds of pairs lists the larger ones (pair nullptr: no list).
+constexpr int kQuadItems = 2048;
+struct SplitBig {
+    const int32_t* pair = nullptr;
+    const int64_t* row0 = nullptr;  // split rows of the listed pairs before each
+    int count = 0;
+    int64_t rows = 0;               // of all listed pairs
+};
 hipError_t launch_split_masks(const BlockPair* bp, int npairs,
                               int64_t rows, int min_np, int max_np, uint64_t seed, uint32_t* mask,
-                              int32_t* sstat, int wg_per_cu, hipStream_t s,
+                              int32_t* sstat, int wg_per_cu, hipStream_t s, SplitBig big = {},
                               int64_t row0 = 0,  // split rows [row0, rows) ...
                               int64_t total_rows = 0);  // ... of this many in the table (0: rows)
 // Explicit masks: copy rows of ceil(N/32) words into the workspace layout and
@@ -224,15 +239,30 @@ constexpr int kRecheckSlotsSingle = 2048;
 inline int64_t recheck_plan_words(int npairs) { return 4 * ((int64_t)npairs + 1); }
 int recheck_segments(int max_np);
 int64_t recheck_slots(int npairs, int d_pad);
+// What ends a call for a pair: null moments of the block's splits (Tw holds
+// their final T_b), and after the last block (res non-null) the result record:
+// count, B, p, null moments and status (the alignment's, else that of the split
+// rows that drew its masks).
+struct PairEnd {
+    const BlockPair* bp;
+    const PairState* st;
+    const int32_t* sstat;
+    const double* Tw;
+    const int64_t* Btot;
+    PairCount* cnt;
+    hbt_result* res;
+};
+// One pair (npairs = 1): no plan is made (its one flag count gives the work),
+// and where a second kernel finishes segmented flags, its last work-group to end
+// also ends the pair (`end`; ticket: a zeroed word); *ended says whether it did.
 hipError_t launch_recheck(int input_dtype, const PairDesc* pairs, const BlockPair* bp, int npairs,
                           const PairState* st, const double* v, const double* t64, const double* coef,
                           const uint32_t* mask, const uint32_t* flags, const uint32_t* nflag, int64_t* plan,
                           int64_t max_flags, int max_np, double* rseg, int64_t slots, int d, int gd,
-                          int alternative, PairCount* cnt, double* Tw, hipStream_t s);
-// Sums of T_b - T_obs and its square per pair over the current block (Tw
-// holds the block's final T_b, recheck applied).
-hipError_t launch_moments(int npairs, const BlockPair* bp, const PairState* st, const double* Tw,
-                          PairCount* cnt, hipStream_t s);
+                          int alternative, PairCount* cnt, double* Tw, hipStream_t s,
+                          const PairEnd* end = nullptr, uint32_t* ticket = nullptr, bool* ended = nullptr);
+// Ends every pair.
+hipError_t launch_pair_end(int npairs, const PairEnd& end, hipStream_t s);
 // --- permutation-budget allocator ---------------------------------------
 size_t mlp_train_ws_bytes(int64_t rows);
 hipError_t launch_features(int64_t npairs, const hbt_result* res, int d, int gd, float* feat,
@@ -251,10 +281,5 @@ hipError_t launch_budgets(int64_t npairs, const float* out, const hbt_result* re
                           hipStream_t s);
 hipError_t launch_budgets_cost(int64_t npairs, const float* out, const hbt_result* res, double lo,
                                double hi, int64_t bmin, int64_t bmax, int64_t* budget, hipStream_t s);
-
-// Per pair: count, B, p, null moments and status (the alignment's, else that
-// of the split rows that drew its masks).
-hipError_t launch_final(int npairs, const BlockPair* bp, const PairState* st, const int32_t* sstat,
-                        const PairCount* cnt, const int64_t* Btot, hbt_result* res, hipStream_t s);
 
 }  // namespace hbt

@@ -112,16 +112,21 @@ __device__ __forceinline__ uint32_t equal_theta(uint4 w, uint32_t theta4) {
     });
 }
 
-// Pair of a split row.  Pairs of one batch mostly have equally many rows, so
-// the pair at the row's place in proportion (pairs_per_row = npairs / rows) is
-// looked at first: one load instead of a search of log2(npairs) loads, each
-// waiting for the one before (half the time of a wave that drew one split).
+// The entry of a table, of `count` runs of rows, that holds a row.  Pairs of one
+// batch mostly have equally many rows, so the entry at the row's place in
+// proportion (per_row = count / rows) is looked at first: one load instead of a
+// search of log2(count) loads, each waiting for the one before.
+template <typename First, typename Len>
+__device__ __forceinline__ int place_of_row(int count, int64_t row, double per_row, First first, Len len) {
+    int p = (int)(((double)row + 0.5) * per_row);
+    p = __builtin_amdgcn_readfirstlane(p < count ? p : count - 1);
+    const int64_t r0 = first(p);
+    if (r0 <= row && row < r0 + len(p)) return p;
+    return upper_index(count, row, first);
+}
 __device__ __forceinline__ int pair_of_row(const BlockPair* bp, int npairs, int64_t row, double pairs_per_row) {
-    int p = (int)(((double)row + 0.5) * pairs_per_row);
-    p = __builtin_amdgcn_readfirstlane(p < npairs ? p : npairs - 1);
-    const int64_t r0 = bp[p].mrow0;
-    if (r0 <= row && row < r0 + bp[p].nb) return p;
-    return upper_index(npairs, row, [&](int k) { return bp[k].mrow0; });
+    return place_of_row(npairs, row, pairs_per_row, [&](int k) { return bp[k].mrow0; },
+                        [&](int k) { return (int64_t)bp[k].nb; });
 }
 
 // A finished mask row from LDS to memory.
@@ -172,9 +177,7 @@ __device__ __forceinline__ void split_row(const BlockPair& pd, int p, int64_t ro
                                           uint32_t key1, uint32_t* __restrict__ mask, int32_t* sstat,
                                           uint32_t (*hist_all)[256], uint32_t* nlist, unsigned char* smem) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int lane = threadIdx.x & 63, N = pd.n + pd.m;
-    // nothing of a row stays in registers across the caller's loop
-    asm volatile("" : "+v"(lane), "+s"(N));
+    const int lane = threadIdx.x & 63, N = pd.n + pd.m;
     const SplitLds L(max_np);
     unsigned char* base = smem + wave * L.total;
     uint32_t* hist = hist_all[wave];
@@ -340,33 +343,38 @@ __device__ __forceinline__ void split_row(const BlockPair& pd, int p, int64_t ro
     write_mask_row(const_cast<uint32_t*>(mask_row(mask, pd, row, pd.Wp)), mlds, pd);
 }
 
-// Wave g takes the rows rows_wave g .. of the pairs of more than skip_wp mask
-// words a row (the others are k_split_quads'); rows_wave > 1 where the rows are
-// many: a quarter of the waves to start and to find their pair.
+// Wave g draws the g-th of the rows [row0, rows): of all pairs, or of the nbig
+// pairs listed in big_pair (their rows before each in big_row0), the pairs of
+// more than skip_wp mask words a row in a call that also has smaller ones
+// (without the list, as in a pipelined call, the wave of a smaller pair's row
+// returns).
 template <int R>
 __global__ __launch_bounds__(64 * kSplitWaves) void k_split_masks(const BlockPair* __restrict__ bp, int npairs,
                                                                   int64_t rows, int max_np, uint32_t key0,
                                                                   uint32_t key1, uint32_t* __restrict__ mask,
                                                                   int32_t* sstat, int64_t row0, int skip_wp,
-                                                                  double pairs_per_row, int rows_wave) {
+                                                                  double pairs_per_row,
+                                                                  const int32_t* __restrict__ big_pair,
+                                                                  const int64_t* __restrict__ big_row0, int nbig) {
     __shared__ uint32_t hist_all[kSplitWaves][256];
     __shared__ uint32_t nlist_all[kSplitWaves];
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int64_t row = ((int64_t)blockIdx.x * kSplitWaves + wave) * rows_wave + row0;
-    const int64_t end = row + rows_wave < rows ? row + rows_wave : rows;
-    while (row < end) {
-        const int p = pair_of_row(bp, npairs, row, pairs_per_row);
-        const BlockPair pd = bp[p];  // the pair's sizes, mask row width and index (not a PairDesc)
-        const int64_t pend = pd.mrow0 + pd.nb < end ? pd.mrow0 + pd.nb : end;
-        // else another pair's rows, or the other kernel, draw these masks (wave-uniform)
-        if (pd.owner == p && pd.Wp > skip_wp)
-            for (; row < pend; ++row) {
-                split_row<R>(pd, p, row, max_np, key0, key1, mask, sstat, hist_all, &nlist_all[wave], smem);
-                wave_sync();
-            }
-        row = pend;
+    int64_t row = (int64_t)blockIdx.x * kSplitWaves + wave + row0;
+    if (row >= rows) return;
+    int p;
+    if (big_pair) {
+        const int k = place_of_row(nbig, row, pairs_per_row, [&](int q) { return big_row0[q]; },
+                                   [&](int q) { return (int64_t)bp[big_pair[q]].nb; });
+        p = big_pair[k];
+        row += bp[p].mrow0 - big_row0[k];
+    } else {
+        p = pair_of_row(bp, npairs, row, pairs_per_row);
     }
+    const BlockPair pd = bp[p];  // the pair's sizes, mask row width and index (not a PairDesc)
+    // another pair's rows, or the other kernel, draw these masks (wave-uniform)
+    if (pd.owner != p || pd.Wp <= skip_wp) return;
+    split_row<R>(pd, p, row, max_np, key0, key1, mask, sstat, hist_all, &nlist_all[wave], smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -565,14 +573,18 @@ __device__ __forceinline__ void split_rows(const BlockPair& pd, int p, int64_t r
 
 // Wave g takes the split rows 4 g .. 4 g + 3, those of one pair together; rows
 // of pairs of more than 16 K blocks are left to k_split_masks.
+// At most 64 registers: with six of its work-groups on a CU (wg_per_cu), a wave
+// of the column sums (112 registers) still fits each SIMD.  The mask rows' LDS is
+// dynamic for the compiler's count of resident waves.
 template <int K>
-__global__ __launch_bounds__(64 * kSplitWaves) void k_split_quads(const BlockPair* __restrict__ bp, int npairs,
+__global__ __launch_bounds__(64 * kSplitWaves, 8) void k_split_quads(const BlockPair* __restrict__ bp, int npairs,
                                                                   int64_t rows, uint32_t key0, uint32_t key1,
                                                                   uint32_t* __restrict__ mask, int32_t* sstat,
                                                                   int64_t row0, double pairs_per_row) {
     __shared__ __attribute__((aligned(1024))) uint32_t hist_all[kSplitWaves][kQuad][256];
     __shared__ uint4 meta_all[kSplitWaves][kQuad];
-    __shared__ uint32_t mlds_all[kSplitWaves][kQuad * 8 * K];
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    uint32_t(*mlds_all)[kQuad * 8 * K] = (uint32_t(*)[kQuad * 8 * K])smem;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int64_t row = ((int64_t)blockIdx.x * kSplitWaves + wave) * kQuad + row0;
     const int64_t end = row + kQuad < rows ? row + kQuad : rows;
@@ -616,15 +628,16 @@ size_t split_lds_limit() {
     return lim;
 }
 
-// Rounds of the four-row kernel and the pooled items it takes.
+// Rounds of the four-row kernel.
 constexpr int kQuadRounds = 8, kQuadRoundsSmall = 4;
-constexpr int kQuadItems = 256 * kQuadRounds;
+static_assert(kQuadItems == 256 * kQuadRounds, "16 blocks of 16 items a round");
 
 size_t split_lds_per_block(int max_np) { return (size_t)kSplitWaves * SplitLds(max_np).total + kSplitStaticLds; }
 
 hipError_t launch_split_masks(const BlockPair* bp, int npairs,
                               int64_t rows, int min_np, int max_np, uint64_t seed, uint32_t* mask,
-                              int32_t* sstat, int wg_per_cu, hipStream_t s, int64_t row0, int64_t total_rows) {
+                              int32_t* sstat, int wg_per_cu, hipStream_t s, SplitBig big, int64_t row0,
+                              int64_t total_rows) {
     if (rows <= row0) return hipSuccess;
     if (total_rows < rows) total_rows = rows;
     const size_t share = wg_per_cu > 0 ? lds_per_cu() / (size_t)wg_per_cu : 0;
@@ -635,8 +648,8 @@ hipError_t launch_split_masks(const BlockPair* bp, int npairs,
         const int64_t per_wg = (int64_t)kSplitWaves * kQuad;
         const dim3 grid((unsigned)((rows - row0 + per_wg - 1) / per_wg));
         auto go = [&](auto kern, int K) {
-            const size_t own = (size_t)kSplitWaves * kQuad * (1024 + 16 + 32 * K);
-            hipLaunchKernelGGL(kern, grid, block, share > own ? share - own : 0, s, bp, npairs, rows, k0, k1, mask,
+            const size_t fixed = (size_t)kSplitWaves * kQuad * (1024 + 16), rows_lds = (size_t)kSplitWaves * kQuad * 32 * K;
+            hipLaunchKernelGGL(kern, grid, block, share > fixed + rows_lds ? share - fixed : rows_lds, s, bp, npairs, rows, k0, k1, mask,
                                sstat, row0, ppr);
         };
         if (max_np <= 256 * kQuadRoundsSmall) go(k_split_quads<kQuadRoundsSmall>, kQuadRoundsSmall);
@@ -648,15 +661,21 @@ hipError_t launch_split_masks(const BlockPair* bp, int npairs,
     size_t lds = (size_t)kSplitWaves * L.total;
     if (share > lds + kSplitStaticLds) lds = share - kSplitStaticLds;
     if (lds + kSplitStaticLds > 65536 || lds + kSplitStaticLds > split_lds_limit()) return hipErrorInvalidValue;
-    const int rows_wave = rows - row0 >= 32768 ? 4 : 1;
-    const int64_t per_wg = (int64_t)kSplitWaves * rows_wave;
-    const dim3 grid((unsigned)((rows - row0 + per_wg - 1) / per_wg));
     const int skip_wp = min_np <= kQuadItems ? kQuadItems / 32 : 0;
+    if (!skip_wp) big = SplitBig{};
+    double per_row = ppr;
+    if (big.pair) {
+        if (big.rows < 1) return hipErrorInvalidValue;
+        per_row = (double)big.count / (double)big.rows;
+        rows = big.rows;
+        row0 = 0;
+    }
+    const dim3 grid((unsigned)((rows - row0 + kSplitWaves - 1) / kSplitWaves));
     // registers for the keys of the largest pair: R blocks of 16 per lane
     const int r = (max_np + 1023) / 1024;
 #define HBT_SPLIT(RR)                                                                                             \
     hipLaunchKernelGGL(k_split_masks<RR>, grid, block, lds, s, bp, npairs, rows, max_np, k0, k1, mask, sstat, row0, \
-                       skip_wp, ppr, rows_wave)
+                       skip_wp, per_row, big.pair, big.row0, big.count)
     if (r <= 4) HBT_SPLIT(4);
     else if (r <= 8) HBT_SPLIT(8);
     else if (r <= 12) HBT_SPLIT(12);

@@ -352,16 +352,15 @@ __device__ __forceinline__ int64_t block_scan(int64_t x, int64_t* sh, int64_t* t
     return r;
 }
 
-// NT threads: 64 for calls of at most 64 pairs (a single pair), else 1024
-template <int NT>
-__global__ __launch_bounds__(NT) void k_recheck_plan(const PairDesc* __restrict__ pairs, int npairs,
+constexpr int kPlanThreads = 1024;
+__global__ __launch_bounds__(kPlanThreads) void k_recheck_plan(const PairDesc* __restrict__ pairs, int npairs,
                                                      const uint32_t* __restrict__ nflag, int64_t slots,
                                                      int64_t* __restrict__ plan) {
-    __shared__ int64_t sh[NT];
+    __shared__ int64_t sh[kPlanThreads];
     const int t = threadIdx.x;
     const int np1 = npairs + 1;
     int64_t bw = 0, bs = 0, bc = 0, bf = 0;
-    for (int p0 = 0; p0 < npairs; p0 += NT) {
+    for (int p0 = 0; p0 < npairs; p0 += kPlanThreads) {
         const int p = p0 + t;
         int64_t F = 0, G = 0;
         if (p < npairs) {
@@ -370,12 +369,12 @@ __global__ __launch_bounds__(NT) void k_recheck_plan(const PairDesc* __restrict_
         }
         const int64_t cand = (G > 1 && F > 0) ? F * G : 0;
         int64_t tc, tw, ts, tf;
-        const int64_t ic = block_scan<NT>(cand, sh, &tc);
+        const int64_t ic = block_scan<kPlanThreads>(cand, sh, &tc);
         const bool seg = cand > 0 && bc + ic <= slots;
         const int64_t wi = seg ? 0 : F, si = seg ? F * G : 0, fi = seg ? F : 0;
-        const int64_t iw = block_scan<NT>(wi, sh, &tw);
-        const int64_t is = block_scan<NT>(si, sh, &ts);
-        const int64_t jf = block_scan<NT>(fi, sh, &tf);
+        const int64_t iw = block_scan<kPlanThreads>(wi, sh, &tw);
+        const int64_t is = block_scan<kPlanThreads>(si, sh, &ts);
+        const int64_t jf = block_scan<kPlanThreads>(fi, sh, &tf);
         if (p < npairs) {
             plan[p] = bw + iw - wi;
             plan[np1 + p] = bs + is - si;
@@ -406,7 +405,8 @@ struct RecheckArgs {
     const uint32_t* mask;
     const uint32_t* flags;
     const uint32_t* nflag;
-    const int64_t* plan;
+    const int64_t* plan;  // nullptr: one pair
+    int64_t slots;
     int d, d_pad, gd, alternative;
     double* rseg;
     PairCount* cnt;
@@ -436,7 +436,7 @@ __device__ void recheck_item(const RecheckArgs& A, int p, int64_t j, int sg0, in
     const double* vp = A.v + (int64_t)p * A.d_pad;
     const double* tp = A.t64 + (int64_t)p * A.d_pad;
     const double* cf = A.coef + pd.coef0;
-    const int64_t slot = whole ? 0 : A.plan[2 * (A.npairs + 1) + p] + j * G;
+    const int64_t slot = whole ? 0 : (A.plan ? A.plan[2 * (A.npairs + 1) + p] : 0) + j * G;
     const int64_t row = A.flags[bq.mrow0 + j];
     const uint32_t* mk = mask_row(A.mask, bq, row, pd.Wp);
     double ssS = 0.0, ssL = 0.0;
@@ -528,10 +528,25 @@ __device__ void recheck_item(const RecheckArgs& A, int p, int64_t j, int sg0, in
     }
 }
 
+// Whether the flags of a call's only pair are segmented items (the plan's rule).
+__device__ __forceinline__ bool one_pair_segmented(int64_t F, int G, int64_t slots) {
+    return G > 1 && F * G <= slots;
+}
+
 template <typename Tin>
 __global__ __launch_bounds__(kRecheckThreads) void k_recheck(RecheckArgs A) {
     __shared__ double part[kRecheckWaves][kRecheckPass];  // per-wave sums of a segment
     __shared__ double red[kRecheckWaves];
+    if (!A.plan) {  // one pair
+        const int64_t F = A.nflag[0];
+        const int G = pair_segs(A.pairs[0]);
+        const bool seg = one_pair_segmented(F, G, A.slots);
+        for (int64_t it = blockIdx.x; it < (seg ? F * G : F); it += gridDim.x) {
+            const int sg = seg ? (int)(it % G) : 0;
+            recheck_item<Tin>(A, 0, seg ? it / G : it, sg, seg ? sg + 1 : G, !seg, part, red);
+        }
+        return;
+    }
     const int np1 = A.npairs + 1;
     const int64_t* wpre = A.plan;
     const int64_t* spre = A.plan + np1;
@@ -551,38 +566,128 @@ __global__ __launch_bounds__(kRecheckThreads) void k_recheck(RecheckArgs A) {
     }
 }
 
+// The null moments of pair p's block, sums of T_b - T_obs and its square in a
+// fixed order (thread t takes splits t, t + 256, ..., eight loads in flight; then
+// a tree), added to the blocks before; then its record (eq:pvalue), if this is
+// the last block.  256 threads.
+__device__ __forceinline__ void end_pair(const PairEnd& E, int p, double* r1, double* r2) {
+    const BlockPair q = E.bp[p];
+    const double c = E.st[p].t_obs;
+    const int t = threadIdx.x;
+    double a = 0.0, b = 0.0;
+    for (int64_t k = t; k < q.nb; k += 8 * 256) {
+        double x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = E.Tw[q.mrow0 + (k + 256 * u < q.nb ? k + 256 * u : k)] - c;
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (k + 256 * u < q.nb) {
+                a += x[u];
+                b += x[u] * x[u];
+            }
+    }
+    r1[t] = a;
+    r2[t] = b;
+    __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+        if (t < o) {
+            r1[t] += r1[t + o];
+            r2[t] += r2[t + o];
+        }
+        __syncthreads();
+    }
+    if (t != 0) return;
+    PairCount k = E.cnt[p];
+    k.sum_dt += r1[0];
+    k.sum_dt2 += r2[0];
+    if (!E.res) {
+        E.cnt[p].sum_dt = k.sum_dt;
+        E.cnt[p].sum_dt2 = k.sum_dt2;
+        return;
+    }
+    const PairState st = E.st[p];
+    hbt_result r = E.res[p];
+    r.count = (int64_t)k.count;
+    r.n_recheck = (int64_t)k.n_recheck;
+    r.B = E.Btot[p];
+    r.p = (1.0 + (double)r.count) / ((double)r.B + 1.0);
+    const double mean = k.sum_dt / (double)r.B;
+    const double var = k.sum_dt2 / (double)r.B - mean * mean;
+    r.t_mean = st.t_obs + mean;
+    r.t_sd = var != var ? var : sqrt(var > 0.0 ? var : 0.0);
+    r.status = st.status != HBT_OK ? st.status : E.sstat[q.owner];  // the alignment's status first
+    E.res[p] = r;
+}
+
+__global__ __launch_bounds__(256) void k_pair_end(PairEnd E) {
+    __shared__ double r1[256], r2[256];
+    end_pair(E, blockIdx.x, r1, r2);
+}
+
+hipError_t launch_pair_end(int npairs, const PairEnd& end, hipStream_t s) {
+    hipLaunchKernelGGL(k_pair_end, dim3(npairs), dim3(256), 0, s, end);
+    return hipGetLastError();
+}
+
 // The segmented flags: sigma_small from the segment sums in segment order,
 // then the same squares, statistic and decision as a whole item.
+__device__ __forceinline__ void finish_flag(const RecheckArgs& A, int p, int64_t j, int64_t slot0, double* red) {
+    const int t = threadIdx.x, d = A.d;
+    const PairDesc pd = A.pairs[p];
+    const int G = pair_segs(pd);
+    const int64_t row = A.flags[A.bp[p].mrow0 + j];
+    const double* src = A.rseg + (slot0 + j * G) * A.d_pad;
+    const double* tp = A.t64 + (int64_t)p * A.d_pad;
+    double ssS = 0.0, ssL = 0.0;
+    for (int c0 = 0; c0 < d; c0 += kRecheckPass)
+#pragma unroll
+        for (int k = 0; k < kRecheckCols; ++k) {
+            const int cc = t + kRecheckThreads * k;
+            const int col = c0 + cc;
+            if (col < d) {
+                double sm = 0.0;
+                for (int sg = 0; sg < G; ++sg) sm += src[(int64_t)sg * A.d_pad + col];
+                add_squares(sm, tp[col], ssS, ssL);
+            }
+        }
+    const double s1 = block_sum(ssS, red), s2 = block_sum(ssL, red);
+    if (t == 0) recheck_decide(pd, A.st[p], p, row, s1, s2, d, A.gd, A.alternative, A.cnt, A.Tw);
+}
+
 __global__ __launch_bounds__(kRecheckThreads) void k_recheck_finish(RecheckArgs A) {
     __shared__ double red[kRecheckWaves];
     const int np1 = A.npairs + 1;
     const int64_t* spl = A.plan + 2 * np1;
     const int64_t* fpre = A.plan + 3 * np1;
     const int64_t NF = fpre[A.npairs];
-    const int t = threadIdx.x, d = A.d;
     for (int64_t qf = blockIdx.x; qf < NF; qf += gridDim.x) {
         const int p = upper_index(A.npairs, qf, [&](int k) { return fpre[k]; });
-        const int64_t j = qf - fpre[p];
-        const PairDesc pd = A.pairs[p];
-        const int G = pair_segs(pd);
-        const int64_t row = A.flags[A.bp[p].mrow0 + j];
-        const double* src = A.rseg + (spl[p] + j * G) * A.d_pad;
-        const double* tp = A.t64 + (int64_t)p * A.d_pad;
-        double ssS = 0.0, ssL = 0.0;
-        for (int c0 = 0; c0 < d; c0 += kRecheckPass)
-#pragma unroll
-            for (int k = 0; k < kRecheckCols; ++k) {
-                const int cc = t + kRecheckThreads * k;
-                const int col = c0 + cc;
-                if (col < d) {
-                    double sm = 0.0;
-                    for (int sg = 0; sg < G; ++sg) sm += src[(int64_t)sg * A.d_pad + col];
-                    add_squares(sm, tp[col], ssS, ssL);
-                }
-            }
-        const double s1 = block_sum(ssS, red), s2 = block_sum(ssL, red);
-        if (t == 0) recheck_decide(pd, A.st[p], p, row, s1, s2, d, A.gd, A.alternative, A.cnt, A.Tw);
+        finish_flag(A, p, qf - fpre[p], spl[p], red);
     }
+}
+
+// One pair: its segmented flags, then the end of the pair by the last of the
+// work-groups that had any (by the first when there were none): they count
+// themselves on `ticket`, each after its own results are visible to the whole
+// device.  Nobody waits for anybody.
+__global__ __launch_bounds__(kRecheckThreads) void k_recheck_finish_end(RecheckArgs A, PairEnd E, uint32_t* ticket) {
+    static_assert(kRecheckThreads == 256, "end_pair takes 256 threads");
+    __shared__ double red[kRecheckWaves];
+    __shared__ double r1[256], r2[256];
+    __shared__ uint32_t before;
+    const int64_t F = A.nflag[0];
+    const int64_t NF = one_pair_segmented(F, pair_segs(A.pairs[0]), A.slots) ? F : 0;
+    const int64_t busy = NF < 1 ? 1 : NF < (int64_t)gridDim.x ? NF : (int64_t)gridDim.x;
+    if (blockIdx.x >= busy) return;
+    for (int64_t j = blockIdx.x; j < NF; j += gridDim.x) finish_flag(A, 0, j, 0, red);
+    if (busy > 1) {
+        __syncthreads();  // thread 0 decided the last flag
+        if (threadIdx.x == 0)
+            before = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (before != (uint32_t)(busy - 1)) return;
+    }
+    end_pair(E, 0, r1, r2);
 }
 
 int recheck_segments(int max_np) { return ((max_np + 31) / 32 + kSegWords - 1) / kSegWords; }
@@ -598,23 +703,23 @@ hipError_t launch_recheck(int input_dtype, const PairDesc* pairs, const BlockPai
                           const PairState* st, const double* v, const double* t64, const double* coef,
                           const uint32_t* mask, const uint32_t* flags, const uint32_t* nflag, int64_t* plan,
                           int64_t max_flags, int max_np, double* rseg, int64_t slots, int d, int gd,
-                          int alternative, PairCount* cnt, double* Tw, hipStream_t s) {
+                          int alternative, PairCount* cnt, double* Tw, hipStream_t s, const PairEnd* end,
+                          uint32_t* ticket, bool* ended) {
     if (max_flags <= 0) return hipSuccess;
     if (!plan || npairs < 1) return hipErrorInvalidValue;
+    if (ended) *ended = false;
     const int d_pad = (d + kDPad - 1) / kDPad * kDPad;
-    if (npairs <= 64)
-        hipLaunchKernelGGL(k_recheck_plan<64>, dim3(1), dim3(64), 0, s, pairs, npairs, nflag,
-                           rseg ? slots : (int64_t)0, plan);
-    else
-        hipLaunchKernelGGL(k_recheck_plan<1024>, dim3(1), dim3(1024), 0, s, pairs, npairs, nflag,
-                           rseg ? slots : (int64_t)0, plan);
-    const RecheckArgs A{pairs, bp, npairs, st, v, t64, coef, mask, flags, nflag, plan,
+    if (!rseg) slots = 0;
+    const bool one = npairs == 1;
+    if (!one)
+        hipLaunchKernelGGL(k_recheck_plan, dim3(1), dim3(kPlanThreads), 0, s, pairs, npairs, nflag, slots, plan);
+    const RecheckArgs A{pairs, bp, npairs, st, v, t64, coef, mask, flags, nflag, one ? nullptr : plan, slots,
                         d, d_pad, gd, alternative, rseg, cnt, Tw};
     // the item count is known on the device only: a grid for the largest
     // count, whose work-groups without an item return at once (a single
-    // pair, whose flags are few, gets at most 1024; the work-groups loop over
-    // the items when there are more)
-    const int64_t gmax_grid = npairs == 1 ? 1024 : 4096;
+    // pair, whose flags are few, gets the 512 that are resident together; the
+    // work-groups loop over the items when there are more)
+    const int64_t gmax_grid = one ? 512 : 4096;
     const int64_t want = max_flags * (int64_t)recheck_segments(max_np);
     const unsigned g = (unsigned)(want < gmax_grid ? want : gmax_grid);
     if (input_dtype == HBT_IN_F64)
@@ -625,78 +730,14 @@ hipError_t launch_recheck(int input_dtype, const PairDesc* pairs, const BlockPai
         // a segmented flag takes at least two slots
         int64_t fw = slots / 2 < max_flags ? slots / 2 : max_flags;
         if (fw > gmax_grid) fw = gmax_grid;
-        if (fw > 0)
+        if (one && end && ticket) {
+            hipLaunchKernelGGL(k_recheck_finish_end, dim3((unsigned)(fw > 0 ? fw : 1)), dim3(kRecheckThreads), 0, s, A,
+                               *end, ticket);
+            if (ended) *ended = true;
+        } else if (fw > 0) {
             hipLaunchKernelGGL(k_recheck_finish, dim3((unsigned)fw), dim3(kRecheckThreads), 0, s, A);
-    }
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// null moments: sums of T_b - T_obs and (T_b - T_obs)^2 over a block's splits,
-// one work-group per pair, in a fixed order; blocks add in stream order
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_moments(const BlockPair* __restrict__ bp,
-                                                 const PairState* __restrict__ st,
-                                                 const double* __restrict__ Tw, PairCount* cnt) {
-    __shared__ double r1[256], r2[256];
-    const int p = blockIdx.x;
-    const BlockPair q = bp[p];
-    const double c = st[p].t_obs;
-    double a = 0.0, b = 0.0;
-    for (int64_t k = threadIdx.x; k < q.nb; k += 256) {
-        const double x = Tw[q.mrow0 + k] - c;
-        a += x;
-        b += x * x;
-    }
-    r1[threadIdx.x] = a;
-    r2[threadIdx.x] = b;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (threadIdx.x < o) {
-            r1[threadIdx.x] += r1[threadIdx.x + o];
-            r2[threadIdx.x] += r2[threadIdx.x + o];
         }
-        __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        cnt[p].sum_dt += r1[0];
-        cnt[p].sum_dt2 += r2[0];
-    }
-}
-
-hipError_t launch_moments(int npairs, const BlockPair* bp, const PairState* st, const double* Tw,
-                          PairCount* cnt, hipStream_t s) {
-    hipLaunchKernelGGL(k_moments, dim3(npairs), dim3(256), 0, s, bp, st, Tw, cnt);
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// p = (1 + count) / (B + 1)  (eq:pvalue)
-// ---------------------------------------------------------------------------
-__global__ void k_final(int npairs, const BlockPair* __restrict__ bp, const PairState* __restrict__ st,
-                        const int32_t* __restrict__ sstat,
-                        const PairCount* __restrict__ cnt, const int64_t* __restrict__ Btot,
-                        hbt_result* res) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= npairs) return;
-    const PairState q = st[p];
-    hbt_result r = res[p];
-    r.count = (int64_t)cnt[p].count;
-    r.n_recheck = (int64_t)cnt[p].n_recheck;
-    r.B = Btot[p];
-    r.p = (1.0 + (double)r.count) / ((double)r.B + 1.0);
-    const double mean = cnt[p].sum_dt / (double)r.B;
-    const double var = cnt[p].sum_dt2 / (double)r.B - mean * mean;
-    r.t_mean = q.t_obs + mean;
-    r.t_sd = var != var ? var : sqrt(var > 0.0 ? var : 0.0);
-    r.status = q.status != HBT_OK ? q.status : sstat[bp[p].owner];  // the alignment's status first
-    res[p] = r;
-}
-
-hipError_t launch_final(int npairs, const BlockPair* bp, const PairState* st, const int32_t* sstat,
-                        const PairCount* cnt, const int64_t* Btot, hbt_result* res, hipStream_t s) {
-    hipLaunchKernelGGL(k_final, dim3((npairs + 255) / 256), dim3(256), 0, s, npairs, bp, st, sstat,
-                       cnt, Btot, res);
     return hipGetLastError();
 }
 

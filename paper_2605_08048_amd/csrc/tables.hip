@@ -83,7 +83,7 @@ __global__ __launch_bounds__(kTabThreads) void k_build_tables(TableArgs A) {
         __syncthreads();  // the clouds' entries are read below
     }
     // 2. pairs and their splits
-    int64_t row = 0, zrow = 0, coef = 0, chunk = 0, xoct = 0, srow = 0, word = 0;
+    int64_t row = 0, zrow = 0, coef = 0, chunk = 0, xoct = 0, srow = 0, word = 0, nbig = 0, bigrow = 0;
     for (int p0 = 0; p0 < A.npairs; p0 += kTabThreads) {
         const int p = p0 + t;
         const bool in = p < A.npairs;
@@ -154,17 +154,28 @@ __global__ __launch_bounds__(kTabThreads) void k_build_tables(TableArgs A) {
         b.Wp = pd.Wp;
         b.pair_index = pd.pair_index;
         b.ygap = pd.ygap;
+        const bool big = in && pd.Np > kQuadItems;
+        const int64_t kb = nbig + tab_scan(big ? 1 : 0, sh, &tot);
+        nbig += tot;
+        const int64_t rb = bigrow + tab_scan(big ? B : 0, sh, &tot);
+        bigrow += tot;
+        if (big) {
+            A.big_pair[kb] = p;
+            A.big_row0[kb] = rb;
+        }
         if (in) {
             A.pairs[p] = pd;
             A.bp[p] = b;
             A.Btot[p] = B;
             A.nflag[p] = 0u;
             A.sstat[p] = 0;
+            A.ticket[p] = 0u;
             if (A.rcnt) A.rcnt[p] = 0u;
         }
         __syncthreads();
         if (in && owner != p) A.bp[p].mword0 = A.bp[owner].mword0;  // an earlier pair's masks
     }
+    if (t == 0 && (A.npairs & 1)) A.nflag[A.npairs] = 0u;  // the odd word (a single pair's ticket)
     // 3. the product's groups: ngw of the wide tiles, then the others, tiles
     //    numbered from 0 in each
     for (int part = 0; part < 2; ++part) {

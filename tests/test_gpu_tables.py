@@ -95,3 +95,18 @@ def test_shared_clouds_equal_the_pairs_stored_apart(C, P, gaps):
     for k in ("count", "B", "n", "m", "status", "p"):
         assert np.array_equal(r[k], s[k]), k
     assert np.allclose(r["t_obs"], s["t_obs"], rtol=0, atol=1e-12 * (1 + np.abs(s["t_obs"]).max()))
+
+
+@pytest.mark.parametrize("d", [64, 300, 700, 1024, 1100, 2500])
+def test_alignment_does_not_depend_on_the_call(d):
+    # one pair's column sums are added by many work-groups, a batch's by one per
+    # pair; enough rows that every quarter of the chunks holds some
+    g = np.random.default_rng(d)
+    n, m = np.array([700, 20, 130] + [5] * 8), np.array([400, 900, 33] + [6] * 8)
+    off = np.concatenate([[0], np.cumsum(n + m)])
+    Z = _rows(g, int(off[-1]), d)
+    r = hbt.perm_test_batched(Z, off, n, m, np.full(11, 30), seed=2)
+    three = hbt.perm_test_batched(Z, off[:4], n[:3], m[:3], np.full(3, 30), seed=2)
+    for p, s in _singles(Z, off, n, m, np.full(11, 30), np.arange(11), range(3), seed=2, precision="bf16x2"):
+        for k in FIELDS + ("r_x", "r_y", "mu_cos", "tau"):
+            assert r[k][p] == s[k] == three[k][p], (p, k)
