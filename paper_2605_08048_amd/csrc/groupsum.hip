@@ -662,7 +662,21 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // FP32 / FP64: v_mfma_{f32_16x16x4f32, f64_16x16x4f64}
 // A (16 x 4) lane l -> row l%16, k l/16; B (4 x 16) lane l -> k l/16, col l%16;
 // D lane l -> col l%16, register v -> row 4(l/16) + v (f32) or 4v + l/16 (f64).
-// Wave tile: 64 columns (4 blocks) x 64 splits (4 blocks).
+// Work-group: 64 columns (4 blocks) x four waves of 16 JB splits.  Bound by the
+// matrix cores.  The 64-column slice of Z, which all four waves multiply, streams
+// through LDS in chunks of 16 KB (64 rows of floats, 32 of doubles) by direct
+// loads, one chunk ahead in two buffers; each row is stored turned by 16 columns
+// times its number modulo 4, so that the four rows of a K-step lie on different
+// banks.  A K-step's operands are read while the one before is multiplied.  (With
+// every wave loading its own operands from memory as it needed them, n = 2000,
+// m = 1500, d = 768, B = 10000 took 620 us in float; now 495, 111 TF/s.  What is left:
+// 40 us of the bits' expansion, which does not overlap its wave's products.)
+// JB = 4 for full tiles; JB = 1, a quarter of the splits per work-group and of a
+// wave's serial K-loop, where the tiles of JB = 4 would leave CUs without one.
+// (n = 2000, m = 1500, d = 768 in float: a whole tile alone on a CU takes 263 us,
+// quarters 66 each where there are several; so 180 tiles take 198 us as quarters,
+// 263 whole, and 240 tiles 265 and 263.  n = 100, m = 80, d = 64, B = 1000 in
+// double, 4 tiles: 8.2 us, 24 as whole tiles with operands from memory.)
 // ---------------------------------------------------------------------------
 template <typename T>
 struct MfmaFp;
@@ -673,6 +687,10 @@ struct MfmaFp<float> {
         return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
     }
     static __device__ __forceinline__ int row(int q, int v) { return 4 * q + v; }
+    // 1 where the bit is set, else 0
+    static __device__ __forceinline__ float member(uint32_t w, int bit) {
+        return __uint_as_float((uint32_t)__builtin_amdgcn_sbfe((int)w, bit, 1) & 0x3f800000u);
+    }
 };
 template <>
 struct MfmaFp<double> {
@@ -681,65 +699,126 @@ struct MfmaFp<double> {
         return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
     }
     static __device__ __forceinline__ int row(int q, int v) { return 4 * v + q; }
+    static __device__ __forceinline__ double member(uint32_t w, int bit) {
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_sbfe((int)w, bit, 1) & 0x3ff00000u;
+        return __builtin_bit_cast(double, (uint64_t)hi << 32);
+    }
 };
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_groupsum_fp(const PairDesc* __restrict__ pairs,
-                                                     const BlockPair* __restrict__ bp,
-                                                     const GemmTile* __restrict__ tiles,
-                                                     int nslot, int d_pad, const T* __restrict__ z,
-                                                     const uint32_t* __restrict__ mask,
-                                                     const T* __restrict__ tvec,
-                                                     double* __restrict__ partial, int64_t prow,
-                                                     float* __restrict__ sig) {
+template <typename T, int JB>
+__global__ __launch_bounds__(256, 2) void k_groupsum_fp(const PairDesc* __restrict__ pairs,
+                                                        const BlockPair* __restrict__ bp,
+                                                        const GemmTile* __restrict__ tiles,
+                                                        int nslot, int d_pad, const T* __restrict__ z,
+                                                        const uint32_t* __restrict__ mask,
+                                                        const T* __restrict__ tvec,
+                                                        double* __restrict__ partial, int64_t prow,
+                                                        float* __restrict__ sig) {
     typedef typename MfmaFp<T>::acc_t acc_t;
-    const GemmTile tile = tiles[blockIdx.x / nslot];
-    const int slot = blockIdx.x % nslot;
+    constexpr int kRows = 256 / (int)sizeof(T);  // of a chunk
+    constexpr int kWords = kRows / 32;           // mask words of a chunk
+    constexpr int kLaneRows = 16 / (int)sizeof(T);  // rows of one 1 KB load
+    constexpr int kSub = 4 / JB;                 // work-groups per tile of kTileB splits
+    static_assert(kTileB == 256 && kDSlot == 64, "tile");
+    __shared__ T zb[2][kRows * kDSlot];
+    const int slot = blockIdx.x % nslot, rest = blockIdx.x / nslot;
+    const GemmTile tile = tiles[rest / kSub];
     const PairDesc pd = pairs[tile.pair];
     const BlockPair bq = bp[tile.pair];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int b0 = tile.b0 + 64 * JB * (rest % kSub);
+    if (b0 >= bq.nb) return;  // work-group-uniform
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int q = lane >> 4, c = lane & 15;
     const int d0 = slot * kDSlot;
-    int brow[4];
-    bool valid[4];
-    const uint32_t* mrow[4];
+    int brow[JB];
+    bool valid[JB];
+    const uint32_t* mrow[JB];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        brow[j] = tile.b0 + wave * 64 + j * 16 + c;
+    for (int j = 0; j < JB; ++j) {
+        brow[j] = b0 + wave * 16 * JB + j * 16 + c;
         valid[j] = brow[j] < bq.nb;
         mrow[j] = mask_row(mask, bq, bq.mrow0 + (valid[j] ? brow[j] : 0), pd.Wp);
     }
     const uint32_t flip = pd.flip ? 0xffffffffu : 0u;
-    const T* za = z + pd.zrow0 * d_pad + d0 + c;
-    acc_t acc[4][4];
+    // Chunk loads: wave w fills LDS bytes 1024 (4 w + k) of the chunk, k < 4;
+    // lane l's 16 bytes hold row r, columns from the turned position back
+    const T* zsrc[4];
+    uint32_t zlds[2];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int per_row = 64 / kLaneRows, u = 4 * wave + k;  // lanes of a row
+        const int r = kLaneRows * u + lane / per_row;
+        const int col = ((16 / (int)sizeof(T)) * (lane % per_row) - 16 * (r & 3)) & (kDSlot - 1);
+        zsrc[k] = z + (pd.zrow0 + r) * d_pad + d0 + col;
+    }
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+        zlds[b] = __builtin_amdgcn_readfirstlane(lds_addr(&zb[b][0]) + 4096u * (uint32_t)wave);
+    const int64_t chunk_stride = (int64_t)kRows * d_pad;
+    auto issue = [&](int ch, int b) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) dma16(zsrc[k] + ch * chunk_stride, zlds[b] + 1024u * k);
+    };
+    uint32_t mw[JB][kWords];
+    auto load_mask = [&](int ch) {
+#pragma unroll
+        for (int j = 0; j < JB; ++j)
+#pragma unroll
+            for (int w = 0; w < kWords; ++w) mw[j][w] = mrow[j][kWords * ch + w];
+    };
+    int aoff[4];  // of this lane's operand of column block i in a K-step's four rows
+#pragma unroll
+    for (int i = 0; i < 4; ++i) aoff[i] = q * kDSlot + 16 * ((i + q) & 3) + c;
+
+    acc_t acc[4][JB];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < JB; ++j)
 #pragma unroll
             for (int v = 0; v < 4; ++v) acc[i][j][v] = 0;
 
-    for (int kw = 0; kw < pd.Wp; ++kw) {
-        uint32_t mw[4];
+    const int nchunk = pd.Np / kRows;
+    issue(0, 0);
+    load_mask(0);
+    __builtin_amdgcn_s_waitcnt(0);
+    lds_barrier();
+    for (int ch = 0; ch < nchunk; ++ch) {
+        // this chunk's mask bits, bit 4 s of word w the lane's row of K-step s
+        uint32_t bits[JB][kWords];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) mw[j] = valid[j] ? (mrow[j][kw] ^ flip) : 0u;
-#pragma unroll 2
-        for (int s = 0; s < 8; ++s) {  // K-steps of 4 pooled rows
-            const int64_t rowz = (int64_t)(32 * kw + 4 * s + q) * d_pad;
-            T a[4], b[4];
+        for (int j = 0; j < JB; ++j)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = za[rowz + 16 * i];
+            for (int w = 0; w < kWords; ++w) bits[j][w] = valid[j] ? (mw[j][w] ^ flip) >> q : 0u;
+        if (ch + 1 < nchunk) {  // uniform
+            issue(ch + 1, (ch + 1) & 1);  // into the buffer read in the last step
+            load_mask(ch + 1);
+        }
+        const T* cur = zb[ch & 1];
+        T a[2][4];
+        auto fetch = [&](int s, T (&x)[4]) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = ((mw[j] >> (4 * s + q)) & 1u) ? (T)1 : (T)0;
+            for (int i = 0; i < 4; ++i) x[i] = cur[4 * kDSlot * s + aoff[i]];
+        };
+        fetch(0, a[0]);
+#pragma unroll
+        for (int s = 0; s < kRows / 4; ++s) {  // K-steps of 4 pooled rows
+            if (s + 1 < kRows / 4) fetch(s + 1, a[(s + 1) & 1]);
+            T b[JB];
+#pragma unroll
+            for (int j = 0; j < JB; ++j) b[j] = MfmaFp<T>::member(bits[j][s / 8], 4 * (s & 7));
+            __builtin_amdgcn_sched_barrier(0);  // the reads stay ahead of these products
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = MfmaFp<T>::mma(a[i], b[j], acc[i][j]);
+                for (int j = 0; j < JB; ++j) acc[i][j] = MfmaFp<T>::mma(a[s & 1][i], b[j], acc[i][j]);
         }
+        __builtin_amdgcn_s_waitcnt(0);  // the next chunk has landed
+        lds_barrier();                  // ... every wave's part, and this one's readers are done
     }
     const T* tp = tvec + (int64_t)tile.pair * d_pad + d0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < JB; ++j) {
         T ss = 0, sl = 0;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -870,18 +949,21 @@ hipError_t launch_groupsum(int precision, const PairDesc* pairs, const BlockPair
                                    pairs, bp, groups + ngw, ng256, nt256, nslot, d_pad, (const uint4*)zstore,
                                    zplane_elems / 16, mask, t64, partial, prow);
             break;
-        case HBT_F32:
+        default: {
             if (ntiles <= 0) return hipSuccess;
-            hipLaunchKernelGGL(k_groupsum_fp<float>, dim3((unsigned)(ntiles * nslot)), block, 0, s,
-                               pairs, bp, tiles, nslot, d_pad, (const float*)zstore, mask, t32,
-                               partial, prow, sig);
+            auto go = [&](auto kern, int sub, auto* zs, auto* tv) {
+                hipLaunchKernelGGL(kern, dim3((unsigned)(ntiles * nslot * sub)), block, 0, s, pairs, bp, tiles, nslot,
+                                   d_pad, zs, mask, tv, partial, prow, sig);
+            };
+            // full tiles for less than 3/4 of the CUs: quarters of a tile, at most
+            // three to a CU (figures at the kernel)
+            const bool few = 4 * (int64_t)ntiles * nslot <= 3 * (int64_t)device_cus();
+            if (precision == HBT_F32 && few) go(k_groupsum_fp<float, 1>, 4, (const float*)zstore, t32);
+            else if (precision == HBT_F32) go(k_groupsum_fp<float, 4>, 1, (const float*)zstore, t32);
+            else if (few) go(k_groupsum_fp<double, 1>, 4, (const double*)zstore, t64);
+            else go(k_groupsum_fp<double, 4>, 1, (const double*)zstore, t64);
             break;
-        default:
-            if (ntiles <= 0) return hipSuccess;
-            hipLaunchKernelGGL(k_groupsum_fp<double>, dim3((unsigned)(ntiles * nslot)), block, 0, s,
-                               pairs, bp, tiles, nslot, d_pad, (const double*)zstore, mask, t64,
-                               partial, prow, sig);
-            break;
+        }
     }
     return hipGetLastError();
 }
