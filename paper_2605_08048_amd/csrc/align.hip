@@ -78,8 +78,39 @@ __device__ __forceinline__ float wave_total_f32(float x) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
+// Row loads through a buffer resource: the hardware returns 0 for every
+// byte offset at or past the resource's size without touching memory, so a
+// row that does not exist (size 0) or a column at or past d reads zero with
+// no branch and no select, and the loads of several rows are all in flight
+// before the first wait.  Word 3 is the gfx9 raw-buffer format (32-bit data).
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* p, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, bytes, 0x00020000);
+}
+
+// This lane's J x 4 columns 256 j + 64 e + lane of one row of d values (all
+// zero when the row is not valid).
+template <int J, typename Tin>
+__device__ __forceinline__ void load_cols(Tin (&x)[J][4], const Tin* row, int d, bool valid) {
+    const int lane = threadIdx.x & 63;
+    const __amdgpu_buffer_rsrc_t rs = row_rsrc(row, valid ? (int)sizeof(Tin) * d : 0);
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int at = (int)sizeof(Tin) * (256 * j + 64 * e + lane);
+            if constexpr (sizeof(Tin) == 4)
+                x[j][e] = __builtin_bit_cast(Tin, __builtin_amdgcn_raw_buffer_load_b32(rs, at, 0, 0));
+            else
+                x[j][e] = __builtin_bit_cast(Tin, __builtin_amdgcn_raw_buffer_load_b64(rs, at, 0, 0));
+        }
+}
+
 // ---------------------------------------------------------------------------
-// column sums: one work-group = 64 columns x one chunk of rows, 4 row phases
+// column sums, any rows of d > 1024: one work-group = 64 columns x one chunk of
+// rows, 4 row phases
 // ---------------------------------------------------------------------------
 template <typename Tin>
 __global__ __launch_bounds__(256) void k_colsum(const PairDesc* __restrict__ pairs,
@@ -123,14 +154,88 @@ __global__ __launch_bounds__(256) void k_colsum(const PairDesc* __restrict__ pai
         partial[(int64_t)blockIdx.x * d + c] = (red[0][tx] + red[1][tx]) + (red[2][tx] + red[3][tx]);
 }
 
-hipError_t launch_colsum(int input_dtype, const PairDesc* pairs, int npairs,
-                         int nchunks, int d, double* partial, int32_t* chunk_bad, hipStream_t s) {
+// The same sums for rows of d <= 1024 that the 16-byte path does not take: one
+// work-group = one chunk x all columns, each row read once for the sums and its
+// test.  A chunk's sum is eight chains of rows, r0 + w, r0 + w + 8, ... (the two
+// accumulators of each phase above), one to a wave, four rows in flight, added
+// in k_colsum's order; so both give the same bits.  Bound by the latency of a
+// wave's loads: n = 777, m = 1333, d = 301, 46 us as 64-column work-groups whose
+// first tested the chunk's rows one by one, 8.7 us so.
+template <typename Tin, int J>
+__global__ __launch_bounds__(512) void k_colsum_rows(const PairDesc* __restrict__ pairs, int npairs, int d,
+                                                     double* __restrict__ partial,
+                                                     int32_t* __restrict__ chunk_bad) {
+    __shared__ double red[4][256 * J];
+    const SumChunk ch = chunk_of(pairs, npairs, blockIdx.x);
+    const PairDesc pd = pairs[ch.pair];
+    const Tin* base = (const Tin*)(ch.side ? pd.Y : pd.X);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    double acc[J][4];
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[j][e] = 0.0;
+    bool bad = false;
+    for (int r = ch.r0 + wave; r < ch.r1; r += 32) {
+        Tin x[4][J][4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int rr = r + 8 * q;
+            load_cols<J>(x[q], base + (int64_t)(rr < ch.r1 ? rr : r) * d, d, rr < ch.r1);
+        }
+        double ss[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            ss[q] = 0.0;
+            if (r + 8 * q >= ch.r1) continue;  // wave-uniform: nothing added past the chunk
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const double a = (double)x[q][j][e];
+                    acc[j][e] += a;
+                    ss[q] += a * a;
+                }
+        }
+        for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) ss[q] += __shfl_xor(ss[q], o, 64);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) bad |= r + 8 * q < ch.r1 && not_unit(ss[q]);
+    }
+    auto col = [&](int j, int e) { return 256 * j + 64 * e + lane; };
+    if (wave >= 4)
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) red[wave - 4][col(j, e)] = acc[j][e];
+    bad = __syncthreads_or(bad);
+    if (threadIdx.x == 0) chunk_bad[blockIdx.x] = bad ? 1 : 0;
+    if (wave < 4)
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) red[wave][col(j, e)] = acc[j][e] + red[wave][col(j, e)];
+    __syncthreads();
+    for (int c = threadIdx.x; c < d; c += 512)
+        partial[(int64_t)blockIdx.x * d + c] = (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
+}
+
+hipError_t launch_colsum(int input_dtype, const PairDesc* pairs, int npairs, int nchunks, int d, int d_pad,
+                         double* partial, int32_t* chunk_bad, hipStream_t s) {
     if (nchunks <= 0) return hipSuccess;
-    dim3 grid(nchunks, (d + 63) / 64);
-    if (input_dtype == HBT_IN_F64)
-        hipLaunchKernelGGL(k_colsum<double>, grid, dim3(256), 0, s, pairs, npairs, d, partial, chunk_bad);
-    else
-        hipLaunchKernelGGL(k_colsum<float>, grid, dim3(256), 0, s, pairs, npairs, d, partial, chunk_bad);
+    const bool f64 = input_dtype == HBT_IN_F64;
+    auto go = [&](auto kern, dim3 grid, int threads) {
+        hipLaunchKernelGGL(kern, grid, dim3(threads), 0, s, pairs, npairs, d, partial, chunk_bad);
+    };
+    const dim3 tiles(nchunks, (d + 63) / 64), chunks(nchunks);
+    switch ((d_pad + 255) / 256) {
+        case 1: f64 ? go(k_colsum_rows<double, 1>, chunks, 512) : go(k_colsum_rows<float, 1>, chunks, 512); break;
+        case 2: f64 ? go(k_colsum_rows<double, 2>, chunks, 512) : go(k_colsum_rows<float, 2>, chunks, 512); break;
+        case 3: f64 ? go(k_colsum_rows<double, 3>, chunks, 512) : go(k_colsum_rows<float, 3>, chunks, 512); break;
+        case 4: f64 ? go(k_colsum_rows<double, 4>, chunks, 512) : go(k_colsum_rows<float, 4>, chunks, 512); break;
+        default: f64 ? go(k_colsum<double>, tiles, 256) : go(k_colsum<float>, tiles, 256); break;
+    }
     return hipGetLastError();
 }
 
@@ -138,32 +243,6 @@ hipError_t launch_colsum(int input_dtype, const PairDesc* pairs, int npairs,
 // work-group = one chunk of rows x all columns; wave w sums rows w, w+4, ...
 // of the chunk with 16-byte loads (lane l: columns 4(l + 64 j) .. +3), the
 // four waves' sums are added in a fixed order through LDS.
-// Row loads through a buffer resource: the hardware returns 0 for every
-// byte offset at or past the resource's size without touching memory, so a
-// row that does not exist (size 0) or a column at or past d reads zero with
-// no branch and no select, and the loads of several rows are all in flight
-// before the first wait.  Word 3 is the gfx9 raw-buffer format (32-bit data).
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* p, int bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, bytes, 0x00020000);
-}
-
-// This lane's J x 4 columns 256 j + 64 e + lane of one FP32 row of d values
-// (all zero when the row is not valid).
-template <int J>
-__device__ __forceinline__ void load_cols(float (&x)[J][4], const float* row, int d, bool valid) {
-    const int lane = threadIdx.x & 63;
-    const __amdgpu_buffer_rsrc_t rs = row_rsrc(row, valid ? 4 * d : 0);
-#pragma unroll
-    for (int j = 0; j < J; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            x[j][e] = __builtin_bit_cast(
-                float, __builtin_amdgcn_raw_buffer_load_b32(rs, 4 * (256 * j + 64 * e + lane), 0, 0));
-}
-
 // (red: at least 3 rows of 256 J doubles)
 template <int J>
 __device__ __forceinline__ void colsum4_chunk(const SumChunk& ch, const PairDesc& pd, int d,
@@ -1014,14 +1093,17 @@ hipError_t launch_colsum_store_vec(int precision, const PairDesc* pairs, int npa
 }
 
 // ---------------------------------------------------------------------------
-// hbt_align's output: X' = H X in the input dtype, one wave per row
+// hbt_align's output: X' = H X in the input dtype, one wave per row.  Rows of
+// d <= 256 J are read once and kept in registers; J = 0, any d, reads them twice.
+// Bound by the latency of a row's loads and its sum over the wave: n = 3000,
+// d = 1024, float, 11.5 us reading them twice, 7.1 so.
 // ---------------------------------------------------------------------------
-template <typename Tin>
+template <typename Tin, int J>
 __global__ __launch_bounds__(256) void k_reflect_out(const PairDesc* __restrict__ pair,
                                                      const PairState* __restrict__ st,
                                                      const double* __restrict__ v, int n, int d,
                                                      Tin* X_out, double* v_out) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int i = blockIdx.x * 4 + wave;
     if (v_out && blockIdx.x == 0)
         for (int c = threadIdx.x; c < d; c += 256) v_out[c] = v[c];
@@ -1030,24 +1112,54 @@ __global__ __launch_bounds__(256) void k_reflect_out(const PairDesc* __restrict_
     Tin* y = X_out + (int64_t)i * d;
     const int identity = st->identity;
     double w = 0.0;
-    if (!identity) {
-        for (int c = lane; c < d; c += 64) w += v[c] * (double)x[c];
-        for (int o = 32; o > 0; o >>= 1) w += __shfl_xor(w, o, 64);
-    }
-    const double k = identity ? 0.0 : 2.0 * w / st->vv;
     // every lane has read its share of the row (inside the dot product) before
     // any write, so X_out may alias X
-    for (int c = lane; c < d; c += 64) y[c] = (Tin)((double)x[c] - k * v[c]);
+    if constexpr (J > 0) {
+        Tin xr[J][4];
+        double vc[J][4];
+        load_cols<J>(xr, x, d, true);
+        load_cols<J>(vc, v, d, true);
+        if (!identity) {
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w += vc[j][e] * (double)xr[j][e];
+            w = wave_sum_f64(w);
+        }
+        const double k = identity ? 0.0 : 2.0 * w / st->vv;
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int c = 256 * j + 64 * e + lane;
+                if (c < d) y[c] = (Tin)((double)xr[j][e] - k * vc[j][e]);
+            }
+    } else {
+        if (!identity) {
+            for (int c = lane; c < d; c += 64) w += v[c] * (double)x[c];
+            w = wave_sum_f64(w);
+        }
+        const double k = identity ? 0.0 : 2.0 * w / st->vv;
+        for (int c = lane; c < d; c += 64) y[c] = (Tin)((double)x[c] - k * v[c]);
+    }
 }
 
 hipError_t launch_reflect_out(int input_dtype, const PairDesc* pair, const PairState* st,
                               const double* v, int n, int d, void* X_out, double* v_out,
                               hipStream_t s) {
-    dim3 g((n + 3) / 4), b(256);
-    if (input_dtype == HBT_IN_F64)
-        hipLaunchKernelGGL(k_reflect_out<double>, g, b, 0, s, pair, st, v, n, d, (double*)X_out, v_out);
-    else
-        hipLaunchKernelGGL(k_reflect_out<float>, g, b, 0, s, pair, st, v, n, d, (float*)X_out, v_out);
+    auto go = [&](auto kern, auto* out) {
+        hipLaunchKernelGGL(kern, dim3((n + 3) / 4), dim3(256), 0, s, pair, st, v, n, d, out, v_out);
+    };
+    const bool f64 = input_dtype == HBT_IN_F64;
+    double* xd = (double*)X_out;
+    float* xf = (float*)X_out;
+    switch ((d + 255) / 256) {
+        case 1: f64 ? go(k_reflect_out<double, 1>, xd) : go(k_reflect_out<float, 1>, xf); break;
+        case 2: f64 ? go(k_reflect_out<double, 2>, xd) : go(k_reflect_out<float, 2>, xf); break;
+        case 3: f64 ? go(k_reflect_out<double, 3>, xd) : go(k_reflect_out<float, 3>, xf); break;
+        case 4: f64 ? go(k_reflect_out<double, 4>, xd) : go(k_reflect_out<float, 4>, xf); break;
+        default: f64 ? go(k_reflect_out<double, 0>, xd) : go(k_reflect_out<float, 0>, xf); break;
+    }
     return hipGetLastError();
 }
 

@@ -696,7 +696,7 @@ hbt_status enqueue_prologue(const Plan& P, const Workspace& w, int align, int gd
         HIP_TRY(launch_colsum_vec(w.pairs, P.npairs, (int)P.nchunks, P.d, P.d_pad, w.partial_sum,
                                   w.chunk_bad, s));
     else
-        HIP_TRY(launch_colsum(P.input_dtype, w.pairs, P.npairs, (int)P.nchunks, P.d,
+        HIP_TRY(launch_colsum(P.input_dtype, w.pairs, P.npairs, (int)P.nchunks, P.d, P.d_pad,
                               w.partial_sum, w.chunk_bad, s));
     HIP_TRY(launch_finalize(w.pairs, P.npairs, w.partial_sum, w.chunk_bad, P.d, P.d_pad, align, gd, w.sxy, w.st,
                             w.v, w.t64, w.t32, w.cnt, res, w.ticket, s));

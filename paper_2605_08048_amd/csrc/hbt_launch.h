@@ -60,7 +60,7 @@ hipError_t launch_build_tables(const TableArgs& A, hipStream_t s);
 // chunk_bad[chunk] = 1 when a row of the chunk is not a unit vector
 // (| |x| - 1 | > 1e-4 or NaN), else 0; every launcher below writes it.
 hipError_t launch_colsum(int input_dtype, const PairDesc* pairs, int npairs,
-                         int nchunks, int d, double* partial, int32_t* chunk_bad, hipStream_t s);
+                         int nchunks, int d, int d_pad, double* partial, int32_t* chunk_bad, hipStream_t s);
 // Per pair: sums, r, mean directions, v, v.v, identity, T_obs, tau, the pooled
 // total t (FP64 and FP32), the hbt_result header.
 hipError_t launch_finalize(const PairDesc* pairs, int npairs, const double* partial,
