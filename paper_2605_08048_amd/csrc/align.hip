@@ -337,33 +337,69 @@ hipError_t launch_colsum_vec(const PairDesc* pairs, int npairs, int nchunks, int
 // ---------------------------------------------------------------------------
 // Householder coefficients 2 (v . x_i) / (v . v) of every X row, for pairs
 // whose rows are stored unreflected (eq:householder_fast folded into the
-// statistic): one wave per row, FP64 dot product of the FP32 row.
+// statistic): FP64 dot products of the FP32 rows (d <= 256 J).  One wave takes
+// kFoldRows consecutive rows, all in flight, against v in registers, which it
+// loads again where its rows pass from one pair to the next.  Bound by the loads
+// and, beside the split kernel, by its share of the CUs: 512 pairs of 20 to 5000
+// rows of d = 768, 850 to 920 us with one row a wave and v read for each, 325 so.
 // ---------------------------------------------------------------------------
+constexpr int kFoldRows = 4;  // 8 take more registers than the split kernel's waves leave
+template <int J>
 __global__ __launch_bounds__(256) void k_fold_coef(const PairDesc* __restrict__ pairs, int npairs,
                                                    const PairState* __restrict__ st,
                                                    const double* __restrict__ v, int d, int d_pad,
                                                    int64_t total, double* __restrict__ coef) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t r = (int64_t)blockIdx.x * 4 + wave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    int64_t r = ((int64_t)blockIdx.x * 4 + wave) * kFoldRows;
     if (r >= total) return;
-    const int p = upper_index(npairs, r, [&](int k) { return pairs[k].coef0; });
-    const PairDesc pd = pairs[p];
-    const int identity = st[p].identity;
-    double w = 0.0;
-    if (!identity) {  // wave-uniform
-        const float* x = (const float*)pd.X + (r - pd.coef0) * d;
-        const double* vp = v + (int64_t)p * d_pad;
-        for (int c = lane; c < d; c += 64) w += vp[c] * (double)x[c];
-        for (int o = 32; o > 0; o >>= 1) w += __shfl_xor(w, o, 64);
+    const int64_t rend = r + kFoldRows < total ? r + kFoldRows : total;
+    int p = upper_index(npairs, r, [&](int k) { return pairs[k].coef0; });
+    for (; r < rend; ++p) {  // wave-uniform
+        const int64_t r0 = pairs[p].coef0, next = r0 + pairs[p].n;
+        const int k = (int)((next < rend ? next : rend) - r);  // rows of this pair
+        double w[kFoldRows];
+#pragma unroll
+        for (int q = 0; q < kFoldRows; ++q) w[q] = 0.0;
+        const int identity = st[p].identity;
+        if (!identity) {
+            const float* x0 = (const float*)pairs[p].X + (r - r0) * d;
+            float x[kFoldRows][J][4];
+            double vc[J][4];
+#pragma unroll
+            for (int q = 0; q < kFoldRows; ++q) load_cols<J>(x[q], x0 + (q < k ? q : 0) * (int64_t)d, d, q < k);
+            load_cols<J>(vc, v + (int64_t)p * d_pad, d, true);
+#pragma unroll
+            for (int q = 0; q < kFoldRows; ++q)
+#pragma unroll
+                for (int j = 0; j < J; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) w[q] += vc[j][e] * (double)x[q][j][e];
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+                for (int q = 0; q < kFoldRows; ++q) w[q] += __shfl_xor(w[q], o, 64);
+        }
+        if (lane < k) {
+            double wl = w[0];
+#pragma unroll
+            for (int q = 1; q < kFoldRows; ++q) wl = lane == q ? w[q] : wl;
+            coef[r + lane] = identity ? 0.0 : 2.0 * wl / st[p].vv;
+        }
+        r += k;
     }
-    if (lane == 0) coef[r] = identity ? 0.0 : 2.0 * w / st[p].vv;
 }
 
 hipError_t launch_fold_coef(const PairDesc* pairs, int npairs, const PairState* st, const double* v, int d,
                             int d_pad, int64_t total, double* coef, hipStream_t s) {
     if (total <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_fold_coef, dim3((unsigned)((total + 3) / 4)), dim3(256), 0, s, pairs, npairs, st, v,
-                       d, d_pad, total, coef);
+    const dim3 g((unsigned)((total + 4 * kFoldRows - 1) / (4 * kFoldRows))), b(256);
+    switch ((d_pad + 255) / 256) {
+        case 1: hipLaunchKernelGGL(k_fold_coef<1>, g, b, 0, s, pairs, npairs, st, v, d, d_pad, total, coef); break;
+        case 2: hipLaunchKernelGGL(k_fold_coef<2>, g, b, 0, s, pairs, npairs, st, v, d, d_pad, total, coef); break;
+        case 3: hipLaunchKernelGGL(k_fold_coef<3>, g, b, 0, s, pairs, npairs, st, v, d, d_pad, total, coef); break;
+        case 4: hipLaunchKernelGGL(k_fold_coef<4>, g, b, 0, s, pairs, npairs, st, v, d, d_pad, total, coef); break;
+        default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 

@@ -1359,7 +1359,7 @@ static bool plan_clouds(Plan& P, int64_t nclouds, const void* Z_all, const int64
         pd.cy1 = cy.cy1;
         P.ncoef += pd.n;
         P.min_np = P.npairs ? std::min(P.min_np, (int)pd.Np) : (int)pd.Np;
-    P.max_np = std::max(P.max_np, (int)pd.Np);
+        P.max_np = std::max(P.max_np, (int)pd.Np);
         P.fold_segs = std::max(P.fold_segs, fold_segments(pd.n));
         P.pairs.push_back(pd);
         const int own = owners.of((int)p, pd.n, pd.m, B[p], pd.pair_index);

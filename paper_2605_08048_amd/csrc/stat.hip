@@ -13,82 +13,84 @@ namespace hbt {
 // Householder fold: c = sum over the smaller group's X rows of 2 (v . x_i) /
 // (v . v) per split row, in segments of kFoldSegWords mask words (512 X
 // items): work-group (x, y) takes the 256 split rows of block x and segment y
-// of each row's pair, and writes the segment's sum (FP64; four running sums,
-// over the indices i % 4 = 0, 1, 2, 3, added at the end) to
-// fpart[y][row]; segments past a pair's fold_segments(n) are not written.
-// Large pairs thus spread over as many waves as they have segments.  In a
-// wave of one pair (consecutive split rows, Wp words apart) the segment's
-// words of the 64 rows pass through LDS, read as 64-byte runs of each row so
-// that every fetched line is used whole; the 32 coefficients of a word are
-// wave-uniform (scalar loads) and a lane adds the ones its bits select, the
-// selection made with sign-extended one-bit masks rather than branches.  A
-// wave across a pair boundary takes each lane's own pair.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8)))
+// of each row's pair, and writes the segment's sum (FP64) to fpart[y][row];
+// segments past a pair's fold_segments(n) are not written.  Large pairs thus
+// spread over as many waves as they have segments.  For each pair of the block
+// the segment's coefficients become a table of the 16 sums of every four
+// consecutive ones (0 past X), so that a lane adds one table entry per four bits
+// of its mask instead of selecting each item; the 16 entries of a table lie on
+// 32 banks of their own, so the lanes' reads do not conflict.  The mask words pass
+// through LDS, read as 64-byte runs of each row so that every fetched line is
+// used whole.  Bound by a segment's loads and its index arithmetic: 512 pairs of 20
+// to 5000 rows, B = 2000, 228 us with a selection and an addition per item, 92 us so
+// (141 with the mask words loaded after the table is built).
+__global__ __launch_bounds__(256)
 void k_fold_c(const PairDesc* __restrict__ pairs, const BlockPair* __restrict__ bp, int npairs,
-              int64_t rows, const uint32_t* __restrict__ mask, const double* __restrict__ coef,
-              double* __restrict__ fpart) {
+              int64_t rows, double pairs_per_row, const uint32_t* __restrict__ mask,
+              const double* __restrict__ coef, double* __restrict__ fpart) {
     constexpr int kW = kFoldSegWords;
+    static_assert(8 * kW == 128, "two threads to a table");
+    __shared__ double tab[8 * kW][16];  // by four items, by their bits
     // 64 rows x 16 words per wave; a row takes 20 words so that the lanes'
     // 16-byte reads of their own rows fall on distinct banks
     __shared__ uint4 stg[4][64][kW / 4 + 1];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int seg = blockIdx.y, w0 = kW * seg;
-    const int64_t row0 = (int64_t)blockIdx.x * 256 + 64 * wave;
-    const int64_t row = row0 + lane;
-    const bool active = row < rows;
-    if (row0 >= rows) return;  // the whole wave
-    int p = 0;
-    if (active) p = upper_index(npairs, row, [&](int k) { return bp[k].mrow0; });
-    const int p0 = __shfl(p, 0, 64);  // lane 0 is active
-    const bool one_pair = __ballot(!active || p == p0) == ~0ull;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    if (one_pair) {
-        const int pu = __builtin_amdgcn_readfirstlane(p0);
-        const int nu = pairs[pu].n, Wp = pairs[pu].Wp;
-        const int nw = (nu + 31) >> 5;  // X words of a row (nw <= Wp, Wp % 4 == 0)
-        if (w0 >= nw) return;           // wave-uniform: no such segment
-        const uint32_t flip = pairs[pu].flip ? 0xffffffffu : 0u;
-        const double* cf = coef + pairs[pu].coef0;
-        const uint32_t* mk0 = mask_row(mask, bp[pu], row0, Wp);  // 16-byte aligned rows
+    const int64_t row0 = (int64_t)blockIdx.x * 256, rend = min(rows, row0 + 256);
+    const int64_t row = row0 + threadIdx.x;
+    int p = pair_of_row(bp, npairs, row0, pairs_per_row);
+    for (int64_t r0 = row0; r0 < rend; ++p) {  // the block's pairs (work-group-uniform)
+        const BlockPair q = bp[p];
+        const int64_t r1 = min(rend, q.mrow0 + q.nb);
+        const int n = pairs[p].n, Wp = pairs[p].Wp;
+        const int nw = (n + 31) >> 5;  // X words of a row (nw <= Wp, Wp % 4 == 0)
+        const uint32_t flip = pairs[p].flip ? 0xffffffffu : 0u;
+        const double* cf = coef + pairs[p].coef0;
+        const bool mine = row >= r0 && row < r1;
+        if (w0 < nw) {
+            const int k4 = (min(kW, nw - w0) + 3) >> 2;  // words, by four
+            // all loads first: this lane's four quarters of rows, its table items
+            uint4 val[kW / 4];
 #pragma unroll
-        for (int i = 0; i < kW / 4; ++i) {
-            const int idx = 64 * i + lane, r = idx >> 2, q = idx & 3, wq = w0 + 4 * q;
-            uint4 val = make_uint4(0u, 0u, 0u, 0u);
-            if (row0 + r < rows && wq < nw) val = *(const uint4*)(mk0 + (int64_t)r * Wp + wq);
-            stg[wave][r][q] = val;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const int kend = min(kW, nw - w0);
-        for (int k = 0; k < kend; ++k) {
-            const int w = w0 + k;
-            const uint4 u = stg[wave][lane][k >> 2];
-            const uint32_t word = (k & 3) == 0 ? u.x : (k & 3) == 1 ? u.y : (k & 3) == 2 ? u.z : u.w;
-            const uint32_t bits = (word ^ flip) & range_bits(w, 0, nu);
-            const double* cw = cf + 32 * w;  // the array has 32 spare entries at its end
+            for (int i = 0; i < kW / 4; ++i) {
+                const int idx = 64 * i + lane, r = idx >> 2, wq = w0 + 4 * (idx & 3);
+                const int64_t rr = row0 + 64 * wave + r;
+                val[i] = make_uint4(0u, 0u, 0u, 0u);
+                if (rr >= r0 && rr < r1 && wq < nw) val[i] = *(const uint4*)(mask_row(mask, q, rr, Wp) + wq);
+            }
+            // thread t: four consecutive items, half of their table
+            const int item = 32 * w0 + 4 * (threadIdx.x >> 1);
+            double c[4];
 #pragma unroll
-            for (int j = 0; j < 32; ++j) {
-                const uint32_t sel = (uint32_t)__builtin_amdgcn_sbfe((int)bits, j, 1);
-                const uint64_t cb = (uint64_t)__double_as_longlong(cw[j]);
-                const uint64_t m = ((uint64_t)sel << 32) | sel;
-                acc[j & 3] += __longlong_as_double((long long)(cb & m));
+            for (int b = 0; b < 4; ++b) c[b] = item + b < n ? cf[item + b] : 0.0;
+            __syncthreads();  // the last table's readers are done
+            double* te = &tab[threadIdx.x >> 1][8 * (threadIdx.x & 1)];
+            const double c3 = threadIdx.x & 1 ? c[3] : 0.0;
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                te[e] = ((e & 1 ? c[0] : 0.0) + (e & 2 ? c[1] : 0.0)) + ((e & 4 ? c[2] : 0.0) + c3);
+#pragma unroll
+            for (int i = 0; i < kW / 4; ++i) {
+                const int idx = 64 * i + lane;
+                stg[wave][idx >> 2][idx & 3] = val[i];
+            }
+            __syncthreads();
+            if (mine) {
+                double acc[4] = {0.0, 0.0, 0.0, 0.0};
+                for (int k = 0; k < k4; ++k) {
+                    const uint4 u = stg[wave][lane][k];
+                    const uint32_t word[4] = {u.x ^ flip, u.y ^ flip, u.z ^ flip, u.w ^ flip};
+                    const double (*t)[16] = tab + 32 * k;
+#pragma unroll
+                    for (int g = 0; g < 4; ++g)
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) acc[j & 3] += t[8 * g + j][(word[g] >> (4 * j)) & 15u];
+                }
+                fpart[(int64_t)seg * rows + row] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
             }
         }
-    } else if (active) {
-        const PairDesc pd = pairs[p];
-        const int nw = (pd.n + 31) >> 5;
-        if (w0 >= nw) return;
-        const uint32_t* mk = mask_row(mask, bp[p], row, pd.Wp);
-        const uint32_t flip = pd.flip ? 0xffffffffu : 0u;
-        const double* cf = coef + pd.coef0;
-        for (int w = w0; w < min(nw, w0 + kW); ++w) {
-            const uint32_t bits = (mk[w] ^ flip) & range_bits(w, 0, pd.n);
-#pragma unroll 4
-            for (int j = 0; j < 32; ++j) acc[j & 3] += (bits >> j) & 1u ? cf[32 * w + j] : 0.0;
-        }
+        r0 = r1;
     }
-    if (active) fpart[(int64_t)seg * rows + row] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
 }
 
 // MODE kStatLazyFirst (the lazy precision's first pass, hi-plane sums): a
@@ -121,7 +123,8 @@ enum StatMode { kStatPlain = 0, kStatLazyFirst = 1, kStatRefined = 2 };
 template <int MODE>
 __global__ __launch_bounds__(256) void k_stat(const PairDesc* __restrict__ pairs,
                                               const BlockPair* __restrict__ bp, int npairs,
-                                              int64_t rows, const PairState* __restrict__ st,
+                                              int64_t rows, double pairs_per_row,
+                                              const PairState* __restrict__ st,
                                               const double* __restrict__ partial, int nslot,
                                               int64_t prow, int d,
                                               int gd, int alternative, RecheckBand band,
@@ -133,11 +136,14 @@ __global__ __launch_bounds__(256) void k_stat(const PairDesc* __restrict__ pairs
                                               uint32_t* __restrict__ rlist, uint32_t* __restrict__ rcnt) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const bool in_range = i < rows;
-    int p = 0;
     bool exceed = false;
-    if (in_range) p = upper_index(npairs, i, [&](int k) { return bp[k].mrow0; });
-    // a wave's first lane is in range whenever any of its lanes is
-    const int p0 = __shfl(p, 0, 64);
+    const int64_t i0 = (int64_t)blockIdx.x * 256 + (__builtin_amdgcn_readfirstlane(threadIdx.x) & ~63);
+    if (i0 >= rows) return;  // the whole wave
+    // the pair of the wave's first row, then each lane's own past that pair's end
+    // (a search per lane: 57 us for 512 pairs of 2000 rows at d = 768, 44 so)
+    const int p0 = pair_of_row(bp, npairs, i0, pairs_per_row);
+    int p = p0;
+    if (in_range && i >= bp[p0].mrow0 + bp[p0].nb) p = upper_index(npairs, i, [&](int k) { return bp[k].mrow0; });
     bool active = in_range;
     bool refine = false;  // kStatLazyFirst: the split goes to its pair's list
     bool flag = false;    // the split goes to its pair's FP64-recheck list
@@ -155,7 +161,18 @@ __global__ __launch_bounds__(256) void k_stat(const PairDesc* __restrict__ pairs
         const double2* pr = (const double2*)partial + row;
         double ss_small = 0.0, ss_large = 0.0;
         const int ns = nslot > 0 ? nslot : pd.Np / 64;  // 0: the point-to-centroid row tiles of the pair
-        for (int k = 0; k < ns; ++k) {
+        int k = 0;
+        for (; k + 4 <= ns; k += 4) {  // four loads in flight, added in order
+            double2 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = pr[(k + u) * prow];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                ss_small += v[u].x;
+                ss_large += v[u].y;
+            }
+        }
+        for (; k < ns; ++k) {
             const double2 v = pr[k * prow];
             ss_small += v.x;
             ss_large += v.y;
@@ -228,12 +245,13 @@ hipError_t launch_stat(const PairDesc* pairs, const BlockPair* bp, int npairs, i
                        double* fpart, int fold_segs) {
     if (rows <= 0) return hipSuccess;
     const dim3 grid((unsigned)((rows + 255) / 256));
+    const double per_row = (double)npairs / (double)rows;
     if (pv) {
         if (!mask || !coef || !fpart || fold_segs < 1 || fold_segs > 65535) return hipErrorInvalidValue;
         hipLaunchKernelGGL(k_fold_c, dim3(grid.x, (unsigned)fold_segs), dim3(256), 0, s, pairs, bp, npairs,
-                           rows, mask, coef, fpart);
+                           rows, per_row, mask, coef, fpart);
     }
-    hipLaunchKernelGGL(k_stat<kStatPlain>, grid, dim3(256), 0, s, pairs, bp, npairs, rows, st, partial, nslot,
+    hipLaunchKernelGGL(k_stat<kStatPlain>, grid, dim3(256), 0, s, pairs, bp, npairs, rows, per_row, st, partial, nslot,
                        prow, d, gd, alternative, band, no_recheck, T_out, T_mode, Tw, cnt, flags, nflag, pv, fpart,
                        nullptr, nullptr);
     return hipGetLastError();
@@ -247,12 +265,13 @@ hipError_t launch_stat_lazy(bool refined, const PairDesc* pairs, const BlockPair
     if (rows <= 0) return hipSuccess;
     if (!rlist || !rcnt) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((rows + 255) / 256));
+    const double per_row = (double)npairs / (double)rows;
     if (refined)
-        hipLaunchKernelGGL(k_stat<kStatRefined>, grid, dim3(256), 0, s, pairs, bp, npairs, rows, st, partial,
+        hipLaunchKernelGGL(k_stat<kStatRefined>, grid, dim3(256), 0, s, pairs, bp, npairs, rows, per_row, st, partial,
                            nslot, prow, d, gd, alternative, band, no_recheck, T_out, T_mode, Tw, cnt, flags, nflag,
                            nullptr, nullptr, rlist, rcnt);
     else
-        hipLaunchKernelGGL(k_stat<kStatLazyFirst>, grid, dim3(256), 0, s, pairs, bp, npairs, rows, st, partial,
+        hipLaunchKernelGGL(k_stat<kStatLazyFirst>, grid, dim3(256), 0, s, pairs, bp, npairs, rows, per_row, st, partial,
                            nslot, prow, d, gd, alternative, band, no_recheck, T_out, T_mode, Tw, cnt, flags, nflag,
                            nullptr, nullptr, rlist, rcnt);
     return hipGetLastError();
