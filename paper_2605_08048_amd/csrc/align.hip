@@ -116,9 +116,10 @@ template <typename Tin>
 __global__ __launch_bounds__(256) void k_colsum(const PairDesc* __restrict__ pairs,
                                                 int npairs, int d,
                                                 double* __restrict__ partial,
-                                                int32_t* __restrict__ chunk_bad) {
-    const SumChunk ch = chunk_of(pairs, npairs, blockIdx.x);
-    const PairDesc pd = pairs[ch.pair];
+                                                int32_t* __restrict__ chunk_bad, const PairTables tab) {
+    write_tables(tab);
+    PairDesc pd;
+    const SumChunk ch = chunk_of(tab, pairs, npairs, blockIdx.x, &pd);
     const Tin* base = (const Tin*)(ch.side ? pd.Y : pd.X);
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     if (blockIdx.y == 0) {  // the first column tile also tests whole rows (wave ty: rows ty, ty + 4, ...)
@@ -164,10 +165,11 @@ __global__ __launch_bounds__(256) void k_colsum(const PairDesc* __restrict__ pai
 template <typename Tin, int J>
 __global__ __launch_bounds__(512) void k_colsum_rows(const PairDesc* __restrict__ pairs, int npairs, int d,
                                                      double* __restrict__ partial,
-                                                     int32_t* __restrict__ chunk_bad) {
+                                                     int32_t* __restrict__ chunk_bad, const PairTables tab) {
     __shared__ double red[4][256 * J];
-    const SumChunk ch = chunk_of(pairs, npairs, blockIdx.x);
-    const PairDesc pd = pairs[ch.pair];
+    write_tables(tab);
+    PairDesc pd;
+    const SumChunk ch = chunk_of(tab, pairs, npairs, blockIdx.x, &pd);
     const Tin* base = (const Tin*)(ch.side ? pd.Y : pd.X);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     double acc[J][4];
@@ -222,11 +224,11 @@ __global__ __launch_bounds__(512) void k_colsum_rows(const PairDesc* __restrict_
 }
 
 hipError_t launch_colsum(int input_dtype, const PairDesc* pairs, int npairs, int nchunks, int d, int d_pad,
-                         double* partial, int32_t* chunk_bad, hipStream_t s) {
+                         double* partial, int32_t* chunk_bad, hipStream_t s, const PairTables& tab) {
     if (nchunks <= 0) return hipSuccess;
     const bool f64 = input_dtype == HBT_IN_F64;
     auto go = [&](auto kern, dim3 grid, int threads) {
-        hipLaunchKernelGGL(kern, grid, dim3(threads), 0, s, pairs, npairs, d, partial, chunk_bad);
+        hipLaunchKernelGGL(kern, grid, dim3(threads), 0, s, pairs, npairs, d, partial, chunk_bad, tab);
     };
     const dim3 tiles(nchunks, (d + 63) / 64), chunks(nchunks);
     switch ((d_pad + 255) / 256) {
@@ -248,7 +250,8 @@ template <int J>
 __device__ __forceinline__ void colsum4_chunk(const SumChunk& ch, const PairDesc& pd, int d,
                                               double* __restrict__ partial_row,
                                               double (*red)[256 * J], int32_t* bad_out) {
-    const float* base = (const float*)(ch.side ? pd.Y : pd.X);
+    const float *xb = (const float*)pd.X, *yb = (const float*)pd.Y;
+    const float* base = ch.side ? yb : xb;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     double acc[J][4];
 #pragma unroll
@@ -309,10 +312,12 @@ template <int J>
 __global__ __launch_bounds__(256) void k_colsum4(const PairDesc* __restrict__ pairs,
                                                  int npairs, int d,
                                                  double* __restrict__ partial,
-                                                 int32_t* __restrict__ chunk_bad) {
+                                                 int32_t* __restrict__ chunk_bad, const PairTables tab) {
     __shared__ double red[3][256 * J];
-    const SumChunk ch = chunk_of(pairs, npairs, blockIdx.x);
-    colsum4_chunk<J>(ch, pairs[ch.pair], d, partial + (int64_t)blockIdx.x * d, red, chunk_bad + blockIdx.x);
+    write_tables(tab);
+    PairDesc pd;
+    const SumChunk ch = chunk_of(tab, pairs, npairs, blockIdx.x, &pd);
+    colsum4_chunk<J>(ch, pd, d, partial + (int64_t)blockIdx.x * d, red, chunk_bad + blockIdx.x);
 }
 
 bool vector_rows_ok(int input_dtype, int d, int d_pad) {
@@ -320,15 +325,16 @@ bool vector_rows_ok(int input_dtype, int d, int d_pad) {
 }
 
 hipError_t launch_colsum_vec(const PairDesc* pairs, int npairs, int nchunks, int d,
-                             int d_pad, double* partial, int32_t* chunk_bad, hipStream_t s) {
+                             int d_pad, double* partial, int32_t* chunk_bad, hipStream_t s,
+                             const PairTables& tab) {
     if (nchunks <= 0) return hipSuccess;
     const int J = (d_pad + 255) / 256;
     const dim3 g(nchunks), b(256);
     switch (J) {
-        case 1: hipLaunchKernelGGL(k_colsum4<1>, g, b, 0, s, pairs, npairs, d, partial, chunk_bad); break;
-        case 2: hipLaunchKernelGGL(k_colsum4<2>, g, b, 0, s, pairs, npairs, d, partial, chunk_bad); break;
-        case 3: hipLaunchKernelGGL(k_colsum4<3>, g, b, 0, s, pairs, npairs, d, partial, chunk_bad); break;
-        case 4: hipLaunchKernelGGL(k_colsum4<4>, g, b, 0, s, pairs, npairs, d, partial, chunk_bad); break;
+        case 1: hipLaunchKernelGGL(k_colsum4<1>, g, b, 0, s, pairs, npairs, d, partial, chunk_bad, tab); break;
+        case 2: hipLaunchKernelGGL(k_colsum4<2>, g, b, 0, s, pairs, npairs, d, partial, chunk_bad, tab); break;
+        case 3: hipLaunchKernelGGL(k_colsum4<3>, g, b, 0, s, pairs, npairs, d, partial, chunk_bad, tab); break;
+        case 4: hipLaunchKernelGGL(k_colsum4<4>, g, b, 0, s, pairs, npairs, d, partial, chunk_bad, tab); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -1030,11 +1036,13 @@ __global__ __launch_bounds__(256) void k_colsum_store4(const PairDesc* __restric
                                                        double* __restrict__ partial, void* zstore,
                                                        int64_t zplane_elems,
                                                        float* __restrict__ z32,
-                                                       int32_t* __restrict__ chunk_bad, int c0) {
+                                                       int32_t* __restrict__ chunk_bad, int c0,
+                                                       const PairTables tab) {
     __shared__ double red[4][256 * J];
+    write_tables(tab);
     const int c = blockIdx.x + c0;
-    const SumChunk ch = chunk_of(pairs, npairs, c);
-    const PairDesc pd = pairs[ch.pair];
+    PairDesc pd;
+    const SumChunk ch = chunk_of(tab, pairs, npairs, c, &pd);
     double* prow = partial + (int64_t)c * d;
     if (!ch.side) {  // work-group-uniform
         colsum4_chunk<J>(ch, pd, d, prow, red, chunk_bad + c);
@@ -1101,13 +1109,13 @@ __global__ __launch_bounds__(256) void k_colsum_store4(const PairDesc* __restric
 hipError_t launch_colsum_store_vec(int precision, const PairDesc* pairs, int npairs, int nchunks,
                                    int d, int d_pad, double* partial, void* zstore,
                                    int64_t zplane_elems, float* z32, int32_t* chunk_bad,
-                                   hipStream_t s, int c0) {
+                                   hipStream_t s, int c0, const PairTables& tab) {
     if (nchunks <= 0) return hipSuccess;
     const int J = (d_pad + 255) / 256;
     const dim3 g(nchunks), b(256);
 #define HBT_C4(PR, JJ)                                                                         \
     hipLaunchKernelGGL((k_colsum_store4<PR, JJ>), g, b, 0, s, pairs, npairs, d, d_pad, partial, \
-                       zstore, zplane_elems, z32, chunk_bad, c0)
+                       zstore, zplane_elems, z32, chunk_bad, c0, tab)
 #define HBT_C4J(PR)                            \
     switch (J) {                               \
         case 1: HBT_C4(PR, 1); break;          \

@@ -300,7 +300,8 @@ Workspace carve(const Plan& P, void* ws) {
         w.rplan = c.take<int64_t>(recheck_plan_words(np));
         w.nflag = c.take<uint32_t>((size_t)(np + 1) / 2 * 2);
         w.sstat = c.take<int32_t>((size_t)(np + 1) / 2 * 2);
-        w.ticket = c.take<uint32_t>((size_t)(np + 1) / 2 * 2);
+        // one pair leaves the second word of its split status free
+        w.ticket = P.batched ? c.take<uint32_t>((size_t)(np + 1) / 2 * 2) : (uint32_t*)(w.sstat + 1);
         if (P.route2) {
             w.sig = c.take<float>((size_t)std::max<int64_t>(P.block_rows, 1) * P.d_pad);
             w.z32 = P.precision == HBT_F32 ? nullptr : c.take<float>((size_t)P.zrows * P.d_pad);
@@ -680,24 +681,33 @@ hipError_t reflect(const Plan& P, const Workspace& w, float* z32, hipStream_t s)
                           P.d_pad, w.coef, w.zstore, P.zrows * P.d_pad, z32, s);
 }
 
+// `bytes` of tables for `dst` that begin with the pair, and the counters to clear.
+PairTables pair_tables(void* dst, const void* tables, size_t bytes, void* clear, size_t clear_bytes) {
+    PairTables t;
+    t.dst = (uint32_t*)dst;
+    t.words = (int32_t)(bytes / 4);
+    t.clear = (uint32_t*)clear;
+    t.clear_words = (int32_t)(clear_bytes / 4);
+    memcpy(&t.pair, tables, sizeof t.pair);
+    memcpy(t.b, tables, bytes);
+    return t;
+}
+
+// Column sums (and the Y storage), then the directions and T_obs.  tab: the
+// tables of a call of one pair, where the column sums are to write them.
 hbt_status enqueue_prologue(const Plan& P, const Workspace& w, int align, int gd, hbt_result* res,
-                            hipStream_t s, bool upload_pairs = true) {
-    if (upload_pairs) {
-        StageTimer t(HBT_STAGE_OTHER, s);
-        HIP_TRY(upload(w.pairs, P.pairs.data(), P.pairs.size() * sizeof(PairDesc), s, w.ticket,
-                       (P.pairs.size() + 1) / 2 * 8));
-    }
+                            hipStream_t s, const PairTables& tab = {}) {
     StageTimer t(HBT_STAGE_ALIGN, s);
     if (vector_rows(P) && P.need_store)
         HIP_TRY(launch_colsum_store_vec(P.precision, w.pairs, P.npairs, (int)P.nchunks, P.d,
                                         P.d_pad, w.partial_sum, w.zstore, P.zrows * P.d_pad, w.z32,
-                                        w.chunk_bad, s));
+                                        w.chunk_bad, s, 0, tab));
     else if (vector_rows(P))
         HIP_TRY(launch_colsum_vec(w.pairs, P.npairs, (int)P.nchunks, P.d, P.d_pad, w.partial_sum,
-                                  w.chunk_bad, s));
+                                  w.chunk_bad, s, tab));
     else
         HIP_TRY(launch_colsum(P.input_dtype, w.pairs, P.npairs, (int)P.nchunks, P.d, P.d_pad,
-                              w.partial_sum, w.chunk_bad, s));
+                              w.partial_sum, w.chunk_bad, s, tab));
     HIP_TRY(launch_finalize(w.pairs, P.npairs, w.partial_sum, w.chunk_bad, P.d, P.d_pad, align, gd, w.sxy, w.st,
                             w.v, w.t64, w.t32, w.cnt, res, w.ticket, s));
     return HBT_OK;
@@ -1110,7 +1120,8 @@ hbt_status hbt_align(int32_t input_dtype, const void* X, int64_t n, const void* 
         return fail(HBT_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, ws_bytes);
     hipStream_t s = (hipStream_t)stream;
     Workspace w = carve(P, ws);
-    st = enqueue_prologue(P, w, align, gd, result, s);
+    const PairTables tab = pair_tables(w.pairs, P.pairs.data(), sizeof(PairDesc), w.ticket, 8);
+    st = enqueue_prologue(P, w, align, gd, result, s, tab);
     if (st) return st;
     HIP_TRY(launch_reflect_out(input_dtype, w.pairs, w.st, w.v, (int)n, (int)d, X_out, v_out, s));
     return HBT_OK;
@@ -1181,14 +1192,23 @@ hbt_status hbt_perm_test(const void* X, const void* Y, const hbt_perm_params* pr
         return launch_split_masks(w.bp, 1, nb, P.min_np, P.max_np, prm->seed, w.mask, w.sstat,
                                   P.tune.split_cap, q);
     };
+    // The first block's splits depend only on the seed and the sizes: they are
+    // drawn on a second stream beside the alignment and joined before the
+    // group sums (as in the batched call); later blocks follow in order.  Few
+    // splits of a small pair stay on the caller's stream: they take less time
+    // than the fork and join.
+    const int64_t nb0 = std::min<int64_t>(B0, prm->B);
+    const bool beside = nb0 * pd.Np > kForkKeys;
+    PairTables tab = {};
     {
         // The plan tables and block 0's tables sit next to each other at the
-        // start of the workspace (pairs, bp, tiles, groups, Btot): one image,
-        // one upload.  The recheck counter (with a ticket behind it), the split
-        // status and the alignment's ticket are adjacent too: cleared by the
-        // same launch.
+        // start of the workspace (pairs, bp, tiles, groups, Btot): one image.
+        // The recheck counter (with a ticket behind it), the split status and
+        // the alignment's ticket are adjacent too and are cleared with it.  The
+        // column sums write and clear them where nothing runs before or beside
+        // them (n = 100, m = 80, d = 64, B = 1000: 70 us a call with a
+        // kernel of its own for that, 65 so).
         StageTimer t_(HBT_STAGE_OTHER, s);
-        const int64_t nb0 = std::min<int64_t>(B0, prm->B);
         const BlockPair bq = block_pair(0, 0, prm->perm_offset, nb0, 0, pd);
         const int wdt = block_width(nb0);
         const GemmGroup grp{0, (int32_t)((nb0 + wdt - 1) / wdt), 0};
@@ -1201,24 +1221,24 @@ hbt_status hbt_perm_test(const void* X, const void* Y, const hbt_perm_params* pr
         put(w.tiles, P.tiles.data(), P.tiles.size() * sizeof(GemmTile));
         put(w.groups, &grp, sizeof grp);
         put(w.Btot, P.Btot.data(), sizeof(int64_t));
-        HIP_TRY(upload(w.pairs, img.data(), img.size(), s, w.nflag,
-                       (size_t)((const char*)(w.ticket + 2) - (const char*)w.nflag)));
+        const size_t clear = (size_t)((const char*)(w.ticket + 1) - (const char*)w.nflag);
+        if (!beside && img.size() <= sizeof tab.b)
+            tab = pair_tables(w.pairs, img.data(), img.size(), w.nflag, clear);
+        else
+            HIP_TRY(upload(w.pairs, img.data(), img.size(), s, w.nflag, clear));
     }
-    // The first block's splits depend only on the seed and the sizes: they are
-    // drawn on a second stream beside the alignment and joined before the
-    // group sums (as in the batched call); later blocks follow in order.  Few
-    // splits of a small pair go ahead of the alignment on the caller's stream:
-    // they take less time than the fork and join.
-    const int64_t nb0 = std::min<int64_t>(B0, prm->B);
-    const bool beside = nb0 * pd.Np > kForkKeys;
     Fork fork(s);
-    if (beside) HIP_TRY(fork.begin());
-    {
-        StageTimer t_(HBT_STAGE_SPLIT, beside ? fork.side : s);
-        HIP_TRY(block_splits(0, nb0, beside ? fork.side : s));
+    if (beside) {
+        HIP_TRY(fork.begin());
+        StageTimer t_(HBT_STAGE_SPLIT, fork.side);
+        HIP_TRY(block_splits(0, nb0, fork.side));
     }
-    st = enqueue_prologue(P, w, prm->align, prm->gd, result, s, false);
+    st = enqueue_prologue(P, w, prm->align, prm->gd, result, s, tab);
     if (st) return st;
+    if (!beside) {
+        StageTimer t_(HBT_STAGE_SPLIT, s);
+        HIP_TRY(block_splits(0, nb0, s));
+    }
     const float* z32 = P.precision == HBT_F32 ? (const float*)w.zstore : w.z32;
     {
         StageTimer t_(HBT_STAGE_ALIGN, s);
@@ -1517,7 +1537,7 @@ hbt_status hbt_perm_test_batched(int64_t npairs, const void* Z_all, const int64_
         HIP_TRY(launch_split_masks(w.bp, np, P.block_rows, P.min_np, P.max_np, common->seed, w.mask, w.sstat,
                                    P.tune.split_cap, qs, split_big(P, w)));
     }
-    st = enqueue_prologue(P, w, common->align, common->gd, results, s, false);
+    st = enqueue_prologue(P, w, common->align, common->gd, results, s);
     if (st) return st;
     {
         StageTimer t_(HBT_STAGE_ALIGN, s);

@@ -91,6 +91,17 @@ __device__ __forceinline__ const uint32_t* mask_row(const uint32_t* mask, const 
 }
 #endif
 
+// The tables of a call of one pair as an argument of its first kernel, which
+// takes the pair from them and writes them to the workspace for the kernels
+// that follow (write_tables), instead of a kernel that only does that.
+struct PairTables {
+    uint32_t* dst;        // where they go; nullptr: the tables are in the workspace already
+    uint32_t* clear;      // the call's counters
+    int32_t words, clear_words;
+    PairDesc pair;
+    uint32_t b[744];      // the tables
+};
+
 // A run of rows of one cloud for the column sums.
 struct SumChunk {
     int32_t pair, side;  // side 0 = X, 1 = Y
@@ -373,10 +384,9 @@ __device__ __forceinline__ int pair_of_row(const BlockPair* bp, int npairs, int6
 // 32-row groups of the Z storage from the one holding row n to the padded
 // end Np: Y chunk k holds pooled rows [max(n, 32 j), min(n + m, 32 (j + 1)))
 // (none for the groups of padding only), j = n / 32 + k.
-__device__ __forceinline__ SumChunk chunk_of(const PairDesc* pairs, int npairs, int c) {
-    const int p = upper_index(npairs, c, [&](int k) { return pairs[k].cx0; });
-    const int cx0 = pairs[p].cx0, cx1 = pairs[p].cx1;
-    const int n = pairs[p].n, N = n + pairs[p].m;
+__device__ __forceinline__ SumChunk chunk_of(const PairDesc& pd, int p, int c) {
+    const int cx0 = pd.cx0, cx1 = pd.cx1;
+    const int n = pd.n, N = n + pd.m;
     SumChunk ch;
     ch.pair = p;
     ch.side = c < cx1 ? 0 : 1;
@@ -389,6 +399,30 @@ __device__ __forceinline__ SumChunk chunk_of(const PairDesc* pairs, int npairs, 
         ch.r1 = (kSumChunkY * (j + 1) < N ? kSumChunkY * (j + 1) : N) - n;
     }
     return ch;
+}
+
+__device__ __forceinline__ void write_tables(const PairTables& t) {
+    if (!t.dst || blockIdx.x != 0 || blockIdx.y != 0) return;
+    for (int i = threadIdx.x; i < t.words; i += blockDim.x) t.dst[i] = t.b[i];
+    for (int i = threadIdx.x; i < t.clear_words; i += blockDim.x) t.clear[i] = 0;
+}
+// The pair and the rows of column-sum chunk c.
+__device__ __forceinline__ SumChunk chunk_of(const PairTables& t, const PairDesc* pairs, int npairs, int c,
+                                             PairDesc* pd) {
+    int p = 0;
+    if (t.dst) {
+        *pd = t.pair;
+    } else {
+        p = upper_index(npairs, c, [&](int k) { return pairs[k].cx0; });
+        // (the kernel arguments' address space, so that either read is a scalar load)
+        typedef const __attribute__((address_space(4))) uint32_t* words_t;
+        const words_t src = (words_t)(uintptr_t)(pairs + p);
+        uint32_t w[sizeof(PairDesc) / 4];
+#pragma unroll
+        for (int i = 0; i < (int)(sizeof(PairDesc) / 4); ++i) w[i] = src[i];
+        __builtin_memcpy(pd, w, sizeof(PairDesc));
+    }
+    return chunk_of(*pd, p, c);
 }
 
 #endif  // __HIPCC__

@@ -60,7 +60,8 @@ hipError_t launch_build_tables(const TableArgs& A, hipStream_t s);
 // chunk_bad[chunk] = 1 when a row of the chunk is not a unit vector
 // (| |x| - 1 | > 1e-4 or NaN), else 0; every launcher below writes it.
 hipError_t launch_colsum(int input_dtype, const PairDesc* pairs, int npairs,
-                         int nchunks, int d, int d_pad, double* partial, int32_t* chunk_bad, hipStream_t s);
+                         int nchunks, int d, int d_pad, double* partial, int32_t* chunk_bad, hipStream_t s,
+                         const PairTables& tab = {});  // one pair's tables still to be written
 // Per pair: sums, r, mean directions, v, v.v, identity, T_obs, tau, the pooled
 // total t (FP64 and FP32), the hbt_result header.
 hipError_t launch_finalize(const PairDesc* pairs, int npairs, const double* partial,
@@ -80,14 +81,16 @@ hipError_t launch_fold_coef(const PairDesc* pairs, int npairs, const PairState* 
 // caller also checks that every X, Y is 16-byte aligned).
 bool vector_rows_ok(int input_dtype, int d, int d_pad);
 hipError_t launch_colsum_vec(const PairDesc* pairs, int npairs, int nchunks, int d,
-                             int d_pad, double* partial, int32_t* chunk_bad, hipStream_t s);
+                             int d_pad, double* partial, int32_t* chunk_bad, hipStream_t s,
+                             const PairTables& tab = {});
 // Column sums plus the storage of the 32-row groups that hold no X rows (the
 // 16-byte path of the group-sum calls); launch_reflect_vec then takes the
 // x_octets(n) octets of each pair (total_octets = their sum over pairs).
 hipError_t launch_colsum_store_vec(int precision, const PairDesc* pairs, int npairs, int nchunks,
                                    int d, int d_pad, double* partial, void* zstore,
                                    int64_t zplane_elems, float* z32, int32_t* chunk_bad,
-                                   hipStream_t s, int c0 = 0);  // chunks [c0, c0 + nchunks)
+                                   hipStream_t s, int c0 = 0,  // chunks [c0, c0 + nchunks)
+                                   const PairTables& tab = {});
 hipError_t launch_reflect_vec(int precision, const PairDesc* pairs, int npairs,
                               int64_t total_octets, const PairState* st, const double* v, int d,
                               int d_pad, double* coef, void* zstore, int64_t zplane_elems,
