@@ -909,7 +909,6 @@ hbt_status batched_epilogue(const Plan& P, const Workspace& w, const hbt_perm_pa
     const int np = P.npairs;
     const int no_recheck = common->flags & HBT_FLAG_NO_RECHECK;
     const PairEnd end{w.bp, w.st, w.sstat, w.tw, w.Btot, w.cnt, results};
-    bool ended = false;
     if (P.lazy) {
         // first pass: decide from the hi-plane sums what they can decide,
         // list the rest; second pass: split-BF16 sums of the listed splits
@@ -935,10 +934,9 @@ hbt_status batched_epilogue(const Plan& P, const Workspace& w, const hbt_perm_pa
         StageTimer t_(HBT_STAGE_RECHECK, s);
         HIP_TRY(launch_recheck(P.input_dtype, w.pairs, w.bp, np, w.st, w.v, w.t64, w.coef, w.mask, w.flags,
                                w.nflag, w.rplan, P.block_rows, P.max_np, w.rseg, recheck_slot_budget(np, P.d_pad),
-                               P.d, common->gd, common->alternative, w.cnt, w.tw, s, &end,
-                               np == 1 ? w.nflag + 1 : nullptr, &ended));
+                               P.d, common->gd, common->alternative, w.cnt, w.tw, s, &end, w.nflag + 1));
     }
-    if (!ended) {
+    if (no_recheck || np > 1) {
         StageTimer t_(HBT_STAGE_OTHER, s);
         HIP_TRY(launch_pair_end(np, end, s));
     }
@@ -1281,7 +1279,6 @@ hbt_status hbt_perm_test(const void* X, const void* Y, const hbt_perm_params* pr
                                     w.mask, w.zt, w.partial2, P.block_rows, s));
         }
         const PairEnd end{w.bp, w.st, w.sstat, w.tw, w.Btot, w.cnt, b0 + nb >= prm->B ? result : nullptr};
-        bool ended = false;
         void* T_blk = T_out ? (char*)T_out + b0 * t_size : nullptr;
         if (P.lazy) {
             // decide what the hi plane can, refine the rest with both planes
@@ -1307,9 +1304,9 @@ hbt_status hbt_perm_test(const void* X, const void* Y, const hbt_perm_params* pr
             StageTimer t_(HBT_STAGE_RECHECK, s);
             HIP_TRY(launch_recheck(P.input_dtype, w.pairs, w.bp, 1, w.st, w.v, w.t64, w.coef, w.mask,
                                    w.flags, w.nflag, w.rplan, nb, P.max_np, w.rseg, recheck_slot_budget(1, P.d_pad),
-                                   P.d, prm->gd, prm->alternative, w.cnt, w.tw, s, &end, w.nflag + 1, &ended));
+                                   P.d, prm->gd, prm->alternative, w.cnt, w.tw, s, &end, w.nflag + 1));
         }
-        if (!ended) {
+        if (no_recheck) {
             StageTimer t_(HBT_STAGE_OTHER, s);
             HIP_TRY(launch_pair_end(1, end, s));
         }

@@ -255,15 +255,14 @@ struct PairEnd {
     PairCount* cnt;
     hbt_result* res;
 };
-// One pair (npairs = 1): no plan is made (its one flag count gives the work),
-// and where a second kernel finishes segmented flags, its last work-group to end
-// also ends the pair (`end`; ticket: a zeroed word); *ended says whether it did.
+// One pair (npairs = 1): no plan is made (its one flag count gives the work), and
+// the last work-group to end also ends the pair (`end`; ticket: a zeroed word).
 hipError_t launch_recheck(int input_dtype, const PairDesc* pairs, const BlockPair* bp, int npairs,
                           const PairState* st, const double* v, const double* t64, const double* coef,
                           const uint32_t* mask, const uint32_t* flags, const uint32_t* nflag, int64_t* plan,
                           int64_t max_flags, int max_np, double* rseg, int64_t slots, int d, int gd,
                           int alternative, PairCount* cnt, double* Tw, hipStream_t s,
-                          const PairEnd* end = nullptr, uint32_t* ticket = nullptr, bool* ended = nullptr);
+                          const PairEnd* end, uint32_t* ticket);
 // Ends every pair.
 hipError_t launch_pair_end(int npairs, const PairEnd& end, hipStream_t s);
 // --- permutation-budget allocator ---------------------------------------

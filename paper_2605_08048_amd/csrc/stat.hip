@@ -210,7 +210,6 @@ __global__ __launch_bounds__(256) void k_stat(const PairDesc* __restrict__ pairs
                 ((float*)T_out)[row] = (float)T;
             }
         }
-        Tw[row] = T;
         const bool two = alternative == HBT_ALT_TWO_SIDED;
         const double val = two ? fabs(T) : T;
         const double thr = (two ? fabs(q.t_obs) : q.t_obs) - q.tau;
@@ -223,6 +222,7 @@ __global__ __launch_bounds__(256) void k_stat(const PairDesc* __restrict__ pairs
             flag = !no_recheck && !nan && fabs(val - thr) <= eps;
             if (!flag) exceed = nan || val >= thr;
         }
+        Tw[row] = flag ? 0.0 : T;  // 0: the count of a flag's segments that k_recheck_one has added
     }
     if (MODE == kStatLazyFirst)
         list_append(refine, one_pair, p0, p, row, bp, rlist, rcnt);
@@ -547,25 +547,10 @@ __device__ void recheck_item(const RecheckArgs& A, int p, int64_t j, int sg0, in
     }
 }
 
-// Whether the flags of a call's only pair are segmented items (the plan's rule).
-__device__ __forceinline__ bool one_pair_segmented(int64_t F, int G, int64_t slots) {
-    return G > 1 && F * G <= slots;
-}
-
 template <typename Tin>
 __global__ __launch_bounds__(kRecheckThreads) void k_recheck(RecheckArgs A) {
     __shared__ double part[kRecheckWaves][kRecheckPass];  // per-wave sums of a segment
     __shared__ double red[kRecheckWaves];
-    if (!A.plan) {  // one pair
-        const int64_t F = A.nflag[0];
-        const int G = pair_segs(A.pairs[0]);
-        const bool seg = one_pair_segmented(F, G, A.slots);
-        for (int64_t it = blockIdx.x; it < (seg ? F * G : F); it += gridDim.x) {
-            const int sg = seg ? (int)(it % G) : 0;
-            recheck_item<Tin>(A, 0, seg ? it / G : it, sg, seg ? sg + 1 : G, !seg, part, red);
-        }
-        return;
-    }
     const int np1 = A.npairs + 1;
     const int64_t* wpre = A.plan;
     const int64_t* spre = A.plan + np1;
@@ -685,22 +670,41 @@ __global__ __launch_bounds__(kRecheckThreads) void k_recheck_finish(RecheckArgs 
     }
 }
 
-// One pair: its segmented flags, then the end of the pair by the last of the
-// work-groups that had any (by the first when there were none): they count
-// themselves on `ticket`, each after its own results are visible to the whole
-// device.  Nobody waits for anybody.
-__global__ __launch_bounds__(kRecheckThreads) void k_recheck_finish_end(RecheckArgs A, PairEnd E, uint32_t* ticket) {
+// One pair: its flags and the end of the pair in one kernel.  Segmented items
+// (the plan's rule) count themselves on their flag's word of Tw, zeroed with the
+// flag; the last of a flag's adds its segments.  The work-groups that had items
+// count themselves on `ticket`, and the last of them (the first where there are
+// none) ends the pair.  Each counts after its own results are visible to the
+// whole device; nobody waits for anybody.  Bound by its launch where there are
+// few flags: n = 100, m = 80, d = 64, B = 1000, 65 to 61 us a
+// call against two kernels; n = 777, m = 1333, d = 301, B = 5003, 150 to 140.
+template <typename Tin>
+__global__ __launch_bounds__(kRecheckThreads) void k_recheck_one(RecheckArgs A, PairEnd E, uint32_t* ticket) {
     static_assert(kRecheckThreads == 256, "end_pair takes 256 threads");
+    __shared__ double part[kRecheckWaves][kRecheckPass];  // per-wave sums of a segment
     __shared__ double red[kRecheckWaves];
     __shared__ double r1[256], r2[256];
     __shared__ uint32_t before;
     const int64_t F = A.nflag[0];
-    const int64_t NF = one_pair_segmented(F, pair_segs(A.pairs[0]), A.slots) ? F : 0;
-    const int64_t busy = NF < 1 ? 1 : NF < (int64_t)gridDim.x ? NF : (int64_t)gridDim.x;
+    const int G = pair_segs(A.pairs[0]);
+    const bool seg = G > 1 && F * G <= A.slots;
+    const int64_t items = seg ? F * G : F;
+    const int64_t busy = items < 1 ? 1 : items < (int64_t)gridDim.x ? items : (int64_t)gridDim.x;
     if (blockIdx.x >= busy) return;
-    for (int64_t j = blockIdx.x; j < NF; j += gridDim.x) finish_flag(A, 0, j, 0, red);
+    for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
+        const int64_t j = seg ? it / G : it;
+        const int sg = seg ? (int)(it % G) : 0;
+        recheck_item<Tin>(A, 0, j, sg, seg ? sg + 1 : G, !seg, part, red);
+        if (!seg) continue;
+        __syncthreads();  // every thread's sums
+        if (threadIdx.x == 0)
+            before = (uint32_t)__hip_atomic_fetch_add((unsigned long long*)&A.Tw[A.flags[A.bp[0].mrow0 + j]], 1ull,
+                                                      __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (before == (uint32_t)(G - 1)) finish_flag(A, 0, j, 0, red);
+    }
+    __syncthreads();  // thread 0 decided the last flag, whose T_b the others read
     if (busy > 1) {
-        __syncthreads();  // thread 0 decided the last flag
         if (threadIdx.x == 0)
             before = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
@@ -723,39 +727,35 @@ hipError_t launch_recheck(int input_dtype, const PairDesc* pairs, const BlockPai
                           const uint32_t* mask, const uint32_t* flags, const uint32_t* nflag, int64_t* plan,
                           int64_t max_flags, int max_np, double* rseg, int64_t slots, int d, int gd,
                           int alternative, PairCount* cnt, double* Tw, hipStream_t s, const PairEnd* end,
-                          uint32_t* ticket, bool* ended) {
+                          uint32_t* ticket) {
     if (max_flags <= 0) return hipSuccess;
-    if (!plan || npairs < 1) return hipErrorInvalidValue;
-    if (ended) *ended = false;
+    if (!plan || npairs < 1 || !end || !ticket) return hipErrorInvalidValue;
     const int d_pad = (d + kDPad - 1) / kDPad * kDPad;
     if (!rseg) slots = 0;
-    const bool one = npairs == 1;
-    if (!one)
-        hipLaunchKernelGGL(k_recheck_plan, dim3(1), dim3(kPlanThreads), 0, s, pairs, npairs, nflag, slots, plan);
-    const RecheckArgs A{pairs, bp, npairs, st, v, t64, coef, mask, flags, nflag, one ? nullptr : plan, slots,
+    const RecheckArgs A{pairs, bp, npairs, st, v, t64, coef, mask, flags, nflag, npairs == 1 ? nullptr : plan, slots,
                         d, d_pad, gd, alternative, rseg, cnt, Tw};
+    const bool f64 = input_dtype == HBT_IN_F64;
     // the item count is known on the device only: a grid for the largest
     // count, whose work-groups without an item return at once (a single
     // pair, whose flags are few, gets the 512 that are resident together; the
     // work-groups loop over the items when there are more)
-    const int64_t gmax_grid = one ? 512 : 4096;
     const int64_t want = max_flags * (int64_t)recheck_segments(max_np);
-    const unsigned g = (unsigned)(want < gmax_grid ? want : gmax_grid);
-    if (input_dtype == HBT_IN_F64)
-        hipLaunchKernelGGL(k_recheck<double>, dim3(g), dim3(kRecheckThreads), 0, s, A);
-    else
-        hipLaunchKernelGGL(k_recheck<float>, dim3(g), dim3(kRecheckThreads), 0, s, A);
+    const dim3 block(kRecheckThreads);
+    if (npairs == 1) {
+        const dim3 g((unsigned)(want < 512 ? want : 512));
+        if (f64) hipLaunchKernelGGL(k_recheck_one<double>, g, block, 0, s, A, *end, ticket);
+        else hipLaunchKernelGGL(k_recheck_one<float>, g, block, 0, s, A, *end, ticket);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(k_recheck_plan, dim3(1), dim3(kPlanThreads), 0, s, pairs, npairs, nflag, slots, plan);
+    const dim3 g((unsigned)(want < 4096 ? want : 4096));
+    if (f64) hipLaunchKernelGGL(k_recheck<double>, g, block, 0, s, A);
+    else hipLaunchKernelGGL(k_recheck<float>, g, block, 0, s, A);
     if (rseg) {
         // a segmented flag takes at least two slots
         int64_t fw = slots / 2 < max_flags ? slots / 2 : max_flags;
-        if (fw > gmax_grid) fw = gmax_grid;
-        if (one && end && ticket) {
-            hipLaunchKernelGGL(k_recheck_finish_end, dim3((unsigned)(fw > 0 ? fw : 1)), dim3(kRecheckThreads), 0, s, A,
-                               *end, ticket);
-            if (ended) *ended = true;
-        } else if (fw > 0) {
-            hipLaunchKernelGGL(k_recheck_finish, dim3((unsigned)fw), dim3(kRecheckThreads), 0, s, A);
-        }
+        if (fw > 4096) fw = 4096;
+        if (fw > 0) hipLaunchKernelGGL(k_recheck_finish, dim3((unsigned)fw), block, 0, s, A);
     }
     return hipGetLastError();
 }
