@@ -4,6 +4,8 @@
 // fixed order, so results do not depend on timing.
 #include <string.h>
 
+#include <type_traits>
+
 #include "hbt_launch.h"
 
 namespace hbt {
@@ -108,6 +110,40 @@ __device__ __forceinline__ void load_cols(Tin (&x)[J][4], const Tin* row, int d,
         }
 }
 
+// Sum of x over the 64 lanes, returned to every lane: each adds the values of
+// lanes l ^ 32, l ^ 16, ..., l ^ 1 (as __shfl_xor would, through LDS), which
+// reach it by a swap of two registers' halves or rows, or by DPP.  (Bound by its
+// latency: the finalize step of d = 1024, three such sums in a chain, took 16.5 us
+// with five of them by __shfl_xor, 12.7 so.)
+__device__ __forceinline__ double wave_sum_f64(double x) {
+    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+    auto join = [](uint32_t lo, uint32_t hi) {
+        return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+    };
+    auto lo = [](double a) { return (uint32_t)(uint64_t)__double_as_longlong(a); };
+    auto hi = [](double a) { return (uint32_t)((uint64_t)__double_as_longlong(a) >> 32); };
+    {
+        const u32x2 l = __builtin_amdgcn_permlane32_swap(lo(x), lo(x), false, false);
+        const u32x2 h = __builtin_amdgcn_permlane32_swap(hi(x), hi(x), false, false);
+        x = join(l.x, h.x) + join(l.y, h.y);
+    }
+    {
+        const u32x2 l = __builtin_amdgcn_permlane16_swap(lo(x), lo(x), false, false);
+        const u32x2 h = __builtin_amdgcn_permlane16_swap(hi(x), hi(x), false, false);
+        x = join(l.x, h.x) + join(l.y, h.y);
+    }
+#define HBT_DPP(v, ctrl) (uint32_t) __builtin_amdgcn_mov_dpp((int)(v), ctrl, 0xF, 0xF, true)
+    x += join(HBT_DPP(lo(x), 0x128), HBT_DPP(hi(x), 0x128));  // row_ror:8
+    {  // l ^ 7 (row_half_mirror), then ^ 3 (quad_perm 3 2 1 0)
+        const uint32_t l = HBT_DPP(lo(x), 0x141), h = HBT_DPP(hi(x), 0x141);
+        x += join(HBT_DPP(l, 0x1B), HBT_DPP(h, 0x1B));
+    }
+    x += join(HBT_DPP(lo(x), 0x4E), HBT_DPP(hi(x), 0x4E));  // quad_perm 2 3 0 1
+    x += join(HBT_DPP(lo(x), 0xB1), HBT_DPP(hi(x), 0xB1));  // quad_perm 1 0 3 2
+#undef HBT_DPP
+    return x;
+}
+
 // ---------------------------------------------------------------------------
 // column sums, any rows of d > 1024: one work-group = 64 columns x one chunk of
 // rows, 4 row phases
@@ -130,7 +166,7 @@ __global__ __launch_bounds__(256) void k_colsum(const PairDesc* __restrict__ pai
                 const double a = (double)base[(int64_t)r * d + cc];
                 ss += a * a;
             }
-            for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+            ss = wave_sum_f64(ss);
             bad |= not_unit(ss);
         }
         bad = __syncthreads_or(bad);
@@ -199,9 +235,8 @@ __global__ __launch_bounds__(512) void k_colsum_rows(const PairDesc* __restrict_
                     ss[q] += a * a;
                 }
         }
-        for (int o = 32; o > 0; o >>= 1)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) ss[q] += __shfl_xor(ss[q], o, 64);
+        for (int q = 0; q < 4; ++q) ss[q] = wave_sum_f64(ss[q]);
 #pragma unroll
         for (int q = 0; q < 4; ++q) bad |= r + 8 * q < ch.r1 && not_unit(ss[q]);
     }
@@ -381,9 +416,7 @@ __global__ __launch_bounds__(256) void k_fold_coef(const PairDesc* __restrict__ 
 #pragma unroll
                     for (int e = 0; e < 4; ++e) w[q] += vc[j][e] * (double)x[q][j][e];
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-                for (int q = 0; q < kFoldRows; ++q) w[q] += __shfl_xor(w[q], o, 64);
+            for (int q = 0; q < kFoldRows; ++q) w[q] = wave_sum_f64(w[q]);
         }
         if (lane < k) {
             double wl = w[0];
@@ -436,7 +469,7 @@ __global__ __launch_bounds__(256) void k_finalize(
     const PairDesc* __restrict__ pairs, const double* __restrict__ partial, const int32_t* __restrict__ chunk_bad,
     int d, int d_pad, int align, int gd, double* sxy, PairState* st, double* v, double* t64, float* t32,
     PairCount* cnt, hbt_result* res, int p0, float* __restrict__ v32, uint32_t* ticket) {
-    __shared__ double red[16];
+    __shared__ double red[2][16];
     __shared__ double part[2][4][kFinCols];
     __shared__ uint32_t before;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -533,21 +566,33 @@ __global__ __launch_bounds__(256) void k_finalize(
             for (int c = c0 + nt; c < d_pad; c += nt) f(j, c, sx[c], sy[c], vp[c]);
         }
     };
-    auto total = [&](const double (&x)[kSlots]) {  // over the slots of all threads; every thread gets it
-        __syncthreads();  // the previous total's readers are done with red
+    // sums of x (and of y) over the slots of all threads; every thread gets them
+    auto total = [&](double (&x)[kSlots], double (&y)[kSlots], auto both, double& sx_, double& sy_) {
+        constexpr bool two = decltype(both)::value;
 #pragma unroll
         for (int j = 0; j < kSlots; ++j) {
             if (256 * j >= nt) continue;  // uniform: nt is a multiple of 256
-            double u = x[j];
-            for (int o = 32; o > 0; o >>= 1) u += __shfl_xor(u, o, 64);
-            if (lane == 0) red[wave + 4 * j] = u;
+            x[j] = wave_sum_f64(x[j]);
+            if (two) y[j] = wave_sum_f64(y[j]);
         }
+        __syncthreads();  // the previous total's readers are done with red
+        if (lane == 0)
+#pragma unroll
+            for (int j = 0; j < kSlots; ++j) {
+                if (256 * j >= nt) continue;
+                red[0][wave + 4 * j] = x[j];
+                if (two) red[1][wave + 4 * j] = y[j];
+            }
         __syncthreads();
-        double u = 0.0;
-        for (int q = 0; q < nt / 64; ++q) u += red[q];
-        return u;
+        sx_ = sy_ = 0.0;
+        for (int q = 0; q < nt / 64; ++q) {
+            sx_ += red[0][q];
+            if (two) sy_ += red[1][q];
+        }
     };
-    double a1[kSlots], a2[kSlots];
+    constexpr std::true_type two{};
+    constexpr std::false_type one{};
+    double a1[kSlots], a2[kSlots], ssx, ssy, vv, w, vt, none;
     auto clear = [&](double (&x)[kSlots]) {
 #pragma unroll
         for (int j = 0; j < kSlots; ++j) x[j] = 0.0;
@@ -559,23 +604,23 @@ __global__ __launch_bounds__(256) void k_finalize(
         a2[j] += y * y;
     });
     bad = __syncthreads_or(bad);
-    const double ssx = total(a1), ssy = total(a2);
+    total(a1, a2, two, ssx, ssy);
     const double nx = sqrt(ssx), ny = sqrt(ssy);
     const double r_x = nx / (double)pd.n, r_y = ny / (double)pd.m;
-    // mean directions and v = mu_x - mu_y (Eq. for u, before normalisation)
+    // mean directions and v = mu_x - mu_y (Eq. for u, before normalisation),
+    // v . v and v . s_x
     clear(a1);
+    clear(a2);
     columns([&](int j, int, double x, double y, double& vc) {
         const double mx = nx > 0.0 ? x / nx : 0.0;
         const double my = ny > 0.0 ? y / ny : 0.0;
         vc = mx - my;
         a1[j] += vc * vc;
+        a2[j] += vc * x;
     });
-    const double vv = total(a1);
+    total(a1, a2, two, vv, w);
     const int identity = (!align) || !(sqrt(vv) > 1e-12) || !(r_x > 0.0) || !(r_y > 0.0);
     // t = H s_x + s_y: the pooled total of Z = [X'; Y]
-    clear(a1);
-    columns([&](int j, int, double x, double, double& vc) { a1[j] += vc * x; });
-    const double w = total(a1);
     const double coef = identity ? 0.0 : 2.0 * w / vv;
     clear(a1);
     columns([&](int j, int c, double x, double y, double& vc) {
@@ -586,10 +631,11 @@ __global__ __launch_bounds__(256) void k_finalize(
         a1[j] += vc * tc;
         if (v32) v32[(int64_t)p * d_pad + c] = (float)vc;
     });
-    const double vt = total(a1);
+    total(a1, a2, one, vt, none);
+    // f(r_x) in lane 0 and f(r_y) in lane 1 of the first wave
+    const double f = wave == 0 ? log_g(lane & 1 ? r_y : r_x, (double)d, gd) : 0.0;
+    const double fx = __shfl(f, 0, 64), fy = __shfl(f, 1, 64);
     if (threadIdx.x == 0) {
-        const double dd = (double)d;
-        const double fx = log_g(r_x, dd, gd), fy = log_g(r_y, dd, gd);
         const double scale = fabs(fx) + fabs(fy);
         PairState q;
         q.r_x = r_x;
@@ -704,7 +750,7 @@ __global__ __launch_bounds__(256) void k_reflect(const PairDesc* __restrict__ pa
         if (!identity && i < pd.n) {
             const Tin* x = (const Tin*)pd.X + (int64_t)i * d;
             for (int c = lane; c < d; c += 64) w += vp[c] * (double)x[c];
-            for (int o = 32; o > 0; o >>= 1) w += __shfl_xor(w, o, 64);
+            w = wave_sum_f64(w);
         }
         if (lane == 0) {
             const double k = (!identity && i < pd.n) ? 2.0 * w / vv : 0.0;
@@ -832,12 +878,6 @@ hipError_t launch_reflect(int input_dtype, int precision, const PairDesc* pairs,
 // contiguous bytes of a row); the coefficients are FP64 wave reductions, and
 // every store instruction then writes one contiguous run of columns (1 KB per
 // plane for split BF16).
-__device__ __forceinline__ double wave_sum_f64(double x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    return x;
-}
-
 // Stores one storage octet of a pair: this lane's J x 4 columns of the 8
 // rows row_of(0..7) (pair-relative pooled rows), z_r = x_r - k_r vc in FP64,
 // in the precision's format.  soct is the octet's index in the whole storage.
