@@ -78,8 +78,8 @@ struct StageTimer {
     }
 };
 
-// Split keys (splits times padded pooled size) of a single pair's block above
-// which they are drawn on a second stream beside the alignment: the fork and
+// Split keys (splits times padded pooled size) of a single pair's block, or of a
+// batched call, above which they are drawn on a second stream beside the alignment: the fork and
 // join (two events, two queues) cost about 30 us, the keys 0.5 us a million (50 x
 // 60, B = 999: 117 us a call with the fork, 86 without; 777 x 1333, B = 5003: 221
 // and 187; 3000 x 2000, B = 20,000: 47 us of splits, hidden).
@@ -796,6 +796,45 @@ SplitBig split_big(const Plan& P, const Workspace& w) {
         }
     return b;
 }
+
+// The split stage of a batched call: beside its alignment, on a second stream
+// forked from the caller's after the tables and joined after the reflection; for
+// few keys (kForkKeys, as for a single pair) in one with them.  (Batches of 8 to
+// 256 pairs of at most 2^26 keys: 170 us a call with the fork, 155 without; 215
+// and 200; 200 and 194.)
+struct SplitStage {
+    const Plan& P;
+    const Workspace& w;
+    uint64_t seed;
+    hipStream_t s, qs;
+    Events ev;
+    hipEvent_t forked = nullptr;
+    SplitStage(const Plan& P_, const Workspace& w_, uint64_t seed_, hipStream_t s_)
+        : P(P_), w(w_), seed(seed_), s(s_), qs(s_) {}
+    hipError_t fork() {
+        int64_t keys = 0;
+        for (size_t p = 0; p < P.pairs.size(); ++p)
+            if (P.bp[p].owner == (int32_t)p) keys += (int64_t)P.bp[p].nb * P.pairs[p].Np;
+        if (keys <= kForkKeys) return hipSuccess;
+        hipError_t e = side_stream(&qs, 0);
+        return e != hipSuccess ? e : ev.record(s, &forked);
+    }
+    hipError_t draw() {
+        if (forked) {
+            const hipError_t e = hipStreamWaitEvent(qs, forked, 0);
+            if (e != hipSuccess) return e;
+        }
+        StageTimer t_(HBT_STAGE_SPLIT, qs);
+        return launch_split_masks(w.bp, P.npairs, P.block_rows, P.min_np, P.max_np, seed, w.mask, w.sstat,
+                                  P.tune.split_cap, qs, split_big(P, w));
+    }
+    hipError_t join() {
+        if (!forked) return hipSuccess;
+        hipEvent_t done;
+        const hipError_t e = ev.record(qs, &done);
+        return e != hipSuccess ? e : hipStreamWaitEvent(s, done, 0);
+    }
+};
 
 // The tables of a batched call (one pipeline chunk) from its compact
 // description: upload and one kernel, which also clears the counters.
@@ -1516,10 +1555,7 @@ hbt_status hbt_perm_test_batched(int64_t npairs, const void* Z_all, const int64_
     // split BF16: 8.03 ms per call at 8 or uncapped, where the alignment
     // then waits for wave slots; 7.25 ms at 6, the two stages 2.1 ms each;
     // 7.56 ms at 5, 7.63 ms at 4).
-    hipStream_t qs;
-    HIP_TRY(side_stream(&qs, 0));
-    Events ev;
-    hipEvent_t e0;
+    SplitStage splits(P, w, common->seed, s);
     {
         StageTimer t_(HBT_STAGE_OTHER, s);
         HIP_TRY(build_tables(P, w, (const char*)Z_all, row_offset, B, pair_index, nullptr, nullptr, common, s));
@@ -1527,21 +1563,15 @@ hbt_status hbt_perm_test_batched(int64_t npairs, const void* Z_all, const int64_
             HIP_TRY(upload(w.tiles, P.tiles.data(), P.tiles.size() * sizeof(GemmTile), s));
         if (P.route2) HIP_TRY(upload(w.ctiles, P.ctiles.data(), P.ctiles.size() * sizeof(CTile), s));
     }
-    HIP_TRY(ev.record(s, &e0));
-    HIP_TRY(hipStreamWaitEvent(qs, e0, 0));
-    {
-        StageTimer t_(HBT_STAGE_SPLIT, qs);
-        HIP_TRY(launch_split_masks(w.bp, np, P.block_rows, P.min_np, P.max_np, common->seed, w.mask, w.sstat,
-                                   P.tune.split_cap, qs, split_big(P, w)));
-    }
+    HIP_TRY(splits.fork());
+    HIP_TRY(splits.draw());
     st = enqueue_prologue(P, w, common->align, common->gd, results, s);
     if (st) return st;
     {
         StageTimer t_(HBT_STAGE_ALIGN, s);
         HIP_TRY(reflect(P, w, P.route2 ? w.z32 : nullptr, s));
     }
-    HIP_TRY(ev.record(qs, &e0));
-    HIP_TRY(hipStreamWaitEvent(s, e0, 0));
+    HIP_TRY(splits.join());
     {
         StageTimer t_(HBT_STAGE_GROUPSUM, s);
         HIP_TRY(launch_groupsum(P.precision, w.pairs, w.bp, w.tiles, (int)P.tiles.size(), w.groups,
@@ -1747,21 +1777,12 @@ hbt_status hbt_perm_test_clouds(int64_t nclouds, const void* Z_all, const int64_
     hipStream_t s = (hipStream_t)stream;
     Workspace w = carve(P, ws);
     const int np = P.npairs;
-    hipStream_t qs;
-    HIP_TRY(side_stream(&qs, 0));
-    Events ev;
-    hipEvent_t e0;
+    SplitStage splits(P, w, common->seed, s);
     {
         StageTimer t_(HBT_STAGE_OTHER, s);
         HIP_TRY(build_tables(P, w, (const char*)Z_all, cloud_offset, B, pair_index, pair_x, pair_y, common, s));
     }
-    HIP_TRY(ev.record(s, &e0));
-    HIP_TRY(hipStreamWaitEvent(qs, e0, 0));
-    {
-        StageTimer t_(HBT_STAGE_SPLIT, qs);
-        HIP_TRY(launch_split_masks(w.bp, np, P.block_rows, P.min_np, P.max_np, common->seed, w.mask, w.sstat,
-                                   P.tune.split_cap, qs, split_big(P, w)));
-    }
+    HIP_TRY(splits.fork());
     {
         // every cloud summed and stored once; per pair the directions, v, T_obs
         // and the reflected total; then the pairs' coefficients 2 (v . x_i) / (v . v)
@@ -1771,10 +1792,10 @@ hbt_status hbt_perm_test_clouds(int64_t nclouds, const void* Z_all, const int64_
                                         w.chunk_bad, s));
         HIP_TRY(launch_finalize(w.pairs, np, w.partial_sum, w.chunk_bad, P.d, P.d_pad, common->align, common->gd,
                                 w.sxy, w.st, w.v, w.t64, w.t32, w.cnt, results, w.ticket, s, 0, w.v32));
+        HIP_TRY(splits.draw());
         HIP_TRY(launch_fold_coef(w.pairs, np, w.st, w.v, P.d, P.d_pad, P.ncoef, w.coef, s));
     }
-    HIP_TRY(ev.record(qs, &e0));
-    HIP_TRY(hipStreamWaitEvent(s, e0, 0));
+    HIP_TRY(splits.join());
     {
         StageTimer t_(HBT_STAGE_GROUPSUM, s);
         HIP_TRY(launch_groupsum(P.precision, w.pairs, w.bp, w.tiles, 0, w.groups, P.ngw, (int)P.ntw, P.ng256,
