@@ -80,18 +80,6 @@ __device__ __forceinline__ float wave_total_f32(float x) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
-// Row loads through a buffer resource: the hardware returns 0 for every
-// byte offset at or past the resource's size without touching memory, so a
-// row that does not exist (size 0) or a column at or past d reads zero with
-// no branch and no select, and the loads of several rows are all in flight
-// before the first wait.  Word 3 is the gfx9 raw-buffer format (32-bit data).
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* p, int bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, bytes, 0x00020000);
-}
-
 // This lane's J x 4 columns 256 j + 64 e + lane of one row of d values (all
 // zero when the row is not valid).
 template <int J, typename Tin>

@@ -361,6 +361,63 @@ __device__ __forceinline__ int upper_index(int count, int64_t x, F key) {
     return lo;
 }
 
+// Row loads through a buffer resource: the hardware returns 0 for every
+// byte offset at or past the resource's size without touching memory, so a
+// row that does not exist (size 0) or a column at or past d reads zero with
+// no branch and no select, and the loads of several rows are all in flight
+// before the first wait.  Word 3 is the gfx9 raw-buffer format (32-bit data).
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* p, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, bytes, 0x00020000);
+}
+
+// Exclusive prefix sums of K values a thread over a work-group of NT threads, and
+// their totals: scans of the waves by DPP row shifts and row broadcasts, then of
+// their totals through LDS, with one pair of barriers for all K (the scans of one
+// work-group are a chain of latencies: 10 of them, one at a time through LDS
+// shuffles, made the tables of 64 pairs 8.7 us instead of 6.5, of 1024 pairs 20
+// instead of 16, and the recheck plan 8 to 10 instead of 4.6 to 6.5).
+template <int NT, int K>
+__device__ __forceinline__ void block_scan(int64_t (&x)[K], int64_t (*sh)[NT / 64], int64_t (&total)[K]) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    int64_t v[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = x[k];
+#define HBT_SCAN_STEP(ctrl, rows)                                                                                  \
+    _Pragma("unroll") for (int k = 0; k < K; ++k) {                                                                \
+        const uint32_t l = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v[k], ctrl, rows, 0xF, false);  \
+        const uint32_t g = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)((uint64_t)v[k] >> 32), ctrl,   \
+                                                                 rows, 0xF, false);                                \
+        v[k] += (int64_t)((uint64_t)g << 32 | l);                                                                  \
+    }
+    HBT_SCAN_STEP(0x111, 0xF)  // row_shr 1, 2, 4, 8
+    HBT_SCAN_STEP(0x112, 0xF)
+    HBT_SCAN_STEP(0x114, 0xF)
+    HBT_SCAN_STEP(0x118, 0xF)
+    HBT_SCAN_STEP(0x142, 0xA)  // row_bcast 15, 31
+    HBT_SCAN_STEP(0x143, 0xC)
+#undef HBT_SCAN_STEP
+    __syncthreads();  // the previous scan's readers are done with sh
+    if (lane == 63)
+#pragma unroll
+        for (int k = 0; k < K; ++k) sh[k][wave] = v[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        int64_t before = 0, all = 0;
+#pragma unroll
+        for (int q = 0; q < NT / 64; ++q) {
+            const int64_t t = sh[k][q];
+            before += q < wave ? t : 0;
+            all += t;
+        }
+        total[k] = all;
+        x[k] = before + v[k] - x[k];
+    }
+}
+
 // The entry of a table, of `count` runs of rows, that holds a row.  Pairs of one
 // batch mostly have equally many rows, so the entry at the row's place in
 // proportion (per_row = count / rows) is looked at first: one load instead of a

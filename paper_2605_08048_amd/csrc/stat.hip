@@ -354,28 +354,11 @@ __device__ void recheck_decide(const PairDesc& pd, const PairState& q, int p, in
 //       exclusive prefixes over the pairs, totals at index npairs.
 // A pair is segmented when it has more than one segment and its flag
 // segments, added to those of the pairs before it, fit `slots`.
-template <int NT>
-__device__ __forceinline__ int64_t block_scan(int64_t x, int64_t* sh, int64_t* total) {
-    const int t = threadIdx.x;
-    sh[t] = x;
-    __syncthreads();
-    for (int o = 1; o < NT; o <<= 1) {
-        const int64_t y = t >= o ? sh[t - o] : 0;
-        __syncthreads();
-        sh[t] += y;
-        __syncthreads();
-    }
-    const int64_t r = sh[t];
-    *total = sh[NT - 1];
-    __syncthreads();
-    return r;
-}
-
-constexpr int kPlanThreads = 1024;
+constexpr int kPlanThreads = 512;
 __global__ __launch_bounds__(kPlanThreads) void k_recheck_plan(const PairDesc* __restrict__ pairs, int npairs,
                                                      const uint32_t* __restrict__ nflag, int64_t slots,
                                                      int64_t* __restrict__ plan) {
-    __shared__ int64_t sh[kPlanThreads];
+    __shared__ int64_t sh[3][kPlanThreads / 64];
     const int t = threadIdx.x;
     const int np1 = npairs + 1;
     int64_t bw = 0, bs = 0, bc = 0, bf = 0;
@@ -387,23 +370,23 @@ __global__ __launch_bounds__(kPlanThreads) void k_recheck_plan(const PairDesc* _
             G = pair_segs(pairs[p]);
         }
         const int64_t cand = (G > 1 && F > 0) ? F * G : 0;
-        int64_t tc, tw, ts, tf;
-        const int64_t ic = block_scan<kPlanThreads>(cand, sh, &tc);
-        const bool seg = cand > 0 && bc + ic <= slots;
-        const int64_t wi = seg ? 0 : F, si = seg ? F * G : 0, fi = seg ? F : 0;
-        const int64_t iw = block_scan<kPlanThreads>(wi, sh, &tw);
-        const int64_t is = block_scan<kPlanThreads>(si, sh, &ts);
-        const int64_t jf = block_scan<kPlanThreads>(fi, sh, &tf);
+        int64_t c[1] = {cand}, tc[1], x[3], tot[3];
+        block_scan<kPlanThreads>(c, sh, tc);
+        const bool seg = cand > 0 && bc + c[0] + cand <= slots;
+        x[0] = seg ? 0 : F;
+        x[1] = seg ? cand : 0;
+        x[2] = seg ? F : 0;
+        block_scan<kPlanThreads>(x, sh, tot);
         if (p < npairs) {
-            plan[p] = bw + iw - wi;
-            plan[np1 + p] = bs + is - si;
-            plan[2 * np1 + p] = bc + ic - cand;
-            plan[3 * np1 + p] = bf + jf - fi;
+            plan[p] = bw + x[0];
+            plan[np1 + p] = bs + x[1];
+            plan[2 * np1 + p] = bc + c[0];
+            plan[3 * np1 + p] = bf + x[2];
         }
-        bw += tw;
-        bs += ts;
-        bc += tc;
-        bf += tf;
+        bw += tot[0];
+        bs += tot[1];
+        bc += tc[0];
+        bf += tot[2];
     }
     if (t == 0) {
         plan[npairs] = bw;
@@ -474,46 +457,61 @@ __device__ void recheck_item(const RecheckArgs& A, int p, int64_t j, int sg0, in
 #pragma unroll
             for (int u = 0; u < kU; ++u) acc[u] = 0.0;
             // this wave's words of the segment: w0, w0 + 4, w0 + 8, w0 + 12
-            const int w0 = sg * kSegWords + wave, we = min(W, (sg + 1) * kSegWords);
+            const int w0 = sg * kSegWords + wave;
+            uint32_t words[kSegWords / kRecheckWaves];
+#pragma unroll
+            for (int i = 0; i < kSegWords / kRecheckWaves; ++i) {
+                const int ww = w0 + kRecheckWaves * i;
+                words[i] = ww < W ? (mk[ww] ^ flip) & item_bits(ww, pd.n, pd.m, pd.ygap) : 0u;
+            }
             int w = w0;
-            auto word_bits = [&](int ww) -> uint32_t {
-                return ww < we ? (mk[ww] ^ flip) & item_bits(ww, pd.n, pd.m, pd.ygap) : 0u;
+            uint32_t U = words[0];
+            auto next_row = [&]() -> int {  // in ascending order; -1: no more
+                while (!U && w < w0 + kSegWords - kRecheckWaves) {
+#pragma unroll
+                    for (int i = 0; i + 1 < kSegWords / kRecheckWaves; ++i) words[i] = words[i + 1];
+                    U = words[0];
+                    w += kRecheckWaves;
+                }
+                if (!U) return -1;
+                const int r = 32 * w + __builtin_ctz(U);
+                U &= U - 1u;
+                return r;
             };
-            uint32_t U = word_bits(w);
-            for (;;) {
-                int rows[kRows];
+            // kRows rows in flight: a row's registers are filled again as soon as
+            // it has been added.  No branch around a load: a row past the last
+            // and a coefficient of a Y row read zero (row_rsrc).
+            int rows[kRows];
+            Tin z[kRows][kU];
+            double kc[kRows];
+            auto fill = [&](int k) {
+                rows[k] = __builtin_amdgcn_readfirstlane(next_row());
+                int i = rows[k] < 0 ? 0 : rows[k];
+                if (i >= pd.n) i -= pd.ygap;  // Y's mask positions to pooled items
+                const bool isx = i < pd.n;
+                const __amdgpu_buffer_rsrc_t ks = row_rsrc(cf + (isx ? i : 0), isx ? 8 : 0);
+                kc[k] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(ks, 0, 0, 0));
+                const Tin* src = (isx ? X + (int64_t)i * d : Y + (int64_t)(i - pd.n) * d) + c0;
+                const __amdgpu_buffer_rsrc_t zs = row_rsrc(src, rows[k] < 0 ? 0 : (int)sizeof(Tin) * (d - c0));
 #pragma unroll
-                for (int k = 0; k < kRows; ++k) {
-                    while (!U && w + kRecheckWaves < we) U = word_bits(w += kRecheckWaves);
-                    if (U) {
-                        rows[k] = 32 * w + __builtin_ctz(U);
-                        U &= U - 1u;
-                    } else {
-                        rows[k] = -1;
-                    }
+                for (int u = 0; u < kU; ++u) {
+                    const int at = (int)sizeof(Tin) * (64 * u + lane);
+                    if constexpr (sizeof(Tin) == 4)
+                        z[k][u] = __builtin_bit_cast(Tin, __builtin_amdgcn_raw_buffer_load_b32(zs, at, 0, 0));
+                    else
+                        z[k][u] = __builtin_bit_cast(Tin, __builtin_amdgcn_raw_buffer_load_b64(zs, at, 0, 0));
                 }
-                if (rows[0] < 0) break;
-                // columns are clamped to the row (no branch around a load)
-                Tin z[kRows][kU];
-                double kc[kRows];
+            };
+#pragma unroll
+            for (int k = 0; k < kRows; ++k) fill(k);
+            while (rows[0] >= 0) {
 #pragma unroll
                 for (int k = 0; k < kRows; ++k) {
-                    int i = rows[k] < 0 ? 0 : rows[k];
-                    if (i >= pd.n) i -= pd.ygap;  // Y's mask positions to pooled items
-                    const bool isx = i < pd.n;
-                    kc[k] = isx ? cf[i] : 0.0;
-                    const Tin* src = isx ? X + (int64_t)i * d : Y + (int64_t)(i - pd.n) * d;
+                    if (rows[k] >= 0) {
 #pragma unroll
-                    for (int u = 0; u < kU; ++u) {
-                        const int col = c0 + 64 * u + lane;
-                        z[k][u] = src[col < d ? col : d - 1];
+                        for (int u = 0; u < kU; ++u) acc[u] += fma(-kc[k], vc[u], (double)z[k][u]);
                     }
-                }
-#pragma unroll
-                for (int k = 0; k < kRows; ++k) {
-                    if (rows[k] < 0) continue;
-#pragma unroll
-                    for (int u = 0; u < kU; ++u) acc[u] += fma(-kc[k], vc[u], (double)z[k][u]);
+                    fill(k);
                 }
             }
             // the segment's sum: the wave sums in wave order
@@ -643,17 +641,33 @@ __device__ __forceinline__ void finish_flag(const RecheckArgs& A, int p, int64_t
     const double* src = A.rseg + (slot0 + j * G) * A.d_pad;
     const double* tp = A.t64 + (int64_t)p * A.d_pad;
     double ssS = 0.0, ssL = 0.0;
-    for (int c0 = 0; c0 < d; c0 += kRecheckPass)
+    for (int c0 = 0; c0 < d; c0 += kRecheckPass) {
+        double sm[kRecheckCols], tc[kRecheckCols];
+        int col[kRecheckCols];
 #pragma unroll
         for (int k = 0; k < kRecheckCols; ++k) {
-            const int cc = t + kRecheckThreads * k;
-            const int col = c0 + cc;
-            if (col < d) {
-                double sm = 0.0;
-                for (int sg = 0; sg < G; ++sg) sm += src[(int64_t)sg * A.d_pad + col];
-                add_squares(sm, tp[col], ssS, ssL);
-            }
+            const int c = c0 + t + kRecheckThreads * k;
+            col[k] = c < d ? c : d - 1;
+            tc[k] = tp[col[k]];
+            sm[k] = 0.0;
         }
+        for (int sg = 0; sg < G; sg += 4) {  // four segments in flight, added in order
+            double x[4][kRecheckCols];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int k = 0; k < kRecheckCols; ++k)
+                    x[u][k] = src[(int64_t)(sg + u < G ? sg + u : G - 1) * A.d_pad + col[k]];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (sg + u < G)  // uniform
+#pragma unroll
+                    for (int k = 0; k < kRecheckCols; ++k) sm[k] += x[u][k];
+        }
+#pragma unroll
+        for (int k = 0; k < kRecheckCols; ++k)
+            if (c0 + t + kRecheckThreads * k < d) add_squares(sm[k], tc[k], ssS, ssL);
+    }
     const double s1 = block_sum(ssS, red), s2 = block_sum(ssL, red);
     if (t == 0) recheck_decide(pd, A.st[p], p, row, s1, s2, d, A.gd, A.alternative, A.cnt, A.Tw);
 }

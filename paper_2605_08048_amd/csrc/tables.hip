@@ -16,29 +16,6 @@ namespace hbt {
 
 constexpr int kTabThreads = 512;
 
-// Exclusive prefix sum over the work-group; every thread gets the total.
-__device__ __forceinline__ int64_t tab_scan(int64_t x, int64_t* sh, int64_t* total) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    long long v = x;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const long long u = __shfl_up(v, o, 64);
-        if (lane >= o) v += u;
-    }
-    __syncthreads();  // the previous scan's readers are done with sh
-    if (lane == 63) sh[wave] = v;
-    __syncthreads();
-    int64_t before = 0, all = 0;
-#pragma unroll
-    for (int q = 0; q < kTabThreads / 64; ++q) {
-        const int64_t t = sh[q];
-        before += q < wave ? t : 0;
-        all += t;
-    }
-    *total = all;
-    return before + v - x;
-}
-
 template <typename T>
 __device__ __forceinline__ T tab_at(const TableArgs& A, int32_t off, int64_t i) {
     return ((const T*)(A.blob + off))[i];
@@ -49,9 +26,9 @@ __device__ __forceinline__ int tab_index(const TableArgs& A, int32_t off, int64_
 }
 
 __global__ __launch_bounds__(kTabThreads) void k_build_tables(TableArgs A) {
-    __shared__ int64_t sh[kTabThreads / 64];
+    constexpr int kScans = 9;  // of a pair
+    __shared__ int64_t sh[kScans][kTabThreads / 64];
     const int t = threadIdx.x;
-    int64_t tot;
     // 1. shared clouds: one run of storage each
     {
         int64_t row = 0, zrow = 0, chunk = 0;
@@ -60,12 +37,12 @@ __global__ __launch_bounds__(kTabThreads) void k_build_tables(TableArgs A) {
             const bool in = c < A.nclouds;
             const int64_t m = in ? tab_at<uint32_t>(A, A.o_cloud_rows, c) : 0;
             const int64_t Np = (m + kRowPad - 1) / kRowPad * kRowPad;
-            const int64_t r = row + tab_scan(m, sh, &tot);
-            row += tot;
-            const int64_t z = zrow + tab_scan(Np, sh, &tot);
-            zrow += tot;
-            const int64_t k = chunk + tab_scan(Np / kSumChunkY, sh, &tot);
-            chunk += tot;
+            int64_t x[3] = {m, Np, Np / kSumChunkY}, tot[3];
+            block_scan<kTabThreads>(x, sh, tot);
+            const int64_t r = row + x[0], z = zrow + x[1], k = chunk + x[2];
+            row += tot[0];
+            zrow += tot[1];
+            chunk += tot[2];
             if (in) {
                 const int64_t first = A.o_offset >= 0 ? tab_at<int64_t>(A, A.o_offset, c) : A.offset0 + r;
                 PairDesc cd = {};
@@ -122,30 +99,31 @@ __global__ __launch_bounds__(kTabThreads) void k_build_tables(TableArgs A) {
         }
         const int64_t nx = in ? (pd.n + kSumChunk - 1) / kSumChunk : 0;
         const int64_t ny = in ? pd.Np / kSumChunkY - pd.n / kSumChunkY : 0;
-        pd.coef0 = coef + tab_scan(pd.n, sh, &tot);
-        coef += tot;
+        const bool big = in && pd.Np > kQuadItems;
+        int64_t x[kScans] = {pd.n, pd.n + pd.m, pd.Np, nx + ny, in ? x_octets(pd.n) : 0,
+                             B, owner == p ? B * pd.Wp : 0, big ? 1 : 0, big ? B : 0}, tot[kScans];
+        block_scan<kTabThreads>(x, sh, tot);
+        pd.coef0 = coef + x[0];
+        coef += tot[0];
         if (!A.nclouds) {
-            const int64_t r = row + tab_scan(pd.n + pd.m, sh, &tot);
-            row += tot;
-            pd.zrow0 = pd.zrow_y = zrow + tab_scan(pd.Np, sh, &tot);
-            zrow += tot;
-            pd.cx0 = (int32_t)(chunk + tab_scan(nx + ny, sh, &tot));
-            chunk += tot;
+            pd.zrow0 = pd.zrow_y = zrow + x[2];
+            pd.cx0 = (int32_t)(chunk + x[3]);
             pd.cx1 = pd.cy0 = (int32_t)(pd.cx0 + nx);
             pd.cy1 = (int32_t)(pd.cx1 + ny);
-            pd.xoct0 = xoct + tab_scan(in ? x_octets(pd.n) : 0, sh, &tot);
-            xoct += tot;
+            pd.xoct0 = xoct + x[4];
             if (in) {
-                const int64_t first = A.o_offset >= 0 ? tab_at<int64_t>(A, A.o_offset, p) : A.offset0 + r;
+                const int64_t first = A.o_offset >= 0 ? tab_at<int64_t>(A, A.o_offset, p) : A.offset0 + row + x[1];
                 pd.X = A.base + first * A.row_bytes;
                 pd.Y = A.base + (first + pd.n) * A.row_bytes;
             }
         }
+        row += tot[1];
+        zrow += tot[2];
+        chunk += tot[3];
+        xoct += tot[4];
         BlockPair b;
-        b.mrow0 = srow + tab_scan(B, sh, &tot);
-        srow += tot;
-        b.mword0 = word + tab_scan(owner == p ? B * pd.Wp : 0, sh, &tot);
-        word += tot;
+        b.mrow0 = srow + x[5];
+        b.mword0 = word + x[6];
         b.perm_base = A.perm_base;
         b.nb = (int32_t)B;
         b.owner = owner;
@@ -154,11 +132,11 @@ __global__ __launch_bounds__(kTabThreads) void k_build_tables(TableArgs A) {
         b.Wp = pd.Wp;
         b.pair_index = pd.pair_index;
         b.ygap = pd.ygap;
-        const bool big = in && pd.Np > kQuadItems;
-        const int64_t kb = nbig + tab_scan(big ? 1 : 0, sh, &tot);
-        nbig += tot;
-        const int64_t rb = bigrow + tab_scan(big ? B : 0, sh, &tot);
-        bigrow += tot;
+        const int64_t kb = nbig + x[7], rb = bigrow + x[8];
+        srow += tot[5];
+        word += tot[6];
+        nbig += tot[7];
+        bigrow += tot[8];
         if (big) {
             A.big_pair[kb] = p;
             A.big_row0[kb] = rb;
@@ -178,22 +156,23 @@ __global__ __launch_bounds__(kTabThreads) void k_build_tables(TableArgs A) {
     if (t == 0 && (A.npairs & 1)) A.nflag[A.npairs] = 0u;  // the odd word (a single pair's ticket)
     // 3. the product's groups: ngw of the wide tiles, then the others, tiles
     //    numbered from 0 in each
-    for (int part = 0; part < 2; ++part) {
-        const int g0 = part ? A.ngw : 0, g1 = part ? A.ngroups : A.ngw;
-        const int width = part ? A.width_narrow : A.width_wide;
-        int64_t tile = 0;
-        for (int gb = g0; gb < g1; gb += kTabThreads) {
-            const int g = gb + t;
-            GemmGroup q = {0, 0, 0};
-            if (g < g1) {
-                q.pair = tab_index(A, A.o_order, g, A.narrow_order);
-                const int64_t B = A.o_splits >= 0 ? tab_at<uint32_t>(A, A.o_splits, q.pair) : A.splits0;
-                q.nbt = (int32_t)((B + width - 1) / width);
-            }
-            q.tile0 = tile + tab_scan((int64_t)q.nbt * A.nslot, sh, &tot);
-            tile += tot;
-            if (g < g1) A.groups[g] = q;
+    int64_t wide = 0, narrow = 0;
+    for (int gb = 0; gb < A.ngroups; gb += kTabThreads) {
+        const int g = gb + t;
+        GemmGroup q = {0, 0, 0};
+        if (g < A.ngroups) {
+            const int width = g < A.ngw ? A.width_wide : A.width_narrow;
+            q.pair = tab_index(A, A.o_order, g, A.narrow_order);
+            const int64_t B = A.o_splits >= 0 ? tab_at<uint32_t>(A, A.o_splits, q.pair) : A.splits0;
+            q.nbt = (int32_t)((B + width - 1) / width);
         }
+        const int64_t tiles = (int64_t)q.nbt * A.nslot;
+        int64_t x[2] = {g < A.ngw ? tiles : 0, g < A.ngw ? 0 : tiles}, tot[2];
+        block_scan<kTabThreads>(x, sh, tot);
+        q.tile0 = g < A.ngw ? wide + x[0] : narrow + x[1];
+        wide += tot[0];
+        narrow += tot[1];
+        if (g < A.ngroups) A.groups[g] = q;
     }
 }
 
