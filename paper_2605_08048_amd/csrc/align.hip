@@ -847,18 +847,6 @@ static hipError_t launch_reflect_t(int precision, const PairDesc* pairs, int npa
     return hipGetLastError();
 }
 
-hipError_t launch_reflect(int input_dtype, int precision, const PairDesc* pairs, int npairs,
-                          int64_t total_octets, const PairState* st, const double* v, int d,
-                          int d_pad, double* coef, void* zstore, int64_t zplane_elems,
-                          float* z32, hipStream_t s) {
-    if (total_octets <= 0) return hipSuccess;
-    if (input_dtype == HBT_IN_F64)
-        return launch_reflect_t<double>(precision, pairs, npairs, total_octets, st, v, d, d_pad,
-                                        coef, zstore, zplane_elems, z32, s);
-    return launch_reflect_t<float>(precision, pairs, npairs, total_octets, st, v, d, d_pad, coef,
-                                   zstore, zplane_elems, z32, s);
-}
-
 // The same reflection and storage for FP32 rows with d a multiple of 4 and
 // 16-byte aligned rows (the condition shared with the vector column sums):
 // one wave per octet, the octet's 8 rows held in registers (lane l: columns
@@ -869,8 +857,8 @@ hipError_t launch_reflect(int input_dtype, int precision, const PairDesc* pairs,
 // Stores one storage octet of a pair: this lane's J x 4 columns of the 8
 // rows row_of(0..7) (pair-relative pooled rows), z_r = x_r - k_r vc in FP64,
 // in the precision's format.  soct is the octet's index in the whole storage.
-template <int PREC, int J, typename RowOf>
-__device__ __forceinline__ void store_octet(const float (&x)[8][J][4], const double (&k)[8],
+template <int PREC, int J, typename Tin, typename RowOf>
+__device__ __forceinline__ void store_octet(const Tin (&x)[8][J][4], const double (&k)[8],
                                             const double (&vc)[J][4], int64_t soct, int64_t zrow0,
                                             RowOf row_of, int o4, int d_pad, void* zstore,
                                             int64_t zplane_elems, float* __restrict__ z32) {
@@ -951,8 +939,10 @@ __device__ __forceinline__ int plane_row(int o4, int k) {
 // The reflection on the 16-byte path: one wave per storage octet of the
 // 32-row groups that hold X rows (x_octets(n) per pair, numbered from
 // PairDesc::xoct0); the groups that hold only Y rows or padding are stored by
-// k_colsum_store4.
-template <int PREC, int J>
+// k_colsum_store4.  ALL (rows that the 16-byte loads do not take): every octet of
+// the storage.  Bound by memory; 64 pairs of 20 to 5000 rows of d = 299 in split
+// BF16, work-groups of one octet that read its rows twice: 150 us, 67 so.
+template <typename Tin, int PREC, int J, bool ALL>
 __global__ __launch_bounds__(256) void k_reflect4(const PairDesc* __restrict__ pairs, int npairs,
                                                   int64_t total_octets,
                                                   const PairState* __restrict__ st,
@@ -963,22 +953,23 @@ __global__ __launch_bounds__(256) void k_reflect4(const PairDesc* __restrict__ p
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int64_t oct = (int64_t)blockIdx.x * 4 + wave + oct0;
     if (oct >= total_octets) return;
-    const int p = upper_index(npairs, oct, [&](int k) { return pairs[k].xoct0; });
+    const int p = ALL ? upper_index(npairs, oct * 8, [&](int k) { return pairs[k].zrow0; })
+                      : upper_index(npairs, oct, [&](int k) { return pairs[k].xoct0; });
     const PairDesc pd = pairs[p];
     const int identity = st[p].identity;
     const double vv = st[p].vv;
     const double* vp = v + (int64_t)p * d_pad;
-    const int lo8 = (int)(oct - pd.xoct0);  // storage octet within the pair
+    const int lo8 = (int)(oct - (ALL ? pd.zrow0 / 8 : pd.xoct0));  // storage octet within the pair
     const int g0 = 32 * (lo8 >> 2), o4 = lo8 & 3;
     const int N = pd.n + pd.m;
     auto row_of = [&](int r) { return g0 + plane_row<PREC>(o4, r); };
     auto col = [&](int j, int e) { return 256 * j + 64 * e + lane; };
-    float x[8][J][4];
+    Tin x[8][J][4];
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
         const int i = row_of(r);  // wave-uniform; a padding row reads Y's last row and keeps zeros
-        const float* row = i < pd.n ? (const float*)pd.X + (int64_t)i * d
-                                    : (const float*)pd.Y + (int64_t)((i < N ? i : N - 1) - pd.n) * d;
+        const Tin* row = i < pd.n ? (const Tin*)pd.X + (int64_t)i * d
+                                  : (const Tin*)pd.Y + (int64_t)((i < N ? i : N - 1) - pd.n) * d;
         load_cols<J>(x[r], row, d, i < N);
     }
     double vc[J][4];
@@ -1029,7 +1020,7 @@ hipError_t launch_reflect_vec(int precision, const PairDesc* pairs, int npairs,
     const int J = (d_pad + 255) / 256;
     const dim3 g((unsigned)((total_octets - oct0 + 3) / 4)), b(256);
 #define HBT_R4(PR, JJ)                                                                         \
-    hipLaunchKernelGGL((k_reflect4<PR, JJ>), g, b, 0, s, pairs, npairs, total_octets, st, v, d, \
+    hipLaunchKernelGGL((k_reflect4<float, PR, JJ, false>), g, b, 0, s, pairs, npairs, total_octets, st, v, d, \
                        d_pad, coef, zstore, zplane_elems, z32, oct0)
 #define HBT_R4J(PR)                            \
     switch (J) {                               \
@@ -1048,6 +1039,44 @@ hipError_t launch_reflect_vec(int precision, const PairDesc* pairs, int npairs,
     }
 #undef HBT_R4J
 #undef HBT_R4
+    return hipGetLastError();
+}
+
+// Rows that the 16-byte path does not take: whole rows in registers where they
+// fit (d <= 1024 in FP32, 512 in FP64), else k_reflect.
+hipError_t launch_reflect(int input_dtype, int precision, const PairDesc* pairs, int npairs,
+                          int64_t total_octets, const PairState* st, const double* v, int d,
+                          int d_pad, double* coef, void* zstore, int64_t zplane_elems,
+                          float* z32, hipStream_t s) {
+    if (total_octets <= 0) return hipSuccess;
+    const bool f64 = input_dtype == HBT_IN_F64;
+    const int J = (d_pad + 255) / 256;
+    if (J > (f64 ? 2 : 4))
+        return f64 ? launch_reflect_t<double>(precision, pairs, npairs, total_octets, st, v, d, d_pad, coef, zstore,
+                                              zplane_elems, z32, s)
+                   : launch_reflect_t<float>(precision, pairs, npairs, total_octets, st, v, d, d_pad, coef, zstore,
+                                             zplane_elems, z32, s);
+    const dim3 g((unsigned)((total_octets + 3) / 4)), b(256);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, g, b, 0, s, pairs, npairs, total_octets, st, v, d, d_pad, coef, zstore, zplane_elems,
+                           z32, (int64_t)0);
+    };
+    auto width = [&](auto prec) {
+        constexpr int PR = decltype(prec)::value;
+        switch (J) {
+            case 1: f64 ? go(k_reflect4<double, PR, 1, true>) : go(k_reflect4<float, PR, 1, true>); break;
+            case 2: f64 ? go(k_reflect4<double, PR, 2, true>) : go(k_reflect4<float, PR, 2, true>); break;
+            case 3: go(k_reflect4<float, PR, 3, true>); break;
+            default: go(k_reflect4<float, PR, 4, true>); break;
+        }
+    };
+    switch (precision) {
+        case HBT_F64: width(std::integral_constant<int, HBT_F64>{}); break;
+        case HBT_F32: width(std::integral_constant<int, HBT_F32>{}); break;
+        case HBT_I8X3: width(std::integral_constant<int, HBT_I8X3>{}); break;
+        case HBT_BF16_E4M3: width(std::integral_constant<int, HBT_BF16_E4M3>{}); break;
+        default: width(std::integral_constant<int, HBT_BF16X2>{}); break;
+    }
     return hipGetLastError();
 }
 
