@@ -331,28 +331,86 @@ __device__ __forceinline__ void colsum4_chunk(const SumChunk& ch, const PairDesc
             }
 }
 
+// hbt_align's column sums of one pair on the 16-byte path.  A CU takes in some
+// 37 GB/s by itself, so the 128 rows of an X chunk, 512 KB at d = 1024, are spread
+// over four work-groups, one to a phase (rows r0 + f, r0 + f + 4, ... of the chunk
+// of k_colsum_store4, in one chain per column); a wave takes 256 columns, and the
+// rows' squares meet in LDS for their test, added as colsum4_chunk adds them.
+// Their sums are added by k_finalize<kFinPhases>, in the order of the four waves of
+// colsum4_chunk.  (n = 3000, m = 2000, d = 1024: 14.3 us with a work-group per
+// chunk, 8.0 so; the finalize step 12.8 and 13.4.)
 template <int J>
 __global__ __launch_bounds__(256) void k_colsum4(const PairDesc* __restrict__ pairs,
                                                  int npairs, int d,
                                                  double* __restrict__ partial,
                                                  int32_t* __restrict__ chunk_bad, const PairTables tab) {
-    __shared__ double red[3][256 * J];
+    constexpr int kRun = kSumChunk / 4;  // rows of a phase
+    __shared__ union {
+        double red[3][256 * J];
+        float sq[kRun][J][64];
+    } sh;
     write_tables(tab);
+    const int b = blockIdx.x;
     PairDesc pd;
-    const SumChunk ch = chunk_of(tab, pairs, npairs, blockIdx.x, &pd);
-    colsum4_chunk<J>(ch, pd, d, partial + (int64_t)blockIdx.x * d, red, chunk_bad + blockIdx.x);
+    SumChunk ch = chunk_of(tab, pairs, npairs, 0, &pd);  // one pair, whose chunks begin at 0
+    double* prow = partial + (int64_t)b * d;
+    if (b >= 4 * pd.cx1) {  // work-group-uniform
+        ch = chunk_of(pd, 0, b - 3 * pd.cx1);
+        colsum4_chunk<J>(ch, pd, d, prow, sh.red, chunk_bad + b);
+        return;
+    }
+    ch = chunk_of(pd, 0, b >> 2);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int r0 = ch.r0 + (b & 3), nr = (ch.r1 - r0 + 3) >> 2;  // this phase's rows (may be none)
+    const float* base = (const float*)pd.X;
+    if (wave < J) {
+        const int c0 = 4 * (lane + 64 * wave);
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int i = 0; i < nr; i += 16) {  // 16 rows in flight
+            u32x4 u[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                const bool in = i + q < nr;
+                const __amdgpu_buffer_rsrc_t rs = row_rsrc(base + (int64_t)(r0 + 4 * (in ? i + q : 0)) * d, in ? 4 * d : 0);
+                u[q] = __builtin_amdgcn_raw_buffer_load_b128(rs, 4 * c0, 0, 0);
+            }
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                if (i + q >= nr) continue;  // uniform: nothing added past the chunk
+                const float4 x = make_float4(__uint_as_float(u[q].x), __uint_as_float(u[q].y),
+                                             __uint_as_float(u[q].z), __uint_as_float(u[q].w));
+                acc[0] += (double)x.x;
+                acc[1] += (double)x.y;
+                acc[2] += (double)x.z;
+                acc[3] += (double)x.w;
+                sh.sq[i + q][wave][lane] = x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (c0 + e < d) prow[c0 + e] = acc[e];
+    }
+    __syncthreads();
+    bool bad = false;
+    for (int i = wave; i < nr; i += 4) {
+        float ss = 0.0f;
+#pragma unroll
+        for (int j = 0; j < J; ++j) ss += sh.sq[i][j][lane];
+        bad |= not_unit((double)wave_total_f32(ss));
+    }
+    bad = __syncthreads_or(bad);
+    if (threadIdx.x == 0) chunk_bad[b] = bad ? 1 : 0;
 }
 
 bool vector_rows_ok(int input_dtype, int d, int d_pad) {
     return input_dtype == HBT_IN_F32 && d % 4 == 0 && d_pad <= 1024;
 }
 
-hipError_t launch_colsum_vec(const PairDesc* pairs, int npairs, int nchunks, int d,
-                             int d_pad, double* partial, int32_t* chunk_bad, hipStream_t s,
-                             const PairTables& tab) {
-    if (nchunks <= 0) return hipSuccess;
+hipError_t launch_colsum_phases(const PairDesc* pairs, int nx, int ny, int d, int d_pad, double* partial,
+                                int32_t* chunk_bad, hipStream_t s, const PairTables& tab) {
+    const int npairs = 1;
     const int J = (d_pad + 255) / 256;
-    const dim3 g(nchunks), b(256);
+    const dim3 g(4 * nx + ny), b(256);
     switch (J) {
         case 1: hipLaunchKernelGGL(k_colsum4<1>, g, b, 0, s, pairs, npairs, d, partial, chunk_bad, tab); break;
         case 2: hipLaunchKernelGGL(k_colsum4<2>, g, b, 0, s, pairs, npairs, d, partial, chunk_bad, tab); break;
@@ -448,7 +506,7 @@ hipError_t launch_fold_coef(const PairDesc* pairs, int npairs, const PairState* 
 // a column's partials as four quarters, each in chunk order; a sum over columns
 // as if by fin_threads(d_pad) threads, thread t taking columns t, t + threads, ...,
 // then a butterfly in each wave, then the waves in order.
-enum FinalizeMode { kFinPair, kFinSplit };
+enum FinalizeMode { kFinPair, kFinSplit, kFinPhases };
 constexpr int kFinCols = 64;
 __host__ __device__ constexpr int fin_threads(int d_pad) { return d_pad >= 1024 ? 1024 : (d_pad + 255) / 256 * 256; }
 
@@ -468,21 +526,35 @@ __global__ __launch_bounds__(256) void k_finalize(
     double* vp = v + (int64_t)p * d_pad;
     double* tp = t64 + (int64_t)p * d_pad;
     float* tq = t32 + (int64_t)p * d_pad;
+    const int extra = MODE == kFinPhases ? 3 * pd.cx1 : 0;  // rows of `partial` that X takes more than its chunks
     // Step 1: sums of X and Y
     auto quarter = [&](int k0, int k1, int q, int c) {
         const int per = (k1 - k0 + 3) / 4, a = k0 + q * per, b = a + per < k1 ? a + per : k1;
         double acc = 0.0;
+        if (MODE == kFinPhases && k0 == pd.cx0) {  // four chunks of four phases in flight
+            for (int k = a; k < b; k += 4) {
+                double t[4][4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int f = 0; f < 4; ++f) t[u][f] = partial[(int64_t)(4 * (k + u < b ? k + u : b - 1) + f) * d + c];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (k + u < b) acc += (t[u][0] + t[u][1]) + (t[u][2] + t[u][3]);
+            }
+            return acc;
+        }
         for (int k = a; k < b; k += 16) {
             double t[16];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) t[u] = partial[(int64_t)(k + u < b ? k + u : b - 1) * d + c];
+            for (int u = 0; u < 16; ++u) t[u] = partial[(int64_t)(extra + (k + u < b ? k + u : b - 1)) * d + c];
 #pragma unroll
             for (int u = 0; u < 16; ++u)
                 if (k + u < b) acc += t[u];  // uniform
         }
         return acc;
     };
-    if constexpr (MODE == kFinSplit) {
+    if constexpr (MODE != kFinPair) {
         const int c = kFinCols * blockIdx.x + lane;
         part[0][wave][lane] = c < d ? quarter(pd.cx0, pd.cx1, wave, c) : 0.0;
         part[1][wave][lane] = c < d ? quarter(pd.cy0, pd.cy1, wave, c) : 0.0;
@@ -503,8 +575,8 @@ __global__ __launch_bounds__(256) void k_finalize(
     constexpr int kSlots = 4;
     const int nt = fin_threads(d_pad);
     int bad = 0;
-    for (int k = pd.cx0 + threadIdx.x; k < pd.cx1; k += 256) bad |= chunk_bad[k];
-    for (int k = pd.cy0 + threadIdx.x; k < pd.cy1; k += 256) bad |= chunk_bad[k];
+    for (int k = pd.cx0 + threadIdx.x; k < pd.cx1 + extra; k += 256) bad |= chunk_bad[k];
+    for (int k = pd.cy0 + extra + threadIdx.x; k < pd.cy1 + extra; k += 256) bad |= chunk_bad[k];
     double x4[kSlots], y4[kSlots], v4[kSlots];
     if constexpr (MODE == kFinPair) {
         auto column = [&](int k0, int k1, int c) {  // four chunks of each quarter in flight
@@ -668,13 +740,15 @@ hipError_t launch_finalize(const PairDesc* pairs, int npairs, const double* part
                            const int32_t* chunk_bad, int d,
                            int d_pad, int align, int gd, double* sxy, PairState* st, double* v,
                            double* t64, float* t32, PairCount* cnt, hbt_result* res, uint32_t* ticket,
-                           hipStream_t s, int p0, float* v32) {
+                           hipStream_t s, int p0, float* v32, bool phases) {
     if (npairs <= 0) return hipSuccess;
     auto go = [&](auto kern, dim3 grid) {
         hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, pairs, partial, chunk_bad, d, d_pad, align, gd, sxy, st, v, t64,
                            t32, cnt, res, p0, v32, ticket);
     };
-    if (npairs <= 8)
+    if (phases)
+        go(k_finalize<kFinPhases>, dim3((d_pad + kFinCols - 1) / kFinCols, npairs));
+    else if (npairs <= 8)
         go(k_finalize<kFinSplit>, dim3((d_pad + kFinCols - 1) / kFinCols, npairs));
     else
         go(k_finalize<kFinPair>, dim3(npairs));

@@ -279,8 +279,10 @@ Workspace carve(const Plan& P, void* ws) {
     w.tiles = c.take<GemmTile>(std::max<size_t>(P.tiles.size(), 1));
     w.groups = c.take<GemmGroup>(std::max<size_t>(P.groups.size(), 1));
     w.Btot = c.take<int64_t>(np);
-    w.partial_sum = c.take<double>(std::max<int64_t>(P.nchunks, 1) * P.d);
-    w.chunk_bad = c.take<int32_t>(std::max<int64_t>(P.nchunks, 1));
+    // (hbt_align: four phases of each X chunk)
+    const int64_t sums = std::max<int64_t>(P.nchunks + (P.need_store ? 0 : 3 * (int64_t)P.pairs[0].cx1), 1);
+    w.partial_sum = c.take<double>(sums * P.d);
+    w.chunk_bad = c.take<int32_t>(sums);
     w.sxy = c.take<double>((size_t)np * 2 * P.d_pad);
     w.st = c.take<PairState>(np);
     w.v = c.take<double>((size_t)np * P.d_pad);
@@ -703,13 +705,14 @@ hbt_status enqueue_prologue(const Plan& P, const Workspace& w, int align, int gd
                                         P.d_pad, w.partial_sum, w.zstore, P.zrows * P.d_pad, w.z32,
                                         w.chunk_bad, s, 0, tab));
     else if (vector_rows(P))
-        HIP_TRY(launch_colsum_vec(w.pairs, P.npairs, (int)P.nchunks, P.d, P.d_pad, w.partial_sum,
-                                  w.chunk_bad, s, tab));
+        HIP_TRY(launch_colsum_phases(w.pairs, P.pairs[0].cx1, (int)P.nchunks - P.pairs[0].cx1, P.d, P.d_pad,
+                                     w.partial_sum, w.chunk_bad, s, tab));
     else
         HIP_TRY(launch_colsum(P.input_dtype, w.pairs, P.npairs, (int)P.nchunks, P.d, P.d_pad,
                               w.partial_sum, w.chunk_bad, s, tab));
     HIP_TRY(launch_finalize(w.pairs, P.npairs, w.partial_sum, w.chunk_bad, P.d, P.d_pad, align, gd, w.sxy, w.st,
-                            w.v, w.t64, w.t32, w.cnt, res, w.ticket, s));
+                            w.v, w.t64, w.t32, w.cnt, res, w.ticket, s, 0, nullptr,
+                            vector_rows(P) && !P.need_store));
     return HBT_OK;
 }
 

@@ -70,7 +70,8 @@ hipError_t launch_finalize(const PairDesc* pairs, int npairs, const double* part
                            double* t64, float* t32, PairCount* cnt, hbt_result* res,
                            uint32_t* ticket,  // a zeroed word per pair (used for up to 8 pairs)
                            hipStream_t s, int p0 = 0,  // pairs [p0, p0 + npairs)
-                           float* v32 = nullptr);      // FP32 copy of v (d_pad per pair), nullable
+                           float* v32 = nullptr,       // FP32 copy of v (d_pad per pair), nullable
+                           bool phases = false);       // sums of launch_colsum_phases
 // coef[coef0 + i] = 2 (v . x_i) / (v . v) (0 when H = I) for the X rows of
 // every pair (FP32 rows), total = sum of n.
 hipError_t launch_fold_coef(const PairDesc* pairs, int npairs, const PairState* st, const double* v, int d,
@@ -80,9 +81,11 @@ hipError_t launch_fold_coef(const PairDesc* pairs, int npairs, const PairState* 
 // 16-byte-load variants for FP32 rows with d % 4 == 0 and d_pad <= 1024 (the
 // caller also checks that every X, Y is 16-byte aligned).
 bool vector_rows_ok(int input_dtype, int d, int d_pad);
-hipError_t launch_colsum_vec(const PairDesc* pairs, int npairs, int nchunks, int d,
-                             int d_pad, double* partial, int32_t* chunk_bad, hipStream_t s,
-                             const PairTables& tab = {});
+// One pair of nx X chunks and ny Y chunks, whose X sums come by phase: rows 4 k + f
+// of partial (and chunk_bad) for phase f of X chunk k, then the Y chunks'
+// (launch_finalize with `phases`).
+hipError_t launch_colsum_phases(const PairDesc* pairs, int nx, int ny, int d, int d_pad, double* partial,
+                                int32_t* chunk_bad, hipStream_t s, const PairTables& tab = {});
 // Column sums plus the storage of the 32-row groups that hold no X rows (the
 // 16-byte path of the group-sum calls); launch_reflect_vec then takes the
 // x_octets(n) octets of each pair (total_octets = their sum over pairs).
