@@ -380,9 +380,8 @@ def main():
               "groupsum_frac_fp32_peak": algo_flops / (g32 * 1e-3) / 1e12 / FP32_PEAK_TFLOPS,
               "speedup_bf16x2_over_fp32": value / v32,
               "pairs_with_equal_counts": f"{agree}/{P}",
-              "kernel": "k_groupsum_fp<float>: v_mfma_f32_16x16x4f32, 64x64 wave tiles, operands loaded "
-                        "from global memory without LDS staging (a comparison path, not tuned like the "
-                        "split-BF16 kernel)"}
+              "kernel": "k_groupsum_fp<float>: v_mfma_f32_16x16x4f32, 64x64 wave tiles, the 64 columns of "
+                        "Z staged in LDS once per work-group (a comparison path)"}
 
     i8 = None
     if args.i8_steps > 0:

@@ -499,7 +499,8 @@ hipError_t launch_fold_coef(const PairDesc* pairs, int npairs, const PairState* 
 // Y's, and the last of the pair's work-groups to end does the rest (they count
 // themselves on the pair's ticket, each after its sums are visible to the whole
 // device; nobody waits for anybody).  One pair of 103 chunks: 16 us, against 32
-// with one work-group.  512 pairs, d = 768: 75 us with kFinPair, 1180 with
+// with one work-group.  kFinPhases is kFinSplit on sums of launch_colsum_phases, X's
+// chunks by their four phases.  512 pairs, d = 768: 75 us with kFinPair, 1180 with
 // kFinSplit, whose fences write back caches full of other pairs' rows, 177 as two
 // launches.
 // Both sum in one order, so a pair's results do not depend on the call it is in:
@@ -1155,7 +1156,7 @@ hipError_t launch_reflect(int input_dtype, int precision, const PairDesc* pairs,
 }
 
 // Column sums and, in the same pass, the Z storage of the Y rows (16-byte
-// path, group-sum calls).  X chunks are summed as in k_colsum4.  A Y chunk is
+// path, group-sum calls).  X chunks are summed by colsum4_chunk.  A Y chunk is
 // one 32-row group of the storage: wave w loads octet w (the 8 rows
 // plane_row(w, .) of the group), adds its Y rows to the sums and stores the
 // octet as it is (H leaves Y unchanged; rows past n + m are the zero

@@ -1246,7 +1246,7 @@ hbt_status hbt_perm_test(const void* X, const void* Y, const hbt_perm_params* pr
         // The recheck counter (with a ticket behind it), the split status and
         // the alignment's ticket are adjacent too and are cleared with it.  The
         // column sums write and clear them where nothing runs before or beside
-        // them (n = 100, m = 80, d = 64, B = 1000: 70 us a call with a
+        // them (n = 50, m = 60, d = 64, B = 999: 70 us a call with a
         // kernel of its own for that, 65 so).
         StageTimer t_(HBT_STAGE_OTHER, s);
         const BlockPair bq = block_pair(0, 0, prm->perm_offset, nb0, 0, pd);

@@ -675,7 +675,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // wave's serial K-loop, where the tiles of JB = 4 would leave CUs without one.
 // (n = 2000, m = 1500, d = 768 in float: a whole tile alone on a CU takes 263 us,
 // quarters 66 each where there are several; so 180 tiles take 198 us as quarters,
-// 263 whole, and 240 tiles 265 and 263.  n = 100, m = 80, d = 64, B = 1000 in
+// 263 whole, and 240 tiles 265 and 263.  n = 50, m = 60, d = 64, B = 999 in
 // double, 4 tiles: 8.2 us, 24 as whole tiles with operands from memory.)
 // ---------------------------------------------------------------------------
 template <typename T>

@@ -690,7 +690,7 @@ __global__ __launch_bounds__(kRecheckThreads) void k_recheck_finish(RecheckArgs 
 // count themselves on `ticket`, and the last of them (the first where there are
 // none) ends the pair.  Each counts after its own results are visible to the
 // whole device; nobody waits for anybody.  Bound by its launch where there are
-// few flags: n = 100, m = 80, d = 64, B = 1000, 65 to 61 us a
+// few flags: n = 50, m = 60, d = 64, B = 999, 65 to 61 us a
 // call against two kernels; n = 777, m = 1333, d = 301, B = 5003, 150 to 140.
 template <typename Tin>
 __global__ __launch_bounds__(kRecheckThreads) void k_recheck_one(RecheckArgs A, PairEnd E, uint32_t* ticket) {
