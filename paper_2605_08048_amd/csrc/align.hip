@@ -561,9 +561,9 @@ __global__ __launch_bounds__(256) void k_finalize(
         part[1][wave][lane] = c < d ? quarter(pd.cy0, pd.cy1, wave, c) : 0.0;
         __syncthreads();
         if (wave < 2)
-            (wave ? sy : sx)[c] = (part[wave][0][lane] + part[wave][1][lane]) + (part[wave][2][lane] + part[wave][3][lane]);
-        // the work-group's sums (the barrier), then device-wide (thread 0's
-        // release); the other work-groups' sums likewise through its acquire
+            store_shared(&(wave ? sy : sx)[c], (part[wave][0][lane] + part[wave][1][lane]) +
+                                                   (part[wave][2][lane] + part[wave][3][lane]));
+        stores_done();  // every wave's sums are there before thread 0 counts the work-group
         __syncthreads();
         if (threadIdx.x == 0)
             before = __hip_atomic_fetch_add(&ticket[p], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
@@ -614,8 +614,8 @@ __global__ __launch_bounds__(256) void k_finalize(
 #pragma unroll
         for (int j = 0; j < kSlots; ++j) {
             const int c = threadIdx.x + 256 * j;
-            x4[j] = c < d_pad ? sx[c] : 0.0;
-            y4[j] = c < d_pad ? sy[c] : 0.0;
+            x4[j] = c < d_pad ? load_shared(sx + c) : 0.0;
+            y4[j] = c < d_pad ? load_shared(sy + c) : 0.0;
         }
     }
     auto columns = [&](auto f) {  // f(slot, c, x, y, v) of each column; f may set v
@@ -624,7 +624,10 @@ __global__ __launch_bounds__(256) void k_finalize(
             const int c0 = threadIdx.x + 256 * j;
             if (256 * j >= nt) continue;
             if (c0 < d_pad) f(j, c0, x4[j], y4[j], v4[j]);
-            for (int c = c0 + nt; c < d_pad; c += nt) f(j, c, sx[c], sy[c], vp[c]);
+            for (int c = c0 + nt; c < d_pad; c += nt) {
+                if (MODE == kFinPair) f(j, c, sx[c], sy[c], vp[c]);
+                else f(j, c, load_shared(sx + c), load_shared(sy + c), vp[c]);
+            }
         }
     };
     // sums of x (and of y) over the slots of all threads; every thread gets them

@@ -373,6 +373,18 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* p, int by
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, bytes, 0x00020000);
 }
 
+// Values that other work-groups of the same kernel read: stored to and loaded from
+// where every XCD sees them.  A barrier alone does not wait for the stores of the
+// work-group's other waves, and one thread's release covers its own wave's only: each
+// wave waits for its stores (stores_done) before the barrier that precedes the count.
+__device__ __forceinline__ void store_shared(double* p, double x) {
+    __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double load_shared(const double* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Exclusive prefix sums of K values a thread over a work-group of NT threads, and
 // their totals: scans of the waves by DPP row shifts and row broadcasts, then of
 // their totals through LDS, with one pair of barriers for all K (the scans of one

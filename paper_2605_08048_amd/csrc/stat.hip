@@ -346,7 +346,7 @@ __device__ void recheck_decide(const PairDesc& pd, const PairState& q, int p, in
     const double thr = (two ? fabs(q.t_obs) : q.t_obs) - q.tau;
     if (T != T || val >= thr) atomicAdd(&cnt[p].count, 1ull);
     atomicAdd(&cnt[p].n_recheck, 1ull);
-    Tw[row] = T;
+    store_shared(&Tw[row], T);
 }
 
 // The work plan (one work-group), four arrays of npairs + 1 int64 in `plan`:
@@ -527,7 +527,7 @@ __device__ void recheck_item(const RecheckArgs& A, int p, int64_t j, int sg0, in
                 if (whole)
                     tot[k] += sm;
                 else if (c0 + cc < d)
-                    A.rseg[(slot + sg) * A.d_pad + c0 + cc] = sm;
+                    store_shared(&A.rseg[(slot + sg) * A.d_pad + c0 + cc], sm);
             }
             __syncthreads();
         }
@@ -633,6 +633,8 @@ hipError_t launch_pair_end(int npairs, const PairEnd& end, hipStream_t s) {
 
 // The segmented flags: sigma_small from the segment sums in segment order,
 // then the same squares, statistic and decision as a whole item.
+// SameKernel: other work-groups of this kernel stored the sums.
+template <bool SameKernel>
 __device__ __forceinline__ void finish_flag(const RecheckArgs& A, int p, int64_t j, int64_t slot0, double* red) {
     const int t = threadIdx.x, d = A.d;
     const PairDesc pd = A.pairs[p];
@@ -657,7 +659,10 @@ __device__ __forceinline__ void finish_flag(const RecheckArgs& A, int p, int64_t
             for (int u = 0; u < 4; ++u)
 #pragma unroll
                 for (int k = 0; k < kRecheckCols; ++k)
-                    x[u][k] = src[(int64_t)(sg + u < G ? sg + u : G - 1) * A.d_pad + col[k]];
+                {
+                    const double* at = src + (int64_t)(sg + u < G ? sg + u : G - 1) * A.d_pad + col[k];
+                    x[u][k] = SameKernel ? load_shared(at) : *at;
+                }
 #pragma unroll
             for (int u = 0; u < 4; ++u)
                 if (sg + u < G)  // uniform
@@ -680,7 +685,7 @@ __global__ __launch_bounds__(kRecheckThreads) void k_recheck_finish(RecheckArgs 
     const int64_t NF = fpre[A.npairs];
     for (int64_t qf = blockIdx.x; qf < NF; qf += gridDim.x) {
         const int p = upper_index(A.npairs, qf, [&](int k) { return fpre[k]; });
-        finish_flag(A, p, qf - fpre[p], spl[p], red);
+        finish_flag<false>(A, p, qf - fpre[p], spl[p], red);
     }
 }
 
@@ -710,13 +715,15 @@ __global__ __launch_bounds__(kRecheckThreads) void k_recheck_one(RecheckArgs A, 
         const int sg = seg ? (int)(it % G) : 0;
         recheck_item<Tin>(A, 0, j, sg, seg ? sg + 1 : G, !seg, part, red);
         if (!seg) continue;
-        __syncthreads();  // every thread's sums
+        stores_done();  // every wave's sums are there before thread 0 counts the item
+        __syncthreads();
         if (threadIdx.x == 0)
             before = (uint32_t)__hip_atomic_fetch_add((unsigned long long*)&A.Tw[A.flags[A.bp[0].mrow0 + j]], 1ull,
                                                       __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
-        if (before == (uint32_t)(G - 1)) finish_flag(A, 0, j, 0, red);
+        if (before == (uint32_t)(G - 1)) finish_flag<true>(A, 0, j, 0, red);
     }
+    stores_done();
     __syncthreads();  // thread 0 decided the last flag, whose T_b the others read
     if (busy > 1) {
         if (threadIdx.x == 0)
