@@ -208,7 +208,7 @@ def _input_dtype(X):
 
 def results_to_numpy(res_tensor):
     host = res_tensor.cpu()
-    r = host.reshape(-1).numpy().view(RESULT_DTYPE)
+    r = np.ascontiguousarray(host.numpy()).reshape(-1).view(RESULT_DTYPE)
     return r.copy() if host is res_tensor else r
 
 
