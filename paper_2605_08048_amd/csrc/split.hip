@@ -625,6 +625,13 @@ hipError_t launch_split_masks(const BlockPair* bp, int npairs,
     if (total_rows < rows) total_rows = rows;
     const size_t share = wg_per_cu > 0 ? lds_per_cu() / (size_t)wg_per_cu : 0;
     const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+    // At most 64 KB of LDS per work-group (of four split rows): the one limit of calls of
+    // every size, checked before either kernel; a cap of one or two work-groups per CU
+    // is past it.
+    const SplitLds L(max_np);
+    size_t lds = (size_t)kSplitWaves * L.total;
+    if (share > lds + kSplitStaticLds) lds = share - kSplitStaticLds;
+    if (lds + kSplitStaticLds > 65536 || lds + kSplitStaticLds > split_lds_limit()) return hipErrorInvalidValue;
     const dim3 block(64 * kSplitWaves);
     const double ppr = (double)npairs / (double)total_rows;
     if (min_np <= kQuadItems) {
@@ -639,11 +646,6 @@ hipError_t launch_split_masks(const BlockPair* bp, int npairs,
         else go(k_split_quads<kQuadRounds>, kQuadRounds);
         if (max_np <= kQuadItems) return hipGetLastError();
     }
-    const SplitLds L(max_np);
-    // four split rows per work-group; at most 64 KB of LDS per work-group
-    size_t lds = (size_t)kSplitWaves * L.total;
-    if (share > lds + kSplitStaticLds) lds = share - kSplitStaticLds;
-    if (lds + kSplitStaticLds > 65536 || lds + kSplitStaticLds > split_lds_limit()) return hipErrorInvalidValue;
     const int skip_wp = min_np <= kQuadItems ? kQuadItems / 32 : 0;
     if (!skip_wp) big = SplitBig{};
     double per_row = ppr;
