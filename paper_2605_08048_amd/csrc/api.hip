@@ -394,7 +394,7 @@ void add_pair(Plan& P, const void* X, const void* Y, int64_t n, int64_t m, uint3
     P.xoct += x_octets(n);
     P.zrows += pd.Np;
     P.ncoef += n;
-    P.min_np = P.npairs ? std::min(P.min_np, (int)pd.Np) : (int)pd.Np;
+    P.min_np = P.pairs.empty() ? (int)pd.Np : std::min(P.min_np, (int)pd.Np);
     P.max_np = std::max(P.max_np, (int)pd.Np);
     P.pairs.push_back(pd);
     P.npairs = (int)P.pairs.size();
@@ -1417,7 +1417,7 @@ static bool plan_clouds(Plan& P, int64_t nclouds, const void* Z_all, const int64
         pd.cy0 = cy.cx1;
         pd.cy1 = cy.cy1;
         P.ncoef += pd.n;
-        P.min_np = P.npairs ? std::min(P.min_np, (int)pd.Np) : (int)pd.Np;
+        P.min_np = P.pairs.empty() ? (int)pd.Np : std::min(P.min_np, (int)pd.Np);
         P.max_np = std::max(P.max_np, (int)pd.Np);
         P.fold_segs = std::max(P.fold_segs, fold_segments(pd.n));
         P.pairs.push_back(pd);
