@@ -279,8 +279,10 @@ Workspace carve(const Plan& P, void* ws) {
     w.tiles = c.take<GemmTile>(std::max<size_t>(P.tiles.size(), 1));
     w.groups = c.take<GemmGroup>(std::max<size_t>(P.groups.size(), 1));
     w.Btot = c.take<int64_t>(np);
-    // (hbt_align: four phases of each X chunk)
-    const int64_t sums = std::max<int64_t>(P.nchunks + (P.need_store ? 0 : 3 * (int64_t)P.pairs[0].cx1), 1);
+    // (hbt_align: four phases of each X chunk where FP32 rows may take 16-byte loads; the
+    // size query knows neither the dtype nor the addresses)
+    const bool phases = !P.need_store && vector_rows_ok(HBT_IN_F32, P.d, P.d_pad);
+    const int64_t sums = std::max<int64_t>(P.nchunks + (phases ? 3 * (int64_t)P.pairs[0].cx1 : 0), 1);
     w.partial_sum = c.take<double>(sums * P.d);
     w.chunk_bad = c.take<int32_t>(sums);
     w.sxy = c.take<double>((size_t)np * 2 * P.d_pad);
