@@ -352,8 +352,10 @@ hbt_status hbt_stage_times(double* ms, int64_t* launches);
  *               launch (default 16);
  *   grid_narrow the same for the 256-split split-BF16 launch (default 32) or
  *               the int8-plane launch (default 16);
- *   split_cap   split-stage work-groups per compute unit while it runs
- *               beside the alignment (default 6);
+ *   split_cap   split-stage work-groups per compute unit, to leave room for
+ *               the alignment beside it (default 6; calls with 1 or 2 are
+ *               refused with HBT_ERR_DEVICE: a work-group's share of the
+ *               compute unit's LDS would pass 64 KB);
  *   chunks      pipeline chunks of the batched call (default 1; see
  *               hbt_pipeline_chunks).
  * No result depends on any of them.

@@ -101,8 +101,8 @@ __device__ __forceinline__ void load_cols(Tin (&x)[J][4], const Tin* row, int d,
 // Sum of x over the 64 lanes, returned to every lane: each adds the values of
 // lanes l ^ 32, l ^ 16, ..., l ^ 1 (as __shfl_xor would, through LDS), which
 // reach it by a swap of two registers' halves or rows, or by DPP.  (Bound by its
-// latency: the finalize step of d = 1024, three such sums in a chain, took 16.5 us
-// with five of them by __shfl_xor, 12.7 so.)
+// latency: three such sums in a chain in the finalize step of one pair of d = 1024
+// took 12.7 us, five of them by __shfl_xor 16.5.)
 __device__ __forceinline__ double wave_sum_f64(double x) {
     typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
     auto join = [](uint32_t lo, uint32_t hi) {
@@ -428,7 +428,7 @@ hipError_t launch_colsum_phases(const PairDesc* pairs, int nx, int ny, int d, in
 // kFoldRows consecutive rows, all in flight, against v in registers, which it
 // loads again where its rows pass from one pair to the next.  Bound by the loads
 // and, beside the split kernel, by its share of the CUs: 512 pairs of 20 to 5000
-// rows of d = 768, 850 to 920 us with one row a wave and v read for each, 325 so.
+// rows of d = 768, 850 to 920 us with one row a wave and v read for each, 212 so.
 // ---------------------------------------------------------------------------
 constexpr int kFoldRows = 4;  // 8 take more registers than the split kernel's waves leave
 template <int J>
@@ -491,16 +491,16 @@ hipError_t launch_fold_coef(const PairDesc* pairs, int npairs, const PairState* 
 // ---------------------------------------------------------------------------
 // finalize: one work-group per pair
 // ---------------------------------------------------------------------------
-// Bound by the memory rate of the CUs that read the chunk partials (103 chunks at
-// d = 1024 are 844 KB).  kFinPair, for batches, where the pairs fill the chip: one
+// Bound by the memory rate of the CUs that read the chunk partials (n = 3000, m =
+// 2000, d = 1024: 91 chunks, 745 KB).  kFinPair, for batches, where the pairs fill the chip: one
 // work-group per pair, a column of a thread after the other, few registers (the
 // split kernel's waves share the CUs).  kFinSplit, for few pairs: work-group
 // (x, p) adds 64 columns of pair p, wave w the w-th quarter of X's chunks and of
 // Y's, and the last of the pair's work-groups to end does the rest (they count
 // themselves on the pair's ticket, each after its sums are visible to the whole
-// device; nobody waits for anybody).  One pair of 103 chunks: 16 us, against 32
-// with one work-group.  kFinPhases is kFinSplit on sums of launch_colsum_phases, X's
-// chunks by their four phases.  512 pairs, d = 768: 75 us with kFinPair, 1180 with
+// device; nobody waits for anybody).  That pair: 13 to 14 us alone, 14 to 16 beside
+// its splits, against 32 with one work-group.  kFinPhases is kFinSplit on sums of launch_colsum_phases, X's
+// chunks by their four phases.  512 pairs, d = 768: 70 us with kFinPair, 1180 with
 // kFinSplit, whose fences write back caches full of other pairs' rows, 177 as two
 // launches.
 // Both sum in one order, so a pair's results do not depend on the call it is in:
@@ -1275,7 +1275,7 @@ hipError_t launch_colsum_store_vec(int precision, const PairDesc* pairs, int npa
 // hbt_align's output: X' = H X in the input dtype, one wave per row.  Rows of
 // d <= 256 J are read once and kept in registers; J = 0, any d, reads them twice.
 // Bound by the latency of a row's loads and its sum over the wave: n = 3000,
-// d = 1024, float, 11.5 us reading them twice, 7.1 so.
+// d = 1024, float, 11.5 us reading them twice, 6.1 so.
 // ---------------------------------------------------------------------------
 template <typename Tin, int J>
 __global__ __launch_bounds__(256) void k_reflect_out(const PairDesc* __restrict__ pair,

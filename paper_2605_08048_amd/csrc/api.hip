@@ -718,10 +718,11 @@ hbt_status enqueue_prologue(const Plan& P, const Workspace& w, int align, int gd
     return HBT_OK;
 }
 
-// A second stream per device for work that runs beside the caller's stream
-// within one call (default priority, created on first use and kept), and the
-// events that fork it from the caller's stream and join it back.  Both are
-// stream-ordered, so a captured call records them as graph edges.
+// Two side streams per device for work that runs beside the caller's stream
+// within one call (default priority, created on first use and kept): 0 for the
+// splits, 1 for long tile lists or a pipelined call's product; and the events that
+// fork them from the caller's stream and join them back.  All are stream-ordered,
+// so a captured call records them as graph edges.
 std::mutex g_side_mu;
 hipStream_t g_side[2][64];
 

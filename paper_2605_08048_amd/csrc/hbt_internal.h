@@ -389,7 +389,7 @@ __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)
 // their totals: scans of the waves by DPP row shifts and row broadcasts, then of
 // their totals through LDS, with one pair of barriers for all K (the scans of one
 // work-group are a chain of latencies: 10 of them, one at a time through LDS
-// shuffles, made the tables of 64 pairs 8.7 us instead of 6.5, of 1024 pairs 20
+// shuffles, made the tables of 64 pairs 8.7 us instead of 6.1, of 1024 pairs 20
 // instead of 16, and the recheck plan 8 to 10 instead of 4.6 to 6.5).
 template <int NT, int K>
 __device__ __forceinline__ void block_scan(int64_t (&x)[K], int64_t (*sh)[NT / 64], int64_t (&total)[K]) {
